@@ -1269,33 +1269,25 @@ size_t snapshot_segment_bytes(const sg_desc *d, int32_t max_shots, int32_t ckpt_
     return sizeof(float) * (size_t)L.K * L.nsnap * L.field;
 }
 
-// Stability of the velocities (read back from the device; one
-// synchronisation of s): positive and finite, 0 < vs < vp and rho > 0 for
-// elastic models, the leapfrog limit of the scheme with a 5 % margin, and
-// the damping limit of the acoustic layer.
+// Stability of the velocities (their range is reduced on the device into
+// *range, a device scratch slot, and read back; one synchronisation of s):
+// positive and finite, 0 < vs < vp and rho > 0 for elastic models, the
+// leapfrog limit of the scheme with a 5 % margin, and the damping limit of
+// the acoustic layer.
 int check_velocities(const sg_desc *d, const Layout &L, const float *vp, const float *vs, const float *rho,
-                     hipStream_t s)
+                     ParamRange *range, hipStream_t s)
 {
     const bool elastic = d->physics == SG_ELASTIC;
-    // stability: velocity range from the device copy
-    const size_t nphys = (size_t)d->nmodels * d->nx * (d->ndim == 3 ? d->ny : 1) * d->nz;
-    std::vector<float> hv(nphys);
-    HIPCHECK(hipMemcpyAsync(hv.data(), vp, sizeof(float) * nphys, hipMemcpyDeviceToHost, s));
+    const long long nphys = (long long)d->nmodels * d->nx * (d->ndim == 3 ? d->ny : 1) * d->nz;
+    launch_param_range(vp, elastic ? vs : nullptr, rho, nphys, range, s);
+    HIPCHECK(hipGetLastError());
+    ParamRange r{};
+    HIPCHECK(hipMemcpyAsync(&r, range, sizeof r, hipMemcpyDeviceToHost, s));
     HIPCHECK(hipStreamSynchronize(s));
-    float vmax = hv[0];
-    for (float v : hv) {
-        if (!(v > 0) || !std::isfinite(v)) return fail(SG_EINVAL, "velocity must be positive and finite");
-        vmax = std::max(vmax, v);
-    }
-    if (elastic) {
-        std::vector<float> hs(nphys), hr(nphys);
-        HIPCHECK(hipMemcpyAsync(hs.data(), vs, sizeof(float) * nphys, hipMemcpyDeviceToHost, s));
-        HIPCHECK(hipMemcpyAsync(hr.data(), rho, sizeof(float) * nphys, hipMemcpyDeviceToHost, s));
-        HIPCHECK(hipStreamSynchronize(s));
-        for (size_t i = 0; i < nphys; ++i)
-            if (!(hs[i] > 0) || !(hs[i] < hv[i]) || !(hr[i] > 0) || !std::isfinite(hr[i]))
-                return fail(SG_EINVAL, "elastic model needs 0 < vs < vp and rho > 0");
-    }
+    if (r.bad & PARAM_BAD_VP) return fail(SG_EINVAL, "velocity must be positive and finite");
+    if (r.bad & PARAM_BAD_ELASTIC) return fail(SG_EINVAL, "elastic model needs 0 < vs < vp and rho > 0");
+    float vmax;
+    std::memcpy(&vmax, &r.vmax_bits, sizeof vmax);
     if (elastic || L.ad2) {
         // 4th-order staggered leapfrog: v dt/dx <= 1/(sqrt(ndim) (9/8 + 1/24))
         // (divergence form: the half-node coefficient never exceeds vmax^2)
@@ -1336,7 +1328,10 @@ int init_model(const sg_desc *d, const float *vp, const float *vs, const float *
     if ((uintptr_t)ws % ALIGN) return fail(SG_EINVAL, "workspace must be %zu-byte aligned", ALIGN);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
 
-    if (const int e = check_velocities(d, L, vp, vs, rho, s)) return e;
+    // the range goes through the misfit's partial sums, which hold nothing between calls
+    if (const int e = check_velocities(d, L, vp, vs, rho,
+                                       reinterpret_cast<ParamRange *>(static_cast<char *>(ws) + L.off_part), s))
+        return e;
     const double zmax = d->npml > 0 ? 3.0 * d->pml_vmax * std::log(1.0 / d->pml_R) / (2.0 * d->npml * d->dx) : 0.0;
 
     sg_model *m = new sg_model();
@@ -1520,7 +1515,7 @@ int update_model(sg_model *m, const float *vp, const float *vs, const float *rho
     if (elastic && (!vs || !rho)) return fail(SG_EINVAL, "elastic models need vs and rho");
     if (!vp) return fail(SG_EINVAL, "vp must be a device pointer");
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    if (const int e = check_velocities(d, L, vp, vs, rho, s)) return e;
+    if (const int e = check_velocities(d, L, vp, vs, rho, reinterpret_cast<ParamRange *>(m->partials), s)) return e;
     if (elastic) launch_el2_prep(L.g2, d->nmodels, vp, vs, rho, m->model, m->model + 5, s);
     else if (L.ad2) launch_ad2_prep(L.g2, d->nmodels, vp, d->dt, d->dx, m->chat, m->cpad, s);
     else if (d->ndim == 2) launch_ac2_prep(L.g2, d->nmodels, vp, d->dt, d->dx, m->chat, m->cpad, s);

@@ -158,6 +158,15 @@ int noalloc_scratch(double **out);
 // flag (nullable): set to 1 when J comes out non-finite, left alone otherwise.
 void launch_misfit(const float *pred, const float *obs, long long n, float *resid,
                    double *partials, int nparts, double *J, int *flag, hipStream_t s);
+// Range of a model's parameters (see launch_param_range).
+enum : unsigned { PARAM_BAD_VP = 1u, PARAM_BAD_ELASTIC = 2u };
+struct ParamRange {
+    unsigned vmax_bits;   // largest valid vp, as float bits
+    unsigned bad;         // PARAM_BAD_*
+};
+// *out (DEVICE, cleared first) = the range of n cells; vs, rho NULL for acoustic models.
+void launch_param_range(const float *vp, const float *vs, const float *rho, long long n, ParamRange *out,
+                        hipStream_t s);
 void launch_dot(const float *x, const float *y, long long n, double *out, hipStream_t s);
 void launch_ricker(double f0, double t0, double dt, int nt, float *out, hipStream_t s);
 
