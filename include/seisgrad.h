@@ -284,8 +284,9 @@ SG_API int set_time_blocking(sg_model *m, int32_t steps);
  *   SG_TUNE_CHUNK_FWD3     planes per z chunk of the 3-D forward tile passes;
  *   SG_TUNE_CHUNK_ADJ3     planes per z chunk of the 3-D adjoint tile passes;
  *   SG_TUNE_CHUNK_LAYER3   planes per work item of the 3-D layer passes
- *                          (3-D chunks: 16 to 64, multiples of 8; defaults
- *                          32, 64, 32);
+ *                          (3-D chunks: 16 to 64, multiples of 8; until set,
+ *                          32 and 64 in the tile passes, shorter on grids
+ *                          of few tiles, and 16);
  *   SG_TUNE_PAIR           2-D acoustic with time blocking: 1 (the default)
  *                          launches the step of the tiles by the layer with
  *                          the two-step launch of the blocked tiles as one

@@ -1027,6 +1027,14 @@ __global__ void ac3_finalize_kernel(Grid3 g, int nmodels, const float *acc, cons
 
 } // namespace
 
+int chunk3(int setting, int def, int fill, int ntl, int NZ, int nshots)
+{
+    if (setting > 0) return setting;
+    int c = def;
+    while (c > TZC_AUTO_MIN && (long long)ntl * nshots * ((NZ + c - 1) / c) < fill) c /= 2;
+    return c;
+}
+
 void launch_ac3_phi(const Ac3PhiArgs &a, int nshots, hipStream_t s)
 {
     if (a.g.P == 0 || nshots == 0 || a.nitems == 0) return;
@@ -1050,6 +1058,7 @@ void launch_ac3_fwd_part(Ac3FwdArgs a, int t0, int ntl, hipStream_t s)
     a.t0 = t0;
     a.ntl = ntl;
     if (ntl == 0 || a.nshots == 0) return;
+    a.g.zcf = chunk3(a.g.zcf, TZCF_DEF, FILL3_FWD, ntl, a.g.NZ, a.nshots);
     const int nb = band_per(ntl) * NXCD * ((a.g.NZ + a.g.zcf - 1) / a.g.zcf) * a.nshots;
     const bool snap = a.snap != nullptr, rec = a.seis != nullptr;
     if (snap) { if (rec) ac3_fwd_kernel<true, true, LAYER><<<nb, NTH3, 0, s>>>(a); else ac3_fwd_kernel<true, false, LAYER><<<nb, NTH3, 0, s>>>(a); }
@@ -1071,7 +1080,9 @@ void launch_ac3_adj(const Ac3AdjArgs &a, hipStream_t s)
         b.t0 = part ? a.nnear : 0;
         b.ntl = part ? nxy - a.nnear : a.nnear;
         if (b.ntl == 0 || a.nshots == 0) continue;
-        const int nb = band_per(b.ntl) * NXCD * a.g.nzc * a.nshots;
+        b.g.zca = chunk3(a.g.zca, TZCA_DEF, FILL3_ADJ, b.ntl, a.g.NZ, a.nshots);
+        b.g.nzc = (a.g.NZ + b.g.zca - 1) / b.g.zca;
+        const int nb = band_per(b.ntl) * NXCD * b.g.nzc * a.nshots;
         if (part) ac3_adj_kernel<false><<<nb, NTH3, 0, s>>>(b);
         else ac3_adj_kernel<true><<<nb, NTH3, 0, s>>>(b);
     }

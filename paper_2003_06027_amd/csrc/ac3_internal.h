@@ -10,8 +10,11 @@ namespace sg {
 // z over chunks of planes with register windows along z.  The chunk lengths
 // are run-time settings of a model (set_tuning; Grid3.zcf, zca and the
 // layer work list), between TZC_MIN and TZC planes; the defaults are below:
-// the forward passes and the layer work items take shorter chunks than the
-// adjoint, whose longer march re-reads fewer window planes.
+// the forward passes take shorter chunks than the adjoint, whose longer
+// march re-reads fewer window planes.  The layer items are the shortest: a
+// march is a serial chain of about 0.6 us per plane, and the items hold the
+// little work that is left when the chip is not full (per step, 32 -> 16
+// planes: 128^3 + 20-cell layer forward 130 -> 110 us, 400^3 + 24 cells 742 -> 736 us).
 constexpr int TX3 = 32;
 constexpr int TY3 = 16;
 constexpr int NTH3 = TX3 * TY3;
@@ -19,8 +22,21 @@ constexpr int TZC = 64;    // the longest chunk (bounds every chunk's 32-bit pla
 constexpr int TZC_MIN = 16;
 constexpr int TZCA_DEF = 64;   // the adjoint tile passes
 constexpr int TZCF_DEF = 32;   // the forward tile passes
-constexpr int TZCI_DEF = 32;   // the layer work items
+constexpr int TZCI_DEF = 16;   // the layer work items
 static_assert(TZCF_DEF <= TZC && TZCI_DEF <= TZC && TZCA_DEF <= TZC && TZC_MIN <= TZCF_DEF, "chunk bounds");
+// Planes per chunk of a tile pass over ntl tiles of nshots shots: the model's
+// setting if it has one, else the default halved (down to TZC_AUTO_MIN
+// planes) until the pass has `fill` workgroups.  A grid of few tiles leaves
+// CUs idle while its chunks march plane by plane, and shorter chunks then
+// cost only their window loads.  Per step, default chunks -> this rule:
+// 128^3 + 20-cell layer forward 130 -> 106 us, restore + recompute + adjoint
+// 438 -> 288 us; 64^3, 2 shots 107 -> 69 and 343 -> 168 us.  Full grids keep the
+// long chunks in the forward (240^3 + 20: 8-plane chunks 217 us, 32-plane 211 us);
+// the adjoint's longer march pays for more workgroups (240 x 240 x 200, 512 -> 2048:
+// 652 -> 628 us; 400^3 2359 -> 2343 us).
+constexpr int TZC_AUTO_MIN = 8;
+constexpr int FILL3_FWD = 512, FILL3_ADJ = 2048;
+int chunk3(int setting, int def, int fill, int ntl, int NZ, int nshots);
 constexpr int OX3 = 32;  // x offset (128-byte aligned rows)
 constexpr int OY3 = 4;
 constexpr int OZ3 = 4;
@@ -33,7 +49,7 @@ struct Grid3 {
     int SX, SY, SZ;
     long long sy, sz, plane;   // strides: sy = SX, sz = SX*SY, plane = sz*SZ
     int ntx, nty, nzc;         // tiles in x, y; adjoint z chunks
-    int zcf, zca;              // planes per chunk: forward and adjoint tile passes
+    int zcf, zca;              // planes per chunk: forward and adjoint tile passes (0: chunk3's rule)
 };
 
 struct Ac3Tabs {               // per-axis damping tables, h = zeta dt / 2

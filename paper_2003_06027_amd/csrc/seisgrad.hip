@@ -183,9 +183,7 @@ Layout make_layout(const sg_desc *d, int max_shots, int max_rec, int ckpt)
         g.P = P; g.nx = d->nx; g.ny = d->ny; g.nz = d->nz;
         g.NX = d->nx + 2 * P; g.NY = d->ny + 2 * P; g.NZ = d->nz + 2 * P;
         g.ntx = (g.NX + TX3 - 1) / TX3; g.nty = (g.NY + TY3 - 1) / TY3;
-        g.zcf = TZCF_DEF;
-        g.zca = TZCA_DEF;
-        g.nzc = (g.NZ + g.zca - 1) / g.zca;
+        g.zcf = g.zca = g.nzc = 0;     // chunk3's rule, until set_tuning
         g.SX = OX3 + g.ntx * TX3 + 32;
         g.SY = OY3 + g.nty * TY3 + 4;
         g.SZ = OZ3 + g.NZ + 4;
@@ -1766,10 +1764,7 @@ int set_tuning(sg_model *m, int32_t key, int32_t value, sg_stream_t stream)
             return fail(SG_EINVAL, "chunk of %d planes outside [%d, %d] or not a multiple of 8", value, TZC_MIN, TZC);
         Grid3 &g = m->L.g3;
         if (key == SG_TUNE_CHUNK_FWD3) g.zcf = value;
-        if (key == SG_TUNE_CHUNK_ADJ3) {
-            g.zca = value;
-            g.nzc = (g.NZ + value - 1) / value;
-        }
+        if (key == SG_TUNE_CHUNK_ADJ3) g.zca = value;
         if (key == SG_TUNE_CHUNK_LAYER3 && m->items3 && value != m->zci) {
             if (build_items3(m, value)) return fail(SG_EINVAL, "layer work list overflows its buffer");
             // the list is read by launches already enqueued: wait for them first
