@@ -45,6 +45,8 @@
 // it made the blocked adjoint 2 % slower.
 #include "sg_internal.h"
 
+#include <type_traits>
+
 namespace sg {
 
 // 8th-order centred weights: second derivative (a_1..a_4; the centre weight
@@ -107,19 +109,34 @@ __device__ __forceinline__ bool near_layer(const Grid2 &g, int x0, int z0)
                        z0 - 4 < g.P || z0 + TZ + 4 > g.P + g.nz);
 }
 
-// Fill the (TZ+8) x (TX+8) LDS tile: own cells by the caller, the 4-cell
+// Work of one workgroup: RW rows of a tile.
+struct TileItem {
+    int tile, shot;
+    int sub;              // which RW rows of the tile
+};
+
+// Item w of a launch over (shot, tile, rows), rows fastest.
+template <int RW>
+__device__ __forceinline__ TileItem tile_item(const int *tiles, int ntl, int w)
+{
+    constexpr int NS = TZ / RW;
+    const int t = w / NS, shot = t / ntl;
+    return TileItem{tiles[t - shot * ntl], shot, w - t * NS};
+}
+
+// Fill the (RW+8) x (TX+8) LDS tile: own cells by the caller, the 4-cell
 // halo here (value f(frame index)).
-template <class Fn>
+template <int RW, class Fn>
 __device__ __forceinline__ void load_halo(const Grid2 &g, float *lds, int x0, int z0, Fn f)
 {
     constexpr int H = 4, W = TX + 2 * H;
-    constexpr int NH = 2 * H * W + 2 * TZ * H;
+    constexpr int NH = 2 * H * W + 2 * RW * H;
     for (int i = threadIdx.x; i < NH; i += NTH) {
         int r, c;
         if (i < 2 * H * W) {
             const int s = i / W;
             c = i - s * W;
-            r = s < H ? s : s + TZ;
+            r = s < H ? s : s + RW;
         } else {
             const int j = i - 2 * H * W;
             const int rr = j / (2 * H), cc = j - rr * (2 * H);
@@ -136,7 +153,9 @@ __device__ __forceinline__ void load_halo(const Grid2 &g, float *lds, int x0, in
 // a source must round identically for the one- and two-step paths to agree).
 __device__ __forceinline__ float src_value(float scale, float w)
 {
-    return __fmul_rn(scale, w);
+    float v = scale * w;
+    asm("" : "+v"(v));                    // __fmul_rn is fused all the same (8-row tiles by the layer)
+    return v;
 }
 
 // A layer cell of the padded grid.
@@ -145,20 +164,101 @@ __device__ __forceinline__ bool layer_cell_at(const Grid2 &g, int iz, int ix)
     return iz < g.P || iz >= g.P + g.nz || ix < g.P || ix >= g.P + g.nx;
 }
 
-// Sum of dt^2/(dx dz) r_j(t_k) over the source nodes j of this shot at
-// local tile cell `cell` (several source nodes per shot; a handful of
-// entries per tile, only in the tiles that hold them).
-__device__ __forceinline__ float node_sources(const Ac2FwdArgs &a, int tile, int shot, int cell)
-{
-    const int ntiles = a.g.ntx * a.g.ntz;
-    const int *off = a.src_off + (long long)shot * (ntiles + 1);
-    float v = 0.f;
-    for (int e = off[tile]; e < off[tile + 1]; ++e) {
-        const int ent = a.src_ent[e];
-        if (src_cell(ent) == cell)
-            v += a.src_scale * a.wav[((long long)shot * a.nsrc + src_node(ent)) * a.nt + a.k];
+// Several source nodes per shot: the sum of dt^2/(dx dz) r_j(t_k) over the
+// nodes j at each cell of these RW rows, in the LDS array sadd (dynamic, only
+// when nsrc > 1).  The entries of a tile are sorted by cell, so one thread
+// adds up a cell's run of entries, in entry order; the cells without one hold
+// zero.  (Every cell stepping through all entries of its tile, one dependent
+// load after another, took 25 us of a 32 us launch at 49 nodes.)  begin()
+// reads the tile's range and clears the array before the barrier that
+// publishes the tile; fill() runs after it and ends with a barrier.
+template <int RW, int NT>
+struct NodeSources {
+    int b, e;
+    __device__ __forceinline__ bool any() const { return b < e; }
+    __device__ __forceinline__ void begin(const Ac2FwdArgs &a, const TileItem &it, float *sadd)
+    {
+        b = e = 0;
+        if (a.nsrc <= 1) return;
+        const int *off = a.src_off + (long long)it.shot * (a.g.ntx * a.g.ntz + 1);
+        b = off[it.tile];
+        e = off[it.tile + 1];
+        if (!any()) return;
+        for (int i = threadIdx.x; i < RW * TX; i += NT) sadd[i] = 0.f;
     }
-    return v;
+    __device__ __forceinline__ void fill(const Ac2FwdArgs &a, const TileItem &it, float *sadd) const
+    {
+        if (!any()) return;               // uniform over the block
+        for (int i = b + threadIdx.x; i < e; i += NT) {
+            const int cell = src_cell(a.src_ent[i]);
+            if (i > b && src_cell(a.src_ent[i - 1]) == cell) continue;    // not first of its cell
+            const int own = cell - it.sub * RW * TX;
+            if (own < 0 || own >= RW * TX) continue;
+            float v = 0.f;
+            for (int m = i; m < e && src_cell(a.src_ent[m]) == cell; ++m)
+                v += a.src_scale * a.wav[((long long)it.shot * a.nsrc + src_node(a.src_ent[m])) * a.nt + a.k];
+            sadd[own] = v;
+        }
+        __syncthreads();
+    }
+};
+
+// The receivers of a tile: its entry range and this thread's first entry,
+// loaded with the tile's operands so that the dependent loads overlap them.
+struct TileRecs {
+    int b, e, ent;
+    template <class Args>
+    __device__ __forceinline__ void begin(const Args &a, const TileItem &it)
+    {
+        const int *off = a.rec_off + (long long)it.shot * (a.g.ntx * a.g.ntz + 1);
+        b = off[it.tile];
+        e = off[it.tile + 1];
+        ent = 0;
+        if (b + (int)threadIdx.x < e) ent = a.rec_ent[b + threadIdx.x];
+    }
+    __device__ __forceinline__ bool any() const { return b < e; }
+};
+
+// Record u^{k+1} of the receivers on these RW rows; val(row, column) reads it
+// from LDS.
+template <int RW, int NT, class Fn>
+__device__ __forceinline__ void record_tile(const Ac2FwdArgs &a, const TileItem &it, const TileRecs &rc, Fn val)
+{
+    for (int i = rc.b + threadIdx.x; i < rc.e; i += NT) {
+        const int ent = i == rc.b + (int)threadIdx.x ? rc.ent : a.rec_ent[i];
+        const int own = rec_cell(ent) - it.sub * RW * TX;
+        if (own < 0 || own >= RW * TX) continue;
+        const int r = own / TX, c = own - r * TX;
+        a.seis[((long long)it.shot * a.nt + a.k) * a.nrec + rec_id(ent)] = val(r, c);
+    }
+}
+
+// Add R^T dJ/dd^{k+1} to the cells of these RW rows (at(row, column) is the
+// LDS cell), deterministic per cell: the thread of a cell's first entry adds
+// up the run.  d0: the sample of this thread's first entry, loaded early.
+template <int RW, int NT, class Fn>
+__device__ __forceinline__ void inject_tile(const Ac2AdjArgs &a, const TileItem &it, const TileRecs &rc, float d0,
+                                            Fn at)
+{
+    const float *d = a.dJdd + ((long long)it.shot * a.nt + a.k) * a.nrec;
+    for (int i = rc.b + threadIdx.x; i < rc.e; i += NT) {
+        const bool pre = i == rc.b + (int)threadIdx.x;
+        const int ent = pre ? rc.ent : a.rec_ent[i];
+        const int cell = rec_cell(ent), own = cell - it.sub * RW * TX;
+        if (own < 0 || own >= RW * TX) continue;
+        if (i > rc.b && rec_cell(a.rec_ent[i - 1]) == cell) continue;  // not first of its cell
+        float sum = 0.f;
+        sum += pre ? d0 : d[rec_id(ent)];
+        for (int m = i + 1; m < rc.e && rec_cell(a.rec_ent[m]) == cell; ++m) sum += d[rec_id(a.rec_ent[m])];
+        const int r = own / TX, c = own - r * TX;
+        at(r, c) += sum;
+    }
+}
+
+__device__ __forceinline__ float first_sample(const Ac2AdjArgs &a, const TileItem &it, const TileRecs &rc)
+{
+    return rc.b + (int)threadIdx.x < rc.e
+               ? a.dJdd[((long long)it.shot * a.nt + a.k) * a.nrec + rec_id(rc.ent)] : 0.f;
 }
 
 __global__ void ac2_src_gather_kernel(int nshots, int nsrc, long long plane, const long long *node_f,
@@ -178,19 +278,26 @@ void launch_ac2_src_gather(int nshots, int nsrc, long long plane, const long lon
 }
 
 // ------------------------------------------------------------ forward pass B
-// A tile away from the layer (the interior update), u^k with a 4-cell halo in LDS.
-template <bool SNAP, bool REC>
-__device__ __forceinline__ void fwd_tile(const Ac2FwdArgs &a, float *su, int tile, int shot)
+// RW rows of a tile away from the layer (the interior update), u^k with a
+// 4-cell halo in LDS.
+template <int RW, bool SNAP, bool REC>
+__device__ __forceinline__ void fwd_tile(const Ac2FwdArgs &a, float *su, float *sadd, const TileItem &it)
 {
-    constexpr int H = 4, W = TX + 2 * H;
+    constexpr int H = 4, W = TX + 2 * H, RPT = RW / (NTH / TX);
     const Grid2 &g = a.g;
-    const int tz = tile / g.ntx, tx = tile - tz * g.ntx;
-    const int x0 = tx * TX, z0 = tz * TZ;
+    const int shot = it.shot;
+    const int tz = it.tile / g.ntx, tx = it.tile - tz * g.ntx;
+    const int x0 = tx * TX, z0 = tz * TZ + it.sub * RW;
+    if (z0 >= g.NZ) return;
     const long long so = (long long)shot * g.plane;
     const float *u = a.u + so;
     const int tid = threadIdx.x, lx = tid % TX, ly = tid / TX;
     const int ix = x0 + lx;
 
+    NodeSources<RW, NTH> ns;
+    ns.begin(a, it, sadd);
+    TileRecs rc{};
+    if constexpr (REC) rc.begin(a, it);
     float uc[RPT];
 #pragma unroll
     for (int j = 0; j < RPT; ++j) {
@@ -198,8 +305,9 @@ __device__ __forceinline__ void fwd_tile(const Ac2FwdArgs &a, float *su, int til
         uc[j] = u[fidx(g, z0 + r, ix)];
         su[(r + H) * W + lx + H] = uc[j];
     }
-    load_halo(g, su, x0, z0, [&](long long f) { return u[f]; });
+    load_halo<RW>(g, su, x0, z0, [&](long long f) { return u[f]; });
     __syncthreads();
+    ns.fill(a, it, sadd);
 
     const float *chat = a.chat + (long long)(shot / a.shots_per_model) * g.plane;
     const float *um = a.um + so;
@@ -217,7 +325,7 @@ __device__ __forceinline__ void fwd_tile(const Ac2FwdArgs &a, float *su, int til
             // 2u - um + chat w = u + ((u - um) + chat w)
             float inc = fmaf(chat[f], w, uc[j] - __builtin_nontemporal_load(um + f));
             if (f == src) inc += sval;
-            if (a.nsrc > 1) inc += node_sources(a, tile, shot, r * TX + lx);
+            if (ns.any()) inc += sadd[r * TX + lx];
             const float v = uc[j] + inc;
             __builtin_nontemporal_store(v, uo + f);
             un[j] = v;
@@ -226,48 +334,45 @@ __device__ __forceinline__ void fwd_tile(const Ac2FwdArgs &a, float *su, int til
     }
 
     if constexpr (REC) {
-        const int ntiles = g.ntx * g.ntz;
-        const int *off = a.rec_off + (long long)shot * (ntiles + 1);
-        const int b = off[tile], e = off[tile + 1];
-        if (b < e) {                      // uniform over the block
+        if (rc.any()) {                   // uniform over the block
             __syncthreads();
 #pragma unroll
             for (int j = 0; j < RPT; ++j) su[(ly * RPT + j + H) * W + lx + H] = un[j];
             __syncthreads();
-            for (int i = b + tid; i < e; i += NTH) {
-                const int ent = a.rec_ent[i];
-                const int cell = rec_cell(ent);
-                const int r = cell / TX, c = cell - r * TX;
-                a.seis[((long long)shot * a.nt + a.k) * a.nrec + rec_id(ent)] = su[(r + H) * W + c + H];
-            }
+            record_tile<RW, NTH>(a, it, rc, [&](int r, int c) { return su[(r + H) * W + c + H]; });
         }
     }
 }
 
 // One forward step on a list of tiles away from the layer.
-template <bool SNAP, bool REC>
+template <int RW, bool SNAP, bool REC>
 __global__ __launch_bounds__(NTH) void ac2_fwd_kernel(Ac2FwdArgs a)
 {
-    __shared__ float su[(TZ + 8) * (TX + 8)];
-    const int w = xcd_work_id(a.ntl * a.nshots);
-    const int shot = w / a.ntl;
-    fwd_tile<SNAP, REC>(a, su, a.tiles[w - shot * a.ntl], shot);
+    __shared__ float su[(RW + 8) * (TX + 8)];
+    extern __shared__ float sadd[];
+    const int w = xcd_work_id(a.ntl * a.nshots * (TZ / RW));
+    fwd_tile<RW, SNAP, REC>(a, su, sadd, tile_item<RW>(a.tiles, a.ntl, w));
 }
 
 // ------------------------------------------------------------ adjoint pass B
-// A tile away from the layer, chat s^{k+2} with a 4-cell halo in LDS.
-__device__ __forceinline__ void adj_tile(const Ac2AdjArgs &a, float *sc, int tile, int shot)
+// RW rows of a tile away from the layer, chat s^{k+2} with a 4-cell halo in LDS.
+template <int RW>
+__device__ __forceinline__ void adj_tile(const Ac2AdjArgs &a, float *sc, const TileItem &it)
 {
-    constexpr int H = 4, W = TX + 2 * H;
+    constexpr int H = 4, W = TX + 2 * H, RPT = RW / (NTH / TX);
     const Grid2 &g = a.g;
-    const int tz = tile / g.ntx, tx = tile - tz * g.ntx;
-    const int x0 = tx * TX, z0 = tz * TZ;
+    const int shot = it.shot;
+    const int tz = it.tile / g.ntx, tx = it.tile - tz * g.ntx;
+    const int x0 = tx * TX, z0 = tz * TZ + it.sub * RW;
+    if (z0 >= g.NZ) return;
     const long long so = (long long)shot * g.plane;
     const float *s2 = a.s2 + so;
     const float *chat = a.chat + (long long)(shot / a.shots_per_model) * g.plane;
     const int tid = threadIdx.x, lx = tid % TX, ly = tid / TX;
     const int ix = x0 + lx;
 
+    TileRecs rc{};
+    rc.begin(a, it);
     float sc2[RPT];
 #pragma unroll
     for (int j = 0; j < RPT; ++j) {
@@ -276,8 +381,9 @@ __device__ __forceinline__ void adj_tile(const Ac2AdjArgs &a, float *sc, int til
         sc2[j] = s2[f];
         sc[(r + H) * W + lx + H] = chat[f] * sc2[j];
     }
-    load_halo(g, sc, x0, z0, [&](long long f) { return chat[f] * s2[f]; });
+    load_halo<RW>(g, sc, x0, z0, [&](long long f) { return chat[f] * s2[f]; });
     __syncthreads();
+    const float d0 = first_sample(a, it, rc);
 
     const float *s3 = a.s3 + so;
     float *s1o = a.s1 + so;
@@ -293,28 +399,15 @@ __device__ __forceinline__ void adj_tile(const Ac2AdjArgs &a, float *sc, int til
         av[j] = v;
     }
 
-    {   // receiver residual injection R^T dJ/dd^{k+1}, deterministic per cell
-        const int ntiles = g.ntx * g.ntz;
-        const int *off = a.rec_off + (long long)shot * (ntiles + 1);
-        const int b = off[tile], e = off[tile + 1];
-        if (b < e) {
-            __syncthreads();
+    if (rc.any()) {   // receiver residual injection, uniform over the block
+        __syncthreads();
 #pragma unroll
-            for (int j = 0; j < RPT; ++j) sc[(ly * RPT + j + H) * W + lx + H] = av[j];
-            __syncthreads();
-            const float *d = a.dJdd + ((long long)shot * a.nt + a.k) * a.nrec;
-            for (int i = b + tid; i < e; i += NTH) {
-                const int cell = rec_cell(a.rec_ent[i]);
-                if (i > b && rec_cell(a.rec_ent[i - 1]) == cell) continue;  // not first of its cell
-                float sum = 0.f;
-                for (int m = i; m < e && rec_cell(a.rec_ent[m]) == cell; ++m) sum += d[rec_id(a.rec_ent[m])];
-                const int r = cell / TX, c = cell - r * TX;
-                sc[(r + H) * W + c + H] += sum;
-            }
-            __syncthreads();
+        for (int j = 0; j < RPT; ++j) sc[(ly * RPT + j + H) * W + lx + H] = av[j];
+        __syncthreads();
+        inject_tile<RW, NTH>(a, it, rc, d0, [&](int r, int c) -> float & { return sc[(r + H) * W + c + H]; });
+        __syncthreads();
 #pragma unroll
-            for (int j = 0; j < RPT; ++j) av[j] = sc[(ly * RPT + j + H) * W + lx + H];
-        }
+        for (int j = 0; j < RPT; ++j) av[j] = sc[(ly * RPT + j + H) * W + lx + H];
     }
 
     const long long src = a.src_f[shot];
@@ -333,12 +426,12 @@ __device__ __forceinline__ void adj_tile(const Ac2AdjArgs &a, float *sc, int til
 
 // (8 waves per SIMD: 64 VGPRs, no spill; measured 2 % faster than the
 // compiler's choice of 70.  The forward's one-step variants are slower at 8.)
+template <int RW>
 __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(8))) void ac2_adj_kernel(Ac2AdjArgs a)
 {
-    __shared__ float sc[(TZ + 8) * (TX + 8)];
-    const int w = xcd_work_id(a.ntl * a.nshots);
-    const int shot = w / a.ntl;
-    adj_tile(a, sc, a.tiles[w - shot * a.ntl], shot);
+    __shared__ float sc[(RW + 8) * (TX + 8)];
+    const int w = xcd_work_id(a.ntl * a.nshots * (TZ / RW));
+    adj_tile<RW>(a, sc, tile_item<RW>(a.tiles, a.ntl, w));
 }
 
 // ---------------------------------------------------------- two-step kernels
@@ -350,17 +443,16 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(8))) void a
 // one write of u^{k+1}, u^{k+2}.  Each value is computed with exactly the
 // operations of the single-step kernel, so results agree bit for bit.
 constexpr int H2 = 8;                       // u^k halo of a blocked tile
-constexpr int W0 = TX + 2 * H2, R0 = TZ + 2 * H2;
-constexpr int W1 = TX + 8, R1 = TZ + 8;
-constexpr int NRING = R1 * W1 - TZ * TX;    // the 4-cell ring around the tile
+constexpr int W0 = TX + 2 * H2, W1 = TX + 8;
+// of RW rows of a tile: rows of the tile + 8 and + 4, cells of the 4-cell ring around them
+constexpr int rows0(int RW) { return RW + 2 * H2; }
+constexpr int rows1(int RW) { return RW + 8; }
+constexpr int nring(int RW) { return rows1(RW) * W1 - RW * TX; }
 // The forward blocked tiles take NTB threads (RB rows each): 8 waves per
 // SIMD in 55 VGPRs against 5 at 256 threads (C2: 141 -> 136 us per launch).
 // The adjoint keeps 256 threads (512 ran 2 % slower).
-constexpr int RING_IT = (NRING + NTH - 1) / NTH;
 constexpr int NTB = 512;
-constexpr int RB = TZ * TX / NTB;
-constexpr int RING_ITB = (NRING + NTB - 1) / NTB;
-static_assert(RB * NTB == TZ * TX && NTB % TX == 0, "whole rows per thread");
+static_assert(8 * TX % NTB == 0 && NTB % TX == 0, "whole rows per thread");
 
 // The tile + 8 of a field (rows start 32-byte aligned: x0 - 8 + OX is a
 // multiple of 8) straight from global memory into LDS:
@@ -368,10 +460,10 @@ static_assert(RB * NTB == TZ * TX && NTB % TX == 0, "whole rows per thread");
 // of W0 floats have no padding, so item order is slot order).  Every cell
 // lies inside the zero frame.  The caller waits for the loads
 // (s_waitcnt) before the barrier that publishes the tile.
-template <int NT>
+template <int RW, int NT>
 __device__ __forceinline__ void dma_tile8(const Grid2 &g, const float *u, float *lds, int x0, int z0)
 {
-    constexpr int Q = W0 / 4, N4 = R0 * Q;
+    constexpr int Q = W0 / 4, N4 = rows0(RW) * Q;
 #pragma unroll
     for (int it = 0; it < (N4 + NT - 1) / NT; ++it) {
         const int q = threadIdx.x + it * NT;
@@ -389,11 +481,11 @@ __device__ __forceinline__ void dma_tile8(const Grid2 &g, const float *u, float 
 // registers; after the caller's wait and barrier, product_in_place multiplies
 // each thread's items in LDS (one FP32 product per cell, chat times s).  The
 // caller synchronises again before the tile is read.
-template <int NT>
+template <int RW, int NT>
 __device__ __forceinline__ void dma_product_load(const Grid2 &g, const float *s, const float *mul, float *lds,
-                                                 int x0, int z0, float4 (&m)[(R0 * (W0 / 4) + NT - 1) / NT])
+                                                 int x0, int z0, float4 (&m)[(rows0(RW) * (W0 / 4) + NT - 1) / NT])
 {
-    constexpr int Q = W0 / 4, N4 = R0 * Q;
+    constexpr int Q = W0 / 4, N4 = rows0(RW) * Q;
 #pragma unroll
     for (int it = 0; it < (N4 + NT - 1) / NT; ++it) {
         const int q = threadIdx.x + it * NT;
@@ -408,10 +500,10 @@ __device__ __forceinline__ void dma_product_load(const Grid2 &g, const float *s,
     }
 }
 
-template <int NT>
-__device__ __forceinline__ void product_in_place(float *lds, const float4 (&m)[(R0 * (W0 / 4) + NT - 1) / NT])
+template <int RW, int NT>
+__device__ __forceinline__ void product_in_place(float *lds, const float4 (&m)[(rows0(RW) * (W0 / 4) + NT - 1) / NT])
 {
-    constexpr int N4 = R0 * (W0 / 4);
+    constexpr int N4 = rows0(RW) * (W0 / 4);
 #pragma unroll
     for (int it = 0; it < (N4 + NT - 1) / NT; ++it) {
         const int q = threadIdx.x + it * NT;
@@ -423,13 +515,14 @@ __device__ __forceinline__ void product_in_place(float *lds, const float4 (&m)[(
     }
 }
 
-// Cell i of the ring (rows 0-3 and 36-39 of the tile + 4, then columns 0-3
-// and 68-71 of rows 4-35), as (row, column) of the tile + 4.
+// Cell i of the ring (the first and last 4 rows of the rows + 4, then columns
+// 0-3 and 68-71 of the rows between), as (row, column) of the rows + 4.
+template <int RW>
 __device__ __forceinline__ void ring_cell(int i, int &r, int &c)
 {
     if (i < 8 * W1) {
         const int rr = i / W1;
-        r = rr < 4 ? rr : rr + TZ;
+        r = rr < 4 ? rr : rr + RW;
         c = i - rr * W1;
     } else {
         const int j = i - 8 * W1, cc = j & 7;
@@ -438,12 +531,15 @@ __device__ __forceinline__ void ring_cell(int i, int &r, int &c)
     }
 }
 
-// s0: u^k on the tile + 8 (R0 x W0), s1: u^{k+1} on the tile + 4 (R1 x W1)
-__device__ __forceinline__ void fwd2_tile(const Ac2Fwd2Args &a, float *s0, float *s1, int tile, int shot)
+// s0: u^k on the rows + 8 (rows0 x W0), s1: u^{k+1} on the rows + 4 (rows1 x W1)
+template <int RW>
+__device__ __forceinline__ void fwd2_tile(const Ac2Fwd2Args &a, float *s0, float *s1, const TileItem &it)
 {
+    constexpr int RB = RW * TX / NTB, NRING = nring(RW), RING_ITB = (NRING + NTB - 1) / NTB;
     const Grid2 &g = a.g;
-    const int tz = tile / g.ntx, tx = tile - tz * g.ntx;
-    const int x0 = tx * TX, z0 = tz * TZ;
+    const int shot = it.shot;
+    const int tz = it.tile / g.ntx, tx = it.tile - tz * g.ntx;
+    const int x0 = tx * TX, z0 = tz * TZ + it.sub * RW;
     const long long so = (long long)shot * g.plane;
     const float *um = a.um + so;
     const float *chat = a.chat + (long long)(shot / a.shots_per_model) * g.plane;
@@ -464,18 +560,18 @@ __device__ __forceinline__ void fwd2_tile(const Ac2Fwd2Args &a, float *s0, float
     float rch[RING_ITB], rpm[RING_ITB];
     long long rf[RING_ITB];
 #pragma unroll
-    for (int it = 0; it < RING_ITB; ++it) {
-        const int i = threadIdx.x + it * NTB;
-        rf[it] = -1;
+    for (int q = 0; q < RING_ITB; ++q) {
+        const int i = threadIdx.x + q * NTB;
+        rf[q] = -1;
         if (i < NRING) {
             int r, c;
-            ring_cell(i, r, c);
-            rf[it] = fidx(g, z0 - 4 + r, x0 - 4 + c);
-            rch[it] = chat[rf[it]];
-            rpm[it] = um[rf[it]];
+            ring_cell<RW>(i, r, c);
+            rf[q] = fidx(g, z0 - 4 + r, x0 - 4 + c);
+            rch[q] = chat[rf[q]];
+            rpm[q] = um[rf[q]];
         }
     }
-    dma_tile8<NTB>(g, a.u0 + so, s0, x0, z0);
+    dma_tile8<RW, NTB>(g, a.u0 + so, s0, x0, z0);
     __builtin_amdgcn_s_waitcnt(0);       // the tile's direct loads have landed in LDS
     __syncthreads();
 
@@ -496,16 +592,16 @@ __device__ __forceinline__ void fwd2_tile(const Ac2Fwd2Args &a, float *s0, float
         if (a.snap0) __builtin_nontemporal_store(wk, a.snap0 + so + f);
     }
 #pragma unroll
-    for (int it = 0; it < RING_ITB; ++it) {
-        const int i = threadIdx.x + it * NTB;
+    for (int q = 0; q < RING_ITB; ++q) {
+        const int i = threadIdx.x + q * NTB;
         if (i < NRING) {
             int r, c;
-            ring_cell(i, r, c);
+            ring_cell<RW>(i, r, c);
             const float *cc = s0 + (r + 4) * W0 + c + 4;
             const float wk = lap8(cc, W0);
             const float u = cc[0];
-            float inc = fmaf(rch[it], wk, u - rpm[it]);
-            if (rf[it] == src) inc += sv0;
+            float inc = fmaf(rch[q], wk, u - rpm[q]);
+            if (rf[q] == src) inc += sv0;
             s1[r * W1 + c] = u + inc;
         }
     }
@@ -524,28 +620,30 @@ __device__ __forceinline__ void fwd2_tile(const Ac2Fwd2Args &a, float *s0, float
     }
 }
 
+template <int RW>
 __global__ __launch_bounds__(NTB) void ac2_fwd2_kernel(Ac2Fwd2Args a)
 {
-    __shared__ __attribute__((aligned(16))) float s0[R0 * W0];
-    __shared__ float s1[R1 * W1];
-    const int w = xcd_work_id(a.ntl * a.nshots);
-    const int shot = w / a.ntl, tile = a.tiles[w - shot * a.ntl];
-    fwd2_tile(a, s0, s1, tile, shot);
+    __shared__ __attribute__((aligned(16))) float s0[rows0(RW) * W0];
+    __shared__ float s1[rows1(RW) * W1];
+    const int w = xcd_work_id(a.ntl * a.nshots * (TZ / RW));
+    fwd2_tile<RW>(a, s0, s1, tile_item<RW>(a.tiles, a.ntl, w));
 }
 
 // Adjoint steps k and k-1 on blocked tiles (no receivers within 4 cells):
 // s^{k+1} on the tile + 4 from chat s^{k+2} on the tile + 8, then s^k on
 // the tile; the gradient gets s^{k+1} w~^k, then s^k w~^{k-1}, as in two
 // single steps.
+template <int RW>
 __global__ __launch_bounds__(NTH) void ac2_adj2_kernel(Ac2Adj2Args a)
 {
-    __shared__ __attribute__((aligned(16))) float p0[R0 * W0];   // chat s^{k+2} on the tile + 8
-    __shared__ float p1[R1 * W1];   // chat s^{k+1} on the tile + 4
+    constexpr int RPT = RW / (NTH / TX), NRING = nring(RW), RING_IT = (NRING + NTH - 1) / NTH;
+    __shared__ __attribute__((aligned(16))) float p0[rows0(RW) * W0];   // chat s^{k+2} on the rows + 8
+    __shared__ float p1[rows1(RW) * W1];   // chat s^{k+1} on the rows + 4
     const Grid2 &g = a.g;
-    const int w = xcd_work_id(a.ntl * a.nshots);
-    const int shot = w / a.ntl, tile = a.tiles[w - shot * a.ntl];
-    const int tz = tile / g.ntx, tx = tile - tz * g.ntx;
-    const int x0 = tx * TX, z0 = tz * TZ;
+    const int w = xcd_work_id(a.ntl * a.nshots * (TZ / RW));
+    const TileItem item = tile_item<RW>(a.tiles, a.ntl, w);
+    const int shot = item.shot, tz = item.tile / g.ntx, tx = item.tile - tz * g.ntx;
+    const int x0 = tx * TX, z0 = tz * TZ + item.sub * RW;
     const long long so = (long long)shot * g.plane;
     const float *s2 = a.s2 + so, *s3 = a.s3 + so;
     const float *chat = a.chat + (long long)(shot / a.shots_per_model) * g.plane;
@@ -569,18 +667,18 @@ __global__ __launch_bounds__(NTH) void ac2_adj2_kernel(Ac2Adj2Args a)
         const int i = threadIdx.x + it * NTH;
         if (i < NRING) {
             int r, c;
-            ring_cell(i, r, c);
+            ring_cell<RW>(i, r, c);
             const long long f = fidx(g, z0 - 4 + r, x0 - 4 + c);
             rch[it] = chat[f];
             rq2[it] = s2[f];
             rq3[it] = s3[f];
         }
     }
-    float4 cm[(R0 * (W0 / 4) + NTH - 1) / NTH];
-    dma_product_load<NTH>(g, s2, chat, p0, x0, z0, cm);
+    float4 cm[(rows0(RW) * (W0 / 4) + NTH - 1) / NTH];
+    dma_product_load<RW, NTH>(g, s2, chat, p0, x0, z0, cm);
     __builtin_amdgcn_s_waitcnt(0);       // the tile's direct loads have landed in LDS
     __syncthreads();
-    product_in_place<NTH>(p0, cm);
+    product_in_place<RW, NTH>(p0, cm);
     __syncthreads();
 
     // step k: s^{k+1} on the tile + 4
@@ -601,7 +699,7 @@ __global__ __launch_bounds__(NTH) void ac2_adj2_kernel(Ac2Adj2Args a)
         const int i = threadIdx.x + it * NTH;
         if (i < NRING) {
             int r, c;
-            ring_cell(i, r, c);
+            ring_cell<RW>(i, r, c);
             float v = lap8(p0 + (r + 4) * W0 + c + 4, W0);
             v += rq2[it] + (rq2[it] - rq3[it]);
             p1[r * W1 + c] = rch[it] * v;
@@ -633,17 +731,17 @@ __global__ __launch_bounds__(NTH) void ac2_adj2_kernel(Ac2Adj2Args a)
 // tile (RN rows each): the LDS arrays cap the workgroups per CU, so a
 // larger workgroup keeps more waves resident.
 constexpr int WPX = TX + 8;      // x auxiliary: columns x0 - 4 .. x0 + TX + 3
-constexpr int RPZ = TZ + 8;      // z auxiliary: rows z0 - 4 .. z0 + TZ + 3
-constexpr int NU = R0 * W0;      // the field on the tile + 8
 constexpr int NTN = 512;         // threads of a near tile
-constexpr int RN = TZ * TX / NTN;
-static_assert(RN * NTN == TZ * TX && NTN % TX == 0, "whole rows per thread");
+static_assert(8 * TX % NTN == 0 && NTN % TX == 0, "whole rows per thread");
+constexpr int nu8(int RW) { return rows0(RW) * W0; }      // the field on the rows + 8
+constexpr int npx(int RW) { return RW * WPX; }            // x auxiliary
+constexpr int npz(int RW) { return (RW + 8) * TX; }       // z auxiliary: rows z0 - 4 .. z0 + RW + 3
 
 // Halo cells of the auxiliaries' LDS arrays: the 4 + 4 columns of the x
-// array beside the tile (TZ x 8, one per thread) and the 4 + 4 rows of the z
-// array above and below it (8 x TX, two per thread).
-constexpr int NHX = TZ * 8, NHZ = 8 * TX;
-constexpr int HXI = (NHX + NTN - 1) / NTN, HZI = (NHZ + NTN - 1) / NTN;   // halo cells per thread
+// array beside the tile (RW x 8, at most one per thread) and the 4 + 4 rows
+// of the z array above and below it (8 x TX, one per thread).
+constexpr int NHZ = 8 * TX;
+static_assert(TZ * 8 <= NTN && NHZ <= NTN, "one halo cell of each array per thread");
 
 __device__ __forceinline__ void halo_x_cell(int i, int &r, int &c)
 {
@@ -652,20 +750,24 @@ __device__ __forceinline__ void halo_x_cell(int i, int &r, int &c)
     c = cc < 4 ? cc : cc + TX;           // column of the x array (x0 - 4 + c)
 }
 
+template <int RW>
 __device__ __forceinline__ void halo_z_cell(int i, int &r, int &c)
 {
     const int rr = i / TX;
     c = i - rr * TX;
-    r = rr < 4 ? rr : rr + TZ;           // row of the z array (z0 - 4 + r)
+    r = rr < 4 ? rr : rr + RW;           // row of the z array (z0 - 4 + r)
 }
 
-template <bool SNAP, bool REC>
-__device__ __forceinline__ void fwd_near_tile(const Ac2FwdArgs &a, float *su, float *sx, float *sz, int tile,
-                                              int shot)
+template <int RW, bool SNAP, bool REC>
+__device__ __forceinline__ void fwd_near_tile(const Ac2FwdArgs &a, float *su, float *sx, float *sz, float *sadd,
+                                              const TileItem &it)
 {
+    constexpr int RN = RW * TX / NTN, NHX = RW * 8;
     const Grid2 &g = a.g;
-    const int tz = tile / g.ntx, tx = tile - tz * g.ntx;
-    const int x0 = tx * TX, z0 = tz * TZ;
+    const int shot = it.shot;
+    const int tz = it.tile / g.ntx, tx = it.tile - tz * g.ntx;
+    const int x0 = tx * TX, z0 = tz * TZ + it.sub * RW;
+    if (z0 >= g.NZ) return;
     const long long so = (long long)shot * g.plane;
     // ly is uniform over a wavefront (TX lanes): rows and their tables in scalar registers
     const int tid = threadIdx.x, lx = tid % TX, ly = __builtin_amdgcn_readfirstlane(tid / TX);
@@ -678,6 +780,10 @@ __device__ __forceinline__ void fwd_near_tile(const Ac2FwdArgs &a, float *su, fl
     float *__restrict__ phx = a.phx + so;
     float *__restrict__ phz = a.phz + so;
 
+    NodeSources<RW, NTN> ns;
+    ns.begin(a, it, sadd);
+    TileRecs rc{};
+    if constexpr (REC && RW < TZ) rc.begin(a, it);
     // operands of the own cells and of the halo cells first (none depends on LDS)
     const float hxc = inx ? a.hx[ix] : 0.f, pxc = inx ? a.px[ix] : 0.f, ihxc = inx ? a.ihx[ix] : 0.f;
     float ch[RN], pm[RN], hzr[RN], fx[RN], fz[RN], pzr[RN], ihzr[RN];
@@ -700,42 +806,33 @@ __device__ __forceinline__ void fwd_near_tile(const Ac2FwdArgs &a, float *su, fl
             }
         }
     }
-    // halo cells of the x and z arrays
-    float xhx[HXI], xhz[HXI], xp[HXI], xih[HXI], xf[HXI];
-    bool xl[HXI];
-    int xr[HXI], xc[HXI];
-#pragma unroll
-    for (int it = 0; it < HXI; ++it) {
-        const int i = tid + it * NTN;
-        halo_x_cell(i < NHX ? i : 0, xr[it], xc[it]);
-        const int iz = z0 + xr[it], jx = x0 - 4 + xc[it];
-        xl[it] = i < NHX && iz < g.NZ && jx >= 0 && jx < g.NX && layer_cell_at(g, iz, jx);
-        xhx[it] = xhz[it] = xp[it] = xih[it] = xf[it] = 0.f;
-        if (xl[it]) {
-            xhx[it] = a.hx[jx]; xhz[it] = a.hz[iz]; xp[it] = a.px[jx]; xih[it] = a.ihx[jx];
-            xf[it] = phx0[fidx(g, iz, jx)];
-        }
+    // halo cells of the x and z arrays, one of each per thread
+    float xhx = 0.f, xhz = 0.f, xp = 0.f, xih = 0.f, xf = 0.f;
+    int xr, xc;
+    halo_x_cell(tid < NHX ? tid : 0, xr, xc);
+    const bool xl = tid < NHX && z0 + xr < g.NZ && x0 - 4 + xc >= 0 && x0 - 4 + xc < g.NX &&
+                    layer_cell_at(g, z0 + xr, x0 - 4 + xc);
+    if (xl) {
+        const int iz = z0 + xr, jx = x0 - 4 + xc;
+        xhx = a.hx[jx]; xhz = a.hz[iz]; xp = a.px[jx]; xih = a.ihx[jx];
+        xf = phx0[fidx(g, iz, jx)];
     }
-    float zhx[HZI], zhz[HZI], zp[HZI], zih[HZI], zf[HZI];
-    bool zl[HZI];
-    int zr[HZI], zc[HZI];
-#pragma unroll
-    for (int it = 0; it < HZI; ++it) {
-        const int i = tid + it * NTN;
-        halo_z_cell(i < NHZ ? i : 0, zr[it], zc[it]);
-        const int iz = z0 - 4 + zr[it], jx = x0 + zc[it];
-        zl[it] = i < NHZ && iz >= 0 && iz < g.NZ && jx < g.NX && layer_cell_at(g, iz, jx);
-        zhx[it] = zhz[it] = zp[it] = zih[it] = zf[it] = 0.f;
-        if (zl[it]) {
-            zhx[it] = a.hx[jx]; zhz[it] = a.hz[iz]; zp[it] = a.pz[iz]; zih[it] = a.ihz[iz];
-            zf[it] = phz0[fidx(g, iz, jx)];
-        }
+    float zhx = 0.f, zhz = 0.f, zp = 0.f, zih = 0.f, zf = 0.f;
+    int zr, zc;
+    halo_z_cell<RW>(tid, zr, zc);
+    const bool zl = tid < NHZ && z0 - 4 + zr >= 0 && z0 - 4 + zr < g.NZ && x0 + zc < g.NX &&
+                    layer_cell_at(g, z0 - 4 + zr, x0 + zc);
+    if (zl) {
+        const int iz = z0 - 4 + zr, jx = x0 + zc;
+        zhx = a.hx[jx]; zhz = a.hz[iz]; zp = a.pz[iz]; zih = a.ihz[iz];
+        zf = phz0[fidx(g, iz, jx)];
     }
-    dma_tile8<NTN>(g, a.u + so, su, x0, z0);               // u^k on the tile + 8
+    dma_tile8<RW, NTN>(g, a.u + so, su, x0, z0);           // u^k on the rows + 8
     const long long src = a.src_f[shot];
     const float sval = src_value(a.src_scale, a.wav[(long long)shot * a.nt + a.k]);
     __builtin_amdgcn_s_waitcnt(0);       // the tile's direct loads have landed in LDS
     __syncthreads();
+    ns.fill(a, it, sadd);
 
     // pass A: phi~^k on the own layer cells (written out) and the halo cells
 #pragma unroll
@@ -756,25 +853,21 @@ __device__ __forceinline__ void fwd_near_tile(const Ac2FwdArgs &a, float *su, fl
         sx[r * WPX + lx + 4] = vx;
         sz[(r + 4) * TX + lx] = vz;
     }
-#pragma unroll
-    for (int it = 0; it < HXI; ++it) {
-        if (tid + it * NTN >= NHX) continue;
+    if (tid < NHX) {
         float v = 0.f;
-        if (xl[it]) {
-            const float qx = 2.f * (xhz[it] - xhx[it]) * xih[it];
-            v = xp[it] * xf[it] + qx * d8(su + (xr[it] + H2) * W0 + xc[it] + 4, 1);
+        if (xl) {
+            const float qx = 2.f * (xhz - xhx) * xih;
+            v = xp * xf + qx * d8(su + (xr + H2) * W0 + xc + 4, 1);
         }
-        sx[xr[it] * WPX + xc[it]] = v;
+        sx[xr * WPX + xc] = v;
     }
-#pragma unroll
-    for (int it = 0; it < HZI; ++it) {
-        if (tid + it * NTN >= NHZ) continue;
+    if (tid < NHZ) {
         float v = 0.f;
-        if (zl[it]) {
-            const float qz = 2.f * (zhx[it] - zhz[it]) * zih[it];
-            v = zp[it] * zf[it] + qz * d8(su + (zr[it] + 4) * W0 + zc[it] + H2, (long long)W0);
+        if (zl) {
+            const float qz = 2.f * (zhx - zhz) * zih;
+            v = zp * zf + qz * d8(su + (zr + 4) * W0 + zc + H2, (long long)W0);
         }
-        sz[zr[it] * TX + zc[it]] = v;
+        sz[zr * TX + zc] = v;
     }
     __syncthreads();
 
@@ -798,7 +891,7 @@ __device__ __forceinline__ void fwd_near_tile(const Ac2FwdArgs &a, float *su, fl
             const float umf = pm[j];
             float inc = (uc - umf) + ((hx + hz) * umf - 4.f * hx * hz * uc) + ch[j] * w;
             if (f == src) inc += sval;
-            if (a.nsrc > 1) inc += node_sources(a, tile, shot, r * TX + lx);
+            if (ns.any()) inc += sadd[r * TX + lx];
             const float v = alpha * (uc + inc);
             __builtin_nontemporal_store(v, uo + f);
             un[j] = v;
@@ -807,20 +900,14 @@ __device__ __forceinline__ void fwd_near_tile(const Ac2FwdArgs &a, float *su, fl
     }
 
     if constexpr (REC) {
-        const int ntiles = g.ntx * g.ntz;
-        const int *off = a.rec_off + (long long)shot * (ntiles + 1);
-        const int b = off[tile], e = off[tile + 1];
-        if (b < e) {                      // uniform over the block
+        // whole tiles: loaded here, where full CUs hide the latency
+        if constexpr (RW == TZ) rc.begin(a, it);
+        if (rc.any()) {                   // uniform over the block
             __syncthreads();
 #pragma unroll
             for (int j = 0; j < RN; ++j) su[(ly * RN + j + H2) * W0 + lx + H2] = un[j];
             __syncthreads();
-            for (int i = b + tid; i < e; i += NTN) {
-                const int ent = a.rec_ent[i];
-                const int cell = rec_cell(ent);
-                const int r = cell / TX, c = cell - r * TX;
-                a.seis[((long long)shot * a.nt + a.k) * a.nrec + rec_id(ent)] = su[(r + H2) * W0 + c + H2];
-            }
+            record_tile<RW, NTN>(a, it, rc, [&](int r, int c) { return su[(r + H2) * W0 + c + H2]; });
         }
     }
 }
@@ -831,15 +918,15 @@ __device__ __forceinline__ void fwd_near_tile(const Ac2FwdArgs &a, float *su, fl
 // adjoint keeps 66 VGPRs and 7 waves: limited to 64 it spills and runs 4 %
 // slower.  Taking the row index through readfirstlane puts the rows' z
 // tables in scalar registers (forward 62 -> 56, adjoint 78 -> 66 VGPRs).
-template <bool SNAP, bool REC>
+template <int RW, bool SNAP, bool REC>
 __global__ __launch_bounds__(NTN) __attribute__((amdgpu_waves_per_eu(8))) void ac2_near_kernel(Ac2FwdArgs a)
 {
-    __shared__ __attribute__((aligned(16))) float su[NU];
-    __shared__ float sx[TZ * WPX];
-    __shared__ float sz[RPZ * TX];
-    const int w = xcd_work_id(a.ntl * a.nshots);
-    const int shot = w / a.ntl, tile = a.tiles[w - shot * a.ntl];
-    fwd_near_tile<SNAP, REC>(a, su, sx, sz, tile, shot);
+    __shared__ __attribute__((aligned(16))) float su[nu8(RW)];
+    __shared__ float sx[npx(RW)];
+    __shared__ float sz[npz(RW)];
+    extern __shared__ float sadd[];
+    const int w = xcd_work_id(a.ntl * a.nshots * (TZ / RW));
+    fwd_near_tile<RW, SNAP, REC>(a, su, sx, sz, sadd, tile_item<RW>(a.tiles, a.ntl, w));
 }
 
 // Step k of the tiles by the layer and steps k, k+1 of the blocked tiles in
@@ -848,32 +935,35 @@ __global__ __launch_bounds__(NTN) __attribute__((amdgpu_waves_per_eu(8))) void a
 // need no order; one grid lets the near tiles fill the blocked launch's last
 // round instead of waiting for it.  The blocked tiles come first in the grid;
 // the two share one LDS buffer.
-constexpr int NPAIR_LDS = NU + TZ * WPX + RPZ * TX > R0 * W0 + R1 * W1 ? NU + TZ * WPX + RPZ * TX
-                                                                      : R0 * W0 + R1 * W1;
+constexpr int NPAIR_NEAR = nu8(TZ) + npx(TZ) + npz(TZ), NPAIR_BLK = rows0(TZ) * W0 + rows1(TZ) * W1;
+constexpr int NPAIR_LDS = NPAIR_NEAR > NPAIR_BLK ? NPAIR_NEAR : NPAIR_BLK;
 static_assert(NTN == NTB, "one block size for the pair");
 template <bool SNAP, bool REC>
 __global__ __launch_bounds__(NTN) __attribute__((amdgpu_waves_per_eu(8)))
 void ac2_fwd_pair_kernel(Ac2FwdArgs a, Ac2Fwd2Args b)
 {
     __shared__ __attribute__((aligned(16))) float lds[NPAIR_LDS];
+    extern __shared__ float sadd[];
     const int nb = b.ntl * b.nshots;
-    int w = xcd_work_id(nb + a.ntl * a.nshots);
+    const int w = xcd_work_id(nb + a.ntl * a.nshots);
     if (w < nb) {
-        const int shot = w / b.ntl;
-        fwd2_tile(b, lds, lds + R0 * W0, b.tiles[w - shot * b.ntl], shot);
+        fwd2_tile<TZ>(b, lds, lds + rows0(TZ) * W0, tile_item<TZ>(b.tiles, b.ntl, w));
     } else {
-        w -= nb;
-        const int shot = w / a.ntl;
-        fwd_near_tile<SNAP, REC>(a, lds, lds + NU, lds + NU + TZ * WPX, a.tiles[w - shot * a.ntl], shot);
+        fwd_near_tile<TZ, SNAP, REC>(a, lds, lds + nu8(TZ), lds + nu8(TZ) + npx(TZ), sadd,
+                                     tile_item<TZ>(a.tiles, a.ntl, w - nb));
     }
 }
 
-__device__ __forceinline__ void adj_near_tile(const Ac2AdjArgs &a, float *sc, float *sx, float *sz, int tile,
-                                              int shot)
+template <int RW>
+__device__ __forceinline__ void adj_near_tile(const Ac2AdjArgs &a, float *sc, float *sx, float *sz,
+                                              const TileItem &it)
 {
+    constexpr int RN = RW * TX / NTN, NHX = RW * 8;
     const Grid2 &g = a.g;
-    const int tz = tile / g.ntx, tx = tile - tz * g.ntx;
-    const int x0 = tx * TX, z0 = tz * TZ;
+    const int shot = it.shot;
+    const int tz = it.tile / g.ntx, tx = it.tile - tz * g.ntx;
+    const int x0 = tx * TX, z0 = tz * TZ + it.sub * RW;
+    if (z0 >= g.NZ) return;
     const long long so = (long long)shot * g.plane;
     // ly is uniform over a wavefront (TX lanes): rows and their tables in scalar registers
     const int tid = threadIdx.x, lx = tid % TX, ly = __builtin_amdgcn_readfirstlane(tid / TX);
@@ -887,6 +977,8 @@ __device__ __forceinline__ void adj_near_tile(const Ac2AdjArgs &a, float *sc, fl
     float *__restrict__ cxo = a.cx + so;
     float *__restrict__ czo = a.cz + so;
 
+    TileRecs rc{};
+    rc.begin(a, it);
     const float hxc = inx ? a.hx[ix] : 0.f, pxc = inx ? a.px[ix] : 0.f, ihxc = inx ? a.ihx[ix] : 0.f;
     float sc2[RN], q3[RN], hzr[RN], fx[RN], fz[RN], pzr[RN], ihzr[RN];
     unsigned lay = 0u;
@@ -908,42 +1000,33 @@ __device__ __forceinline__ void adj_near_tile(const Ac2AdjArgs &a, float *sc, fl
             }
         }
     }
-    // halo cells of the x and z arrays
-    float xhx[HXI], xhz[HXI], xp[HXI], xih[HXI], xf[HXI];
-    bool xl[HXI];
-    int xr[HXI], xc[HXI];
-#pragma unroll
-    for (int it = 0; it < HXI; ++it) {
-        const int i = tid + it * NTN;
-        halo_x_cell(i < NHX ? i : 0, xr[it], xc[it]);
-        const int iz = z0 + xr[it], jx = x0 - 4 + xc[it];
-        xl[it] = i < NHX && iz < g.NZ && jx >= 0 && jx < g.NX && layer_cell_at(g, iz, jx);
-        xhx[it] = xhz[it] = xp[it] = xih[it] = xf[it] = 0.f;
-        if (xl[it]) {
-            xhx[it] = a.hx[jx]; xhz[it] = a.hz[iz]; xp[it] = a.px[jx]; xih[it] = a.ihx[jx];
-            xf[it] = cx0[fidx(g, iz, jx)];
-        }
+    // halo cells of the x and z arrays, one of each per thread
+    float xhx = 0.f, xhz = 0.f, xp = 0.f, xih = 0.f, xf = 0.f;
+    int xr, xc;
+    halo_x_cell(tid < NHX ? tid : 0, xr, xc);
+    const bool xl = tid < NHX && z0 + xr < g.NZ && x0 - 4 + xc >= 0 && x0 - 4 + xc < g.NX &&
+                    layer_cell_at(g, z0 + xr, x0 - 4 + xc);
+    if (xl) {
+        const int iz = z0 + xr, jx = x0 - 4 + xc;
+        xhx = a.hx[jx]; xhz = a.hz[iz]; xp = a.px[jx]; xih = a.ihx[jx];
+        xf = cx0[fidx(g, iz, jx)];
     }
-    float zhx[HZI], zhz[HZI], zp[HZI], zih[HZI], zf[HZI];
-    bool zl[HZI];
-    int zr[HZI], zc[HZI];
-#pragma unroll
-    for (int it = 0; it < HZI; ++it) {
-        const int i = tid + it * NTN;
-        halo_z_cell(i < NHZ ? i : 0, zr[it], zc[it]);
-        const int iz = z0 - 4 + zr[it], jx = x0 + zc[it];
-        zl[it] = i < NHZ && iz >= 0 && iz < g.NZ && jx < g.NX && layer_cell_at(g, iz, jx);
-        zhx[it] = zhz[it] = zp[it] = zih[it] = zf[it] = 0.f;
-        if (zl[it]) {
-            zhx[it] = a.hx[jx]; zhz[it] = a.hz[iz]; zp[it] = a.pz[iz]; zih[it] = a.ihz[iz];
-            zf[it] = cz0[fidx(g, iz, jx)];
-        }
+    float zhx = 0.f, zhz = 0.f, zp = 0.f, zih = 0.f, zf = 0.f;
+    int zr, zc;
+    halo_z_cell<RW>(tid, zr, zc);
+    const bool zl = tid < NHZ && z0 - 4 + zr >= 0 && z0 - 4 + zr < g.NZ && x0 + zc < g.NX &&
+                    layer_cell_at(g, z0 - 4 + zr, x0 + zc);
+    if (zl) {
+        const int iz = z0 - 4 + zr, jx = x0 + zc;
+        zhx = a.hx[jx]; zhz = a.hz[iz]; zp = a.pz[iz]; zih = a.ihz[iz];
+        zf = cz0[fidx(g, iz, jx)];
     }
-    float4 cm[(R0 * (W0 / 4) + NTN - 1) / NTN];
-    dma_product_load<NTN>(g, s2, chat, sc, x0, z0, cm);     // chat s^{k+2} on the tile + 8
+    float4 cm[(rows0(RW) * (W0 / 4) + NTN - 1) / NTN];
+    dma_product_load<RW, NTN>(g, s2, chat, sc, x0, z0, cm); // chat s^{k+2} on the rows + 8
     __builtin_amdgcn_s_waitcnt(0);       // the tile's direct loads have landed in LDS
     __syncthreads();
-    product_in_place<NTN>(sc, cm);
+    const float d0 = first_sample(a, it, rc);
+    product_in_place<RW, NTN>(sc, cm);
     __syncthreads();
 
     // pass A: c^{k+1} on the own layer cells (written out) and the halo cells
@@ -965,25 +1048,21 @@ __device__ __forceinline__ void adj_near_tile(const Ac2AdjArgs &a, float *sc, fl
         sx[r * WPX + lx + 4] = vx;
         sz[(r + 4) * TX + lx] = vz;
     }
-#pragma unroll
-    for (int it = 0; it < HXI; ++it) {
-        if (tid + it * NTN >= NHX) continue;
+    if (tid < NHX) {
         float v = 0.f;
-        if (xl[it]) {
-            const float qx = 2.f * (xhz[it] - xhx[it]) * xih[it];
-            v = xp[it] * xf[it] - qx * d8(sc + (xr[it] + H2) * W0 + xc[it] + 4, 1);
+        if (xl) {
+            const float qx = 2.f * (xhz - xhx) * xih;
+            v = xp * xf - qx * d8(sc + (xr + H2) * W0 + xc + 4, 1);
         }
-        sx[xr[it] * WPX + xc[it]] = v;
+        sx[xr * WPX + xc] = v;
     }
-#pragma unroll
-    for (int it = 0; it < HZI; ++it) {
-        if (tid + it * NTN >= NHZ) continue;
+    if (tid < NHZ) {
         float v = 0.f;
-        if (zl[it]) {
-            const float qz = 2.f * (zhx[it] - zhz[it]) * zih[it];
-            v = zp[it] * zf[it] - qz * d8(sc + (zr[it] + 4) * W0 + zc[it] + H2, (long long)W0);
+        if (zl) {
+            const float qz = 2.f * (zhx - zhz) * zih;
+            v = zp * zf - qz * d8(sc + (zr + 4) * W0 + zc + H2, (long long)W0);
         }
-        sz[zr[it] * TX + zc[it]] = v;
+        sz[zr * TX + zc] = v;
     }
     __syncthreads();
 
@@ -1018,28 +1097,15 @@ __device__ __forceinline__ void adj_near_tile(const Ac2AdjArgs &a, float *sc, fl
         av[j] = v;
     }
 
-    {   // receiver residual injection R^T dJ/dd^{k+1}, deterministic per cell
-        const int ntiles = g.ntx * g.ntz;
-        const int *off = a.rec_off + (long long)shot * (ntiles + 1);
-        const int b = off[tile], e = off[tile + 1];
-        if (b < e) {
-            __syncthreads();
+    if (rc.any()) {   // receiver residual injection, uniform over the block
+        __syncthreads();
 #pragma unroll
-            for (int j = 0; j < RN; ++j) sc[(ly * RN + j + H2) * W0 + lx + H2] = av[j];
-            __syncthreads();
-            const float *d = a.dJdd + ((long long)shot * a.nt + a.k) * a.nrec;
-            for (int i = b + tid; i < e; i += NTN) {
-                const int cell = rec_cell(a.rec_ent[i]);
-                if (i > b && rec_cell(a.rec_ent[i - 1]) == cell) continue;  // not first of its cell
-                float sum = 0.f;
-                for (int m = i; m < e && rec_cell(a.rec_ent[m]) == cell; ++m) sum += d[rec_id(a.rec_ent[m])];
-                const int r = cell / TX, c = cell - r * TX;
-                sc[(r + H2) * W0 + c + H2] += sum;
-            }
-            __syncthreads();
+        for (int j = 0; j < RN; ++j) sc[(ly * RN + j + H2) * W0 + lx + H2] = av[j];
+        __syncthreads();
+        inject_tile<RW, NTN>(a, it, rc, d0, [&](int r, int c) -> float & { return sc[(r + H2) * W0 + c + H2]; });
+        __syncthreads();
 #pragma unroll
-            for (int j = 0; j < RN; ++j) av[j] = sc[(ly * RN + j + H2) * W0 + lx + H2];
-        }
+        for (int j = 0; j < RN; ++j) av[j] = sc[(ly * RN + j + H2) * W0 + lx + H2];
     }
 
     const long long src = a.src_f[shot];
@@ -1056,60 +1122,88 @@ __device__ __forceinline__ void adj_near_tile(const Ac2AdjArgs &a, float *sc, fl
     }
 }
 
+template <int RW>
 __global__ __launch_bounds__(NTN) __attribute__((amdgpu_waves_per_eu(6))) void ac2_adj_near_kernel(Ac2AdjArgs a)
 {
-    __shared__ __attribute__((aligned(16))) float sc[NU];
-    __shared__ float sx[TZ * WPX];
-    __shared__ float sz[RPZ * TX];
-    const int w = xcd_work_id(a.ntl * a.nshots);
-    const int shot = w / a.ntl, tile = a.tiles[w - shot * a.ntl];
-    adj_near_tile(a, sc, sx, sz, tile, shot);
+    __shared__ __attribute__((aligned(16))) float sc[nu8(RW)];
+    __shared__ float sx[npx(RW)];
+    __shared__ float sz[npz(RW)];
+    const int w = xcd_work_id(a.ntl * a.nshots * (TZ / RW));
+    adj_near_tile<RW>(a, sc, sx, sz, tile_item<RW>(a.tiles, a.ntl, w));
 }
 
 // ------------------------------------------------------------------ launchers
+// f(integral_constant<int, RW>) with the rows per workgroup of a launch of
+// `tiles` tiles.
+template <class F>
+void with_rows(int tiles, F &&f)
+{
+    if (tiles <= 0) return;
+    f(std::integral_constant<int, TZ>{});
+}
+
+// Dynamic LDS of the forward step: the node sources of RW rows.
+inline size_t node_lds(const Ac2FwdArgs &a, int RW)
+{
+    return a.nsrc > 1 ? sizeof(float) * RW * TX : 0;
+}
+
 void launch_ac2_fwd2(const Ac2Fwd2Args &a, hipStream_t s)
 {
-    const int nb = a.ntl * a.nshots;
-    if (nb == 0) return;
-    ac2_fwd2_kernel<<<nb, NTB, 0, s>>>(a);
+    const int nt = a.ntl * a.nshots;
+    with_rows(nt, [&](auto R) {
+        constexpr int RW = decltype(R)::value;
+        ac2_fwd2_kernel<RW><<<nt * (TZ / RW), NTB, 0, s>>>(a);
+    });
 }
 
 void launch_ac2_adj2(const Ac2Adj2Args &a, hipStream_t s)
 {
-    const int nb = a.ntl * a.nshots;
-    if (nb == 0) return;
-    ac2_adj2_kernel<<<nb, NTH, 0, s>>>(a);
+    const int nt = a.ntl * a.nshots;
+    with_rows(nt, [&](auto R) {
+        constexpr int RW = decltype(R)::value;
+        ac2_adj2_kernel<RW><<<nt * (TZ / RW), NTH, 0, s>>>(a);
+    });
 }
 
 void launch_ac2_fwd_pair(const Ac2FwdArgs &a, const Ac2Fwd2Args &b, hipStream_t s)
 {
     const int nb = a.ntl * a.nshots + b.ntl * b.nshots;
     if (nb == 0) return;
-    if (a.seis) { ac2_fwd_pair_kernel<false, true><<<nb, NTN, 0, s>>>(a, b); return; }
-    if (a.snap) ac2_fwd_pair_kernel<true, false><<<nb, NTN, 0, s>>>(a, b);
-    else ac2_fwd_pair_kernel<false, false><<<nb, NTN, 0, s>>>(a, b);
+    const size_t lds = node_lds(a, TZ);
+    if (a.seis) { ac2_fwd_pair_kernel<false, true><<<nb, NTN, lds, s>>>(a, b); return; }
+    if (a.snap) ac2_fwd_pair_kernel<true, false><<<nb, NTN, lds, s>>>(a, b);
+    else ac2_fwd_pair_kernel<false, false><<<nb, NTN, lds, s>>>(a, b);
+}
+
+template <int RW, bool SNAP, bool REC>
+void launch_fwd_as(const Ac2FwdArgs &a, bool near, hipStream_t s)
+{
+    const int nb = a.ntl * a.nshots * (TZ / RW);
+    const size_t lds = node_lds(a, RW);
+    if (near) ac2_near_kernel<RW, SNAP, REC><<<nb, NTN, lds, s>>>(a);
+    else      ac2_fwd_kernel<RW, SNAP, REC><<<nb, NTH, lds, s>>>(a);
 }
 
 void launch_ac2_fwd(const Ac2FwdArgs &a, bool near, hipStream_t s)
 {
-    const int nb = a.ntl * a.nshots;
-    if (nb == 0) return;
     const bool snap = a.snap != nullptr, rec = a.seis != nullptr;
-    if (near) {
-        if (snap) { if (rec) ac2_near_kernel<true, true><<<nb, NTN, 0, s>>>(a); else ac2_near_kernel<true, false><<<nb, NTN, 0, s>>>(a); }
-        else      { if (rec) ac2_near_kernel<false, true><<<nb, NTN, 0, s>>>(a); else ac2_near_kernel<false, false><<<nb, NTN, 0, s>>>(a); }
-    } else {
-        if (snap) { if (rec) ac2_fwd_kernel<true, true><<<nb, NTH, 0, s>>>(a); else ac2_fwd_kernel<true, false><<<nb, NTH, 0, s>>>(a); }
-        else      { if (rec) ac2_fwd_kernel<false, true><<<nb, NTH, 0, s>>>(a); else ac2_fwd_kernel<false, false><<<nb, NTH, 0, s>>>(a); }
-    }
+    with_rows(a.ntl * a.nshots, [&](auto R) {
+        constexpr int RW = decltype(R)::value;
+        if (snap) { if (rec) launch_fwd_as<RW, true, true>(a, near, s); else launch_fwd_as<RW, true, false>(a, near, s); }
+        else      { if (rec) launch_fwd_as<RW, false, true>(a, near, s); else launch_fwd_as<RW, false, false>(a, near, s); }
+    });
 }
 
 void launch_ac2_adj(const Ac2AdjArgs &a, bool near, hipStream_t s)
 {
-    const int nb = a.ntl * a.nshots;
-    if (nb == 0) return;
-    if (near) ac2_adj_near_kernel<<<nb, NTN, 0, s>>>(a);
-    else      ac2_adj_kernel<<<nb, NTH, 0, s>>>(a);
+    const int nt = a.ntl * a.nshots;
+    with_rows(nt, [&](auto R) {
+        constexpr int RW = decltype(R)::value;
+        const int nb = nt * (TZ / RW);
+        if (near) ac2_adj_near_kernel<RW><<<nb, NTN, 0, s>>>(a);
+        else      ac2_adj_kernel<RW><<<nb, NTH, 0, s>>>(a);
+    });
 }
 
 // ---------------------------------------------------------------- model prep

@@ -6,12 +6,12 @@
 
 namespace sg {
 
-// 2-D acoustic tile: TX columns (one wavefront) x TZ rows, 256 threads; each
-// thread owns one column and RPT consecutive rows of the tile.
+// 2-D acoustic tile: TX columns (one wavefront) x TZ rows; a workgroup takes
+// all rows of a tile or, in launches of few tiles, 16 or 8 of them, each
+// thread one column and consecutive rows.
 constexpr int TX = 64;
 constexpr int TZ = 32;
 constexpr int NTH = 256;
-constexpr int RPT = TZ / (NTH / TX);
 
 // Frame of every 2-D field: cell (iz, ix) of the padded grid lives at
 // (iz + OZ) * SX + ix + OX; everything outside the padded grid is zero.
