@@ -109,7 +109,13 @@ __device__ __forceinline__ bool near_layer(const Grid2 &g, int x0, int z0)
                        z0 - 4 < g.P || z0 + TZ + 4 > g.P + g.nz);
 }
 
-// Work of one workgroup: RW rows of a tile.
+// Rows of a tile per workgroup.  A launch of few tiles is bound by the
+// instruction stream of one wavefront, not by the chip: at 32 rows a thread
+// of a tile by the layer works through 4 rows of about 200 VALU instructions
+// each, 7 us for a launch that leaves most CUs idle.  Tiles are then split
+// into 2 or 4 workgroups of 16 or 8 rows (the halo rows loaded and, by the
+// layer, their phi terms formed by both neighbours).  Every value is formed
+// by the same expression, so results do not depend on the split.
 struct TileItem {
     int tile, shot;
     int sub;              // which RW rows of the tile
@@ -1134,12 +1140,19 @@ __global__ __launch_bounds__(NTN) __attribute__((amdgpu_waves_per_eu(6))) void a
 
 // ------------------------------------------------------------------ launchers
 // f(integral_constant<int, RW>) with the rows per workgroup of a launch of
-// `tiles` tiles.
+// `tiles` tiles: whole tiles where they give every CU two workgroups, else
+// half or quarter tiles.  Measured on forward + recompute + adjoint, us per
+// step, 32 / 16 / 8 rows: 15 tiles 22.3 / - / 15.2; 300 tiles 21.0 / 18.8 /
+// 21.2; 900 tiles 34.8 / 36.8 / 45.5; 192 tiles by the layer and 420 blocked
+// ones, forward alone, 10.9 / 10.4 / 10.2; from 768 tiles the repeated halo work costs more than it fills.
+constexpr int FILL2 = 512;
 template <class F>
 void with_rows(int tiles, F &&f)
 {
     if (tiles <= 0) return;
-    f(std::integral_constant<int, TZ>{});
+    if (tiles >= FILL2) f(std::integral_constant<int, TZ>{});
+    else if (2 * tiles >= FILL2) f(std::integral_constant<int, TZ / 2>{});
+    else f(std::integral_constant<int, TZ / 4>{});
 }
 
 // Dynamic LDS of the forward step: the node sources of RW rows.
