@@ -4,13 +4,14 @@
 // The paper's inversions use L-BFGS-B (Applications, FWI); here the bounds
 // are kept by clipping the model after each step and the direction is the
 // two-loop recursion (Nocedal & Wright, Algorithm 7.4).  Models of a batch
-// keep separate histories; one workgroup of 1024 threads serves one model,
-// every inner product is an FP64 block reduction in a fixed order, so the
-// direction is bitwise reproducible.
+// keep separate histories; every inner product is an FP64 reduction in a
+// fixed order, so the direction is bitwise reproducible.
 #include "../../include/seisgrad.h"
 #include "sg_error.h"
 
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
 
 using sg::fail;
 
@@ -18,46 +19,320 @@ namespace {
 
 constexpr int LB_THREADS = 1024;
 constexpr int LB_MAXMEM = 64;
+constexpr int LB_CHUNKS = 256;   // workgroups per model of the partial sums, at most
+static_assert(LB_CHUNKS <= LB_THREADS && 4 * LB_CHUNKS <= 16 * LB_THREADS, "partial sums fit");
 
-// Sum of one double per thread in a fixed tree order; every thread gets it.
+// Sum of one double per thread in a fixed order (wavefront tree, then the
+// wavefronts in turn); every thread gets it.
 __device__ double block_sum(double v, double *red)
 {
-    red[threadIdx.x] = v;
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
-    for (int s = LB_THREADS / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-        __syncthreads();
-    }
-    const double r = red[0];
+    double r = 0.0;
+    for (int i = 0; i < LB_THREADS / 64; ++i) r += red[i];
     __syncthreads();
     return r;
 }
 
-__global__ __launch_bounds__(LB_THREADS) void lbfgs_push_kernel(int nmodels, long long n, int mem,
+// A model's vectors are only 4-byte aligned (n may be odd): doubles in two words.
+__device__ __forceinline__ void put_f64(float *p, double v)
+{
+    const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+    p[0] = __uint_as_float((unsigned)u);
+    p[1] = __uint_as_float((unsigned)(u >> 32));
+}
+__device__ __forceinline__ double get_f64(const float *p)
+{
+    return __longlong_as_double((long long)(__float_as_uint(p[0]) | (unsigned long long)__float_as_uint(p[1]) << 32));
+}
+
+// s, y of the models that store a pair, and their sums (y.s, y.y).  Elements
+// are loaded NL at a time: with one in flight per thread a model of 10201
+// elements took ten memory latencies.  ONE: one workgroup per model, which
+// writes the sums.  Otherwise nb workgroups per model leave their two partial
+// sums in the first 4 nb elements of the stored y, which lbfgs_pair_kernel
+// adds up and then replaces by the elements.
+template <bool ONE>
+__global__ __launch_bounds__(LB_THREADS) void lbfgs_push_kernel(int nmodels, long long n, int mem, int nb,
                                                                 const int *slot, const float *m_new,
                                                                 const float *m_old, const float *g_new,
-                                                                const float *g_old, float *S, float *Y,
-                                                                double *ysyy)
+                                                                const float *g_old, float *S, float *Y, double *ysyy)
 {
-    __shared__ double red[LB_THREADS];
-    const int b = blockIdx.x;
+    constexpr int NL = 4;
+    __shared__ double red[LB_THREADS / 64];
+    const int b = blockIdx.x / nb, blk = blockIdx.x - b * nb;
     const int k = slot[b];
     if (k < 0 || k >= mem) return;                 // this model keeps its history unchanged
     const long long o = (long long)b * n;
     float *s = S + ((long long)k * nmodels + b) * n, *y = Y + ((long long)k * nmodels + b) * n;
     double ys = 0.0, yy = 0.0;
-    for (long long i = threadIdx.x; i < n; i += LB_THREADS) {
-        const float si = m_new[o + i] - m_old[o + i], yi = g_new[o + i] - g_old[o + i];
-        s[i] = si;
-        y[i] = yi;
-        ys += (double)yi * si;
-        yy += (double)yi * yi;
+    for (long long i0 = blk * (long long)(NL * LB_THREADS) + threadIdx.x; i0 < n;
+         i0 += nb * (long long)(NL * LB_THREADS)) {
+        float mn[NL], mo[NL], gn[NL], go[NL];
+#pragma unroll
+        for (int j = 0; j < NL; ++j) {
+            const long long i = min(i0 + j * LB_THREADS, n - 1);
+            mn[j] = m_new[o + i]; mo[j] = m_old[o + i]; gn[j] = g_new[o + i]; go[j] = g_old[o + i];
+        }
+#pragma unroll
+        for (int j = 0; j < NL; ++j) {
+            const long long i = i0 + j * LB_THREADS;
+            if (i >= n) break;
+            const float si = mn[j] - mo[j], yi = gn[j] - go[j];
+            s[i] = si;
+            if (ONE || i >= 4 * nb) y[i] = yi;
+            ys += (double)yi * si;
+            yy += (double)yi * yi;
+        }
     }
     ys = block_sum(ys, red);
     yy = block_sum(yy, red);
     if (threadIdx.x == 0) {
+        if constexpr (ONE) {
+            ysyy[2 * ((long long)k * nmodels + b)] = ys;
+            ysyy[2 * ((long long)k * nmodels + b) + 1] = yy;
+        } else {
+            put_f64(y + 4 * blk, ys);
+            put_f64(y + 4 * blk + 2, yy);
+        }
+    }
+}
+
+// The sums of the pairs just formed from their nb <= LB_THREADS partial sums,
+// then the elements of y that held them; one workgroup per model.
+__global__ __launch_bounds__(LB_THREADS) void lbfgs_pair_kernel(int nmodels, long long n, int mem, int nb,
+                                                                const int *slot, const float *g_new,
+                                                                const float *g_old, float *Y, double *ysyy)
+{
+    __shared__ double red[LB_THREADS / 64];
+    const int b = blockIdx.x;
+    const int k = slot[b];
+    if (k < 0 || k >= mem) return;
+    const long long o = (long long)b * n;
+    float *y = Y + ((long long)k * nmodels + b) * n;
+    const int t = threadIdx.x;
+    double ys = t < nb ? get_f64(y + 4 * t) : 0.0, yy = t < nb ? get_f64(y + 4 * t + 2) : 0.0;
+    ys = block_sum(ys, red);
+    yy = block_sum(yy, red);              // its barriers: every partial sum has been read
+    for (int i = t; i < 4 * nb; i += LB_THREADS) y[i] = g_new[o + i] - g_old[o + i];
+    if (t == 0) {
         ysyy[2 * ((long long)k * nmodels + b)] = ys;
         ysyy[2 * ((long long)k * nmodels + b) + 1] = yy;
+    }
+}
+
+// ---------------------------------------------------- direction over the chip
+// The two-loop recursion needs q only in inner products with the stored
+// vectors, so with the products of the vectors among themselves and with g
+// in hand it runs on scalars (FP64):
+//   s_i.q_i = s_i.g - sum_{j newer} alpha_j s_i.y_j
+//   y_i.r_i = gamma (y_i.g - sum_j alpha_j y_i.y_j) + sum_{j older} (alpha_j - beta_j) y_i.s_j
+// and p = -(gamma (g - sum alpha_j y_j) + sum (alpha_j - beta_j) s_j).  The
+// vectors are read twice, by every CU, instead of once per loop step by one
+// workgroup whose every step waits for the reduction before it (push +
+// direction, 8 pairs: 20 models of 10201 elements 76 -> 30 us, 200 models 129 ->
+// 82 us, one model of 500000 4.85 ms -> 45 us).
+// The products are summed per chunk of elements and then over the chunks in
+// order.  The partial sums and then the coefficients live in p, which is
+// written last: the coefficients in its first LB_HEAD floats, whose elements
+// a launch of their own forms.
+constexpr int LB_CMAX = 15;      // pairs: the columns (y of each, g) fill one matrix tile, the rows two
+constexpr int LB_SUB = 512;      // chunks are multiples of this many elements
+constexpr int LB_GT = 256;
+constexpr int LB_HEAD = 64;      // floats
+static_assert(2 * (2 * LB_CMAX + 1) <= LB_HEAD, "the coefficients fit the head");
+
+// Products of c pairs, newest first: s_i.g, y_i.g, then for j < i (j newer) s_i.y_j and y_i.y_j.
+__host__ __device__ constexpr int lb_dots(int c) { return c * c + c; }
+__device__ __forceinline__ int lb_sg(int i) { return 2 * i; }
+__device__ __forceinline__ int lb_yg(int i) { return 2 * i + 1; }
+__device__ __forceinline__ int lb_sy(int c, int i, int j) { return 2 * c + i * (i - 1) + 2 * j; }
+__device__ __forceinline__ int lb_yy(int c, int i, int j) { return lb_sy(c, i, j) + 1; }
+
+struct LbHist {
+    int newest, count;
+    __device__ LbHist(const int *hist, int b, int mem)
+    {
+        newest = hist[2 * b + 1];
+        count = (newest < 0 || newest >= mem) ? 0 : max(0, min(hist[2 * b], mem));
+    }
+    __device__ int slot(int j, int mem) const { return (newest - j + mem) % mem; }   // j = 0: newest
+};
+
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));   // a vector's elements are 4-byte aligned
+
+// One chunk of one model: its share of every product, on the FP64 matrix
+// cores: rows (s, y by pair, 16 per tile) times columns (y by pair, then g),
+// K = elements.  A wavefront takes every fourth run of 16 LB_U elements; lane
+// (row or column l mod 16, l / 16) loads four neighbouring elements of each 16
+// and gives them to four instructions (both operands the same elements, so
+// their order within K is free).  The four wavefronts' sums are added in
+// turn.  (Products formed one after another on staged vectors: 20 us against
+// the 3 us of the loads for 20 models of 10201, 8 pairs.)
+constexpr int LB_U = 4;
+template <int TILES>
+__global__ __launch_bounds__(LB_GT) void lbfgs_products_kernel(int nmodels, long long n, int mem, int nchunks,
+                                                               long long chunk, const int *hist, const float *S,
+                                                               const float *Y, const float *g, float *p)
+{
+    constexpr int WAVES = LB_GT / 64;
+    __shared__ double part[WAVES][TILES * 16][17];
+    const int b = blockIdx.x / nchunks, ch = blockIdx.x - b * nchunks;
+    const LbHist h(hist, b, mem);
+    const int c = h.count;
+    const long long o = (long long)b * n;
+    const long long lo = ch * chunk, hi = min(n, lo + chunk);
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int rc = lane & 15, kk = lane >> 4;
+    // vector q of the products (2 pair: s, 2 pair + 1: y, 2 c: g); g for an unused row or column
+    auto vec = [&](int q) {
+        return q >= 2 * c ? g + o : (q & 1 ? Y : S) + ((long long)h.slot(q >> 1, mem) * nmodels + b) * n;
+    };
+    const float *A[TILES], *B = vec(min(2 * rc + 1, 2 * c));
+    f64x4 acc[TILES];
+#pragma unroll
+    for (int t = 0; t < TILES; ++t) {
+        A[t] = vec(16 * t + rc);
+        acc[t] = f64x4{0.0, 0.0, 0.0, 0.0};
+    }
+    for (long long e0 = lo + wv * 16 * LB_U; e0 < hi; e0 += WAVES * 16 * LB_U) {
+        f32x4u xa[TILES][LB_U], xb[LB_U];
+        if (e0 + 16 * LB_U <= hi) {
+#pragma unroll
+            for (int u = 0; u < LB_U; ++u) {
+                const long long e = e0 + 16 * u + 4 * kk;
+                xb[u] = *reinterpret_cast<const f32x4u *>(B + e);
+#pragma unroll
+                for (int t = 0; t < TILES; ++t) xa[t][u] = *reinterpret_cast<const f32x4u *>(A[t] + e);
+            }
+        } else {                          // the end of the chunk: elements past it are zero
+#pragma unroll
+            for (int u = 0; u < LB_U; ++u)
+#pragma unroll
+                for (int m = 0; m < 4; ++m) {
+                    const long long e = e0 + 16 * u + 4 * kk + m, ec = min(e, hi - 1);
+                    const float bv = B[ec];
+                    xb[u][m] = e < hi ? bv : 0.f;
+#pragma unroll
+                    for (int t = 0; t < TILES; ++t) {
+                        const float av = A[t][ec];
+                        xa[t][u][m] = e < hi ? av : 0.f;
+                    }
+                }
+        }
+#pragma unroll
+        for (int u = 0; u < LB_U; ++u)
+#pragma unroll
+            for (int m = 0; m < 4; ++m)
+#pragma unroll
+                for (int t = 0; t < TILES; ++t)
+                    acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)xa[t][u][m], (double)xb[u][m], acc[t], 0, 0, 0);
+    }
+    // register m of lane (column rc, kk) holds row 4 m + kk
+#pragma unroll
+    for (int t = 0; t < TILES; ++t)
+#pragma unroll
+        for (int m = 0; m < 4; ++m) part[wv][16 * t + 4 * m + kk][rc] = acc[t][m];
+    __syncthreads();
+    float *out = p + o + LB_HEAD + 2ll * ch * lb_dots(mem);
+    auto put = [&](int d, int row, int col) {
+        double t = 0.0;
+        for (int w = 0; w < WAVES; ++w) t += part[w][row][col];
+        put_f64(out + 2 * d, t);
+    };
+    for (int q = threadIdx.x; q < 2 * c * (c + 1); q += LB_GT) {
+        const int row = q / (c + 1), j = q - row * (c + 1), i = row >> 1;
+        if (j == c) put(row & 1 ? lb_yg(i) : lb_sg(i), row, c);
+        else if (j < i) put(row & 1 ? lb_yy(c, i, j) : lb_sy(c, i, j), row, j);
+    }
+}
+
+// The scalar recursion of one model; coefficients of g, then of (s, y) by
+// pair.  Eight lanes add up a product's chunks (l, l + 8, ..), then the
+// lanes in turn; in the recursion lane i carries pair i.
+__global__ __launch_bounds__(LB_THREADS) void lbfgs_scalars_kernel(int nmodels, long long n, int mem, int nchunks,
+                                                                   const int *hist, const double *ysyy, float *p)
+{
+    constexpr int NL = 8;
+    __shared__ double dot[lb_dots(LB_CMAX)];
+    const int b = blockIdx.x;
+    const LbHist h(hist, b, mem);
+    const int c = h.count, nd = lb_dots(c);
+    float *pm = p + (long long)b * n;
+    for (int d0 = 0; d0 < nd; d0 += LB_THREADS / 8) {
+        const int d = d0 + (int)(threadIdx.x >> 3), l = threadIdx.x & 7;
+        const float *src = pm + LB_HEAD + 2ll * min(d, nd - 1);
+        double t = 0.0;
+        for (int q0 = l; q0 < nchunks; q0 += 8 * NL) {
+            double x[NL];
+#pragma unroll
+            for (int q = 0; q < NL; ++q)
+                x[q] = q0 + 8 * q < nchunks ? get_f64(src + 2ll * (q0 + 8 * q) * lb_dots(mem)) : 0.0;
+#pragma unroll
+            for (int q = 0; q < NL; ++q) t += x[q];
+        }
+        double sum = 0.0;
+        for (int q = 0; q < 8; ++q) sum += __shfl(t, q, 8);
+        if (l == 0 && d < nd) dot[d] = sum;
+    }
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
+    const int i = threadIdx.x, ic = min(i, max(c - 1, 0));
+    double ys = 1.0, yy = 1.0;
+    if (i < c) {
+        const long long k = (long long)h.slot(i, mem) * nmodels + b;
+        ys = ysyy[2 * k];
+        yy = ysyy[2 * k + 1];
+    }
+    const double gamma = c > 0 ? __shfl(ys, 0, 64) / __shfl(yy, 0, 64) : 1.0;
+    double t = c > 0 ? dot[lb_sg(ic)] : 0.0, al = 0.0, u = c > 0 ? dot[lb_yg(ic)] : 0.0, cs = 0.0;
+    for (int j = 0; j < c; ++j) {
+        if (i == j) al = t / ys;
+        const double aj = __shfl(al, j, 64);
+        if (i > j && i < c) t -= aj * dot[lb_sy(c, ic, j)];
+        if (i < c) u -= aj * (i == j ? yy : i > j ? dot[lb_yy(c, ic, j)] : dot[lb_yy(c, j, ic)]);
+    }
+    u *= gamma;
+    for (int j = c - 1; j >= 0; --j) {
+        if (i == j) cs = al - u / ys;
+        const double cj = __shfl(cs, j, 64);
+        if (i < j) u += cj * dot[lb_sy(c, j, ic)];
+    }
+    if (i == 0) put_f64(pm, -gamma);
+    if (i < c) {
+        put_f64(pm + 2 + 4 * i, -cs);
+        put_f64(pm + 4 + 4 * i, gamma * al);
+    }
+}
+
+// p of the elements after the head, or of the head alone (HEAD: one workgroup
+// per model, the coefficients read before any is overwritten).
+template <bool HEAD>
+__global__ __launch_bounds__(LB_GT) void lbfgs_combine_kernel(int nmodels, long long n, int mem, int nb,
+                                                              const int *hist, const float *S, const float *Y,
+                                                              const float *g, float *p)
+{
+    __shared__ double co[2 * LB_CMAX + 1];
+    const int b = blockIdx.x / nb;
+    const LbHist h(hist, b, mem);
+    const int c = h.count;
+    const long long o = (long long)b * n;
+    float *pm = p + o;
+    if ((int)threadIdx.x < 2 * c + 1) co[threadIdx.x] = get_f64(pm + 2 * threadIdx.x);
+    __syncthreads();
+    const long long last = HEAD ? LB_HEAD : n;
+    for (long long i = (HEAD ? 0 : LB_HEAD) + (blockIdx.x - b * nb) * (long long)LB_GT + threadIdx.x; i < last;
+         i += nb * (long long)LB_GT) {
+        double t = co[0] * g[o + i];
+#pragma unroll 4
+        for (int j = 0; j < c; ++j) {
+            const long long k = ((long long)h.slot(j, mem) * nmodels + b) * n + i;
+            t += co[1 + 2 * j] * S[k];
+            t += co[2 + 2 * j] * Y[k];
+        }
+        pm[i] = (float)t;
     }
 }
 
@@ -68,7 +343,7 @@ __global__ __launch_bounds__(LB_THREADS) void lbfgs_direction_kernel(int nmodels
                                                                      const float *Y, const double *ysyy,
                                                                      const float *g, float *p)
 {
-    __shared__ double red[LB_THREADS];
+    __shared__ double red[LB_THREADS / 64];
     __shared__ double alpha[LB_MAXMEM];
     const int b = blockIdx.x;
     const int newest = hist[2 * b + 1];
@@ -123,8 +398,18 @@ int lbfgs_push(int32_t nmodels, int64_t n, int32_t mem, const int32_t *slot, con
         return fail(SG_EINVAL, "need nmodels, n >= 1 and 1 <= mem <= %d", LB_MAXMEM);
     if (!slot || !m_new || !m_old || !g_new || !g_old || !S || !Y || !ysyy)
         return fail(SG_EINVAL, "NULL pointer argument");
-    lbfgs_push_kernel<<<nmodels, LB_THREADS, 0, (hipStream_t)stream>>>(nmodels, n, mem, slot, m_new, m_old, g_new,
-                                                                       g_old, S, Y, ysyy);
+    hipStream_t st = (hipStream_t)stream;
+    // short vectors: one workgroup per model forms the pair and its sums
+    // (10201 elements: two launches would cost more than they spread)
+    if (n <= 16 * LB_THREADS || nmodels > (1 << 20)) {
+        lbfgs_push_kernel<true><<<nmodels, LB_THREADS, 0, st>>>(nmodels, n, mem, 1, slot, m_new, m_old, g_new, g_old,
+                                                                S, Y, ysyy);
+    } else {
+        const int nb = (int)std::min<long long>((n + 4 * LB_THREADS - 1) / (4 * LB_THREADS), LB_CHUNKS);
+        lbfgs_push_kernel<false><<<nmodels * nb, LB_THREADS, 0, st>>>(nmodels, n, mem, nb, slot, m_new, m_old, g_new,
+                                                                      g_old, S, Y, ysyy);
+        lbfgs_pair_kernel<<<nmodels, LB_THREADS, 0, st>>>(nmodels, n, mem, nb, slot, g_new, g_old, Y, ysyy);
+    }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(SG_EDEVICE, "lbfgs_push launch: %s", hipGetErrorString(e));
     return SG_OK;
@@ -137,7 +422,28 @@ int lbfgs_direction(int32_t nmodels, int64_t n, int32_t mem, const int32_t *hist
         return fail(SG_EINVAL, "need nmodels, n >= 1 and 1 <= mem <= %d", LB_MAXMEM);
     if (!hist || !S || !Y || !ysyy || !g || !p) return fail(SG_EINVAL, "NULL pointer argument");
     if (p == g) return fail(SG_EINVAL, "p must not alias g");
-    lbfgs_direction_kernel<<<nmodels, LB_THREADS, 0, (hipStream_t)stream>>>(nmodels, n, mem, hist, S, Y, ysyy, g, p);
+    hipStream_t st = (hipStream_t)stream;
+    // The products over the whole chip where p has room for two chunks' partial
+    // sums; long histories and short loops keep one workgroup per model (push +
+    // direction, loop / products: 2500 elements, 5 pairs 27.2 / 28.3 us; 1000, 8
+    // 31.9 / 27.4; 6000, 5 38.8 / 28.7; both launches near the host's rate).
+    const int per = 2 * lb_dots(std::min<int>(mem, LB_CMAX));     // floats of a chunk's partial sums
+    if (mem <= LB_CMAX && n >= LB_HEAD + 2 * per && mem * (n + 3000) >= 30000 && nmodels <= (1 << 20)) {
+        const long long room = std::min<long long>((n - LB_HEAD) / per, LB_CHUNKS);
+        const long long want = std::min<long long>((n + LB_SUB - 1) / LB_SUB, room);
+        const long long chunk = ((n + want - 1) / want + LB_SUB - 1) / LB_SUB * LB_SUB;
+        const int nchunks = (int)((n + chunk - 1) / chunk);
+        if (mem <= 8)
+            lbfgs_products_kernel<1><<<nmodels * nchunks, LB_GT, 0, st>>>(nmodels, n, mem, nchunks, chunk, hist, S, Y, g, p);
+        else
+            lbfgs_products_kernel<2><<<nmodels * nchunks, LB_GT, 0, st>>>(nmodels, n, mem, nchunks, chunk, hist, S, Y, g, p);
+        lbfgs_scalars_kernel<<<nmodels, LB_THREADS, 0, st>>>(nmodels, n, mem, nchunks, hist, ysyy, p);
+        const int nb = (int)std::min<long long>((n - LB_HEAD + LB_GT - 1) / LB_GT, std::max(1, 16384 / nmodels));
+        lbfgs_combine_kernel<false><<<nmodels * nb, LB_GT, 0, st>>>(nmodels, n, mem, nb, hist, S, Y, g, p);
+        lbfgs_combine_kernel<true><<<nmodels, LB_GT, 0, st>>>(nmodels, n, mem, 1, hist, S, Y, g, p);
+    } else {
+        lbfgs_direction_kernel<<<nmodels, LB_THREADS, 0, st>>>(nmodels, n, mem, hist, S, Y, ysyy, g, p);
+    }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(SG_EDEVICE, "lbfgs_direction launch: %s", hipGetErrorString(e));
     return SG_OK;
