@@ -33,24 +33,33 @@
 // snapshot loads of the adjoint stay cached, since the half-node averages
 // read each of them from two rows (streaming them cost 16 % of the adjoint).
 #include <algorithm>
+#include <type_traits>
 #include "ad2_internal.h"
+
+// Multiply-adds are fused only where written as fmaf: whether the compiler
+// would fuse the others depends on the rows per workgroup, and a shot's
+// values must not.
+#pragma clang fp contract(off)
 
 namespace sg {
 namespace {
 
-// 512 threads per 64 x 32 tile, 4 rows each: 8 waves per SIMD, against 5
-// with 256 threads of 8 rows (C2 grid: forward 391 -> 347 us, adjoint 480 ->
-// 450 us per step).  A thread's rows are uniform over its wavefront (TX
-// lanes); taken through readfirstlane, they put the z tables in scalar
-// registers (46-62 VGPRs against 61-65, with a spill, before), which leaves
-// room to load the adjoint's gradient accumulator with the other operands
-// before the first barrier (adjoint 457 -> 413 us per step).
+// A workgroup takes 16 rows of a 64 x 32 tile, 512 threads of 2 rows each,
+// at 8 waves per SIMD, or 8 rows in launches of fewer than FILL_AD2 tiles.
+// Whole tiles (4 rows per thread) leave no registers to load the layer
+// memories and snapshots before the first barrier, and a wavefront's longer
+// instruction stream bounds a launch of few tiles.  Forward + recompute +
+// adjoint, us per step, 32 / 16 / 8 rows: 36 tiles 34.1 / - / 21.7; 108 tiles
+// 39.1 / 25.1 / 26.2; 144 tiles 38.3 / 27.0 / 28.9; 864 tiles 80 / 71 / 95;
+// 19584 tiles (1000 x 500 + 32-cell layer, 64 shots) 1126 / 1103 / -.  A
+// thread's rows are uniform over its wavefront (TX lanes); taken through
+// readfirstlane, they put the z tables in scalar registers.
+constexpr int FILL_AD2 = 96;
 constexpr int NTA = 512;
-constexpr int RPA = TZ * TX / NTA;
-static_assert(RPA * NTA == TZ * TX && NTA % TX == 0, "whole rows per thread");
+static_assert(8 * TX % NTA == 0 && NTA % TX == 0, "whole rows per thread");
 constexpr int AH = 3;              // halo of the composite stencil Dm' khat Dp'
-constexpr int AW = TX + 2 * AH;    // node tile with halo: AR rows of AW
-constexpr int AR = TZ + 2 * AH;
+constexpr int AW = TX + 2 * AH;    // node tile with halo: RW + 2 AH rows of AW
+constexpr int nodes(int RW) { return (RW + 2 * AH) * AW; }
 constexpr int QXW = TX + 3;        // x half nodes x0-2 .. x0+TX on each row of the tile
 constexpr float S1 = (float)(9.0 / 8.0);
 constexpr float S2 = (float)(-1.0 / 24.0);
@@ -79,26 +88,71 @@ __device__ __forceinline__ int xcd_id(int nblocks)
 
 // Does the tile or its 3-node halo reach the absorbing layer or the edge of
 // the grid (layer memories, masks of the half-node range)?
+template <int RW>
 __device__ __forceinline__ bool near_edge(const Grid2 &g, int x0, int z0)
 {
-    return x0 - AH < g.P || x0 + TX + AH > g.P + g.nx || z0 - AH < g.P || z0 + TZ + AH > g.P + g.nz;
+    return x0 - AH < g.P || x0 + TX + AH > g.P + g.nx || z0 - AH < g.P || z0 + RW + AH > g.P + g.nz;
 }
 
-// acc[cell] = sum of val(entry) over the tile's entries [b, e) of each local
-// cell (acc: TX*TZ floats, zeroed here).  Entries are sorted by cell; the
-// first entry of each cell sums its run in entry order, so duplicates add up
-// deterministically.  Every thread of the block must call this.
-template <class CellOf, class ValOf>
-__device__ __forceinline__ void gather_entries(float *acc, const int *ent, int b, int e, CellOf cell_of, ValOf val_of)
+// RW rows (sub) of a tile.
+struct Rows {
+    int tile, shot, sub, x0, z0;
+};
+template <int RW>
+__device__ __forceinline__ Rows rows_of(const Grid2 &g, int nshots)
 {
-    for (int i = threadIdx.x; i < TX * TZ; i += NTA) acc[i] = 0.f;
+    constexpr int NS = TZ / RW;
+    const int ntl = g.ntx * g.ntz;
+    const int w = xcd_id(ntl * nshots * NS), t = w / NS;
+    Rows o;
+    o.sub = w - t * NS;
+    o.shot = t / ntl;
+    o.tile = t - o.shot * ntl;
+    const int tz = o.tile / g.ntx, tx = o.tile - tz * g.ntx;
+    o.x0 = tx * TX;
+    o.z0 = tz * TZ + o.sub * RW;
+    return o;
+}
+
+// A tile's source or receiver entries: the range, and this thread's first
+// entry with its value, loaded early.
+struct Entries {
+    int b, e, ent;
+    float v;
+    __device__ __forceinline__ void range(const int *off, const int *list, const Rows &o, int ntiles)
+    {
+        off += (long long)o.shot * (ntiles + 1);
+        b = off[o.tile];
+        e = off[o.tile + 1];
+        ent = b + (int)threadIdx.x < e ? list[b + threadIdx.x] : 0;
+        v = 0.f;
+    }
+    template <class F>
+    __device__ __forceinline__ void first(F val_of)
+    {
+        if (b + (int)threadIdx.x < e) v = val_of(ent);
+    }
+    __device__ __forceinline__ bool any() const { return b < e; }
+};
+
+// acc[cell] = sum of add(sum, value) over the tile's entries of each cell of
+// these RW rows (acc: TX*RW floats, zeroed here).  Entries are sorted by
+// cell; the first entry of each cell sums its run in entry order, so
+// duplicates add up deterministically.  Every thread of the block must call
+// this.
+template <int RW, class CellOf, class ValOf, class Add>
+__device__ __forceinline__ void gather_entries(float *acc, const int *ent, const Entries &en, int sub, CellOf cell_of,
+                                               ValOf val_of, Add add)
+{
+    for (int i = threadIdx.x; i < TX * RW; i += NTA) acc[i] = 0.f;
     __syncthreads();
-    for (int i = b + (int)threadIdx.x; i < e; i += NTA) {
-        const int c = cell_of(ent[i]);
-        if (i > b && cell_of(ent[i - 1]) == c) continue;
-        float v = 0.f;
-        for (int j = i; j < e && cell_of(ent[j]) == c; ++j) v += val_of(ent[j]);
-        acc[c] = v;
+    for (int i = en.b + (int)threadIdx.x; i < en.e; i += NTA) {
+        const bool pre = i == en.b + (int)threadIdx.x;
+        const int x = pre ? en.ent : ent[i], c = cell_of(x), own = c - sub * RW * TX;
+        if (own < 0 || own >= RW * TX || (i > en.b && cell_of(ent[i - 1]) == c)) continue;
+        float v = add(0.f, pre ? en.v : val_of(x));
+        for (int j = i + 1; j < en.e && cell_of(ent[j]) == c; ++j) v = add(v, val_of(ent[j]));
+        acc[own] = v;
     }
     __syncthreads();
 }
@@ -112,9 +166,10 @@ __device__ __forceinline__ void gather_entries(float *acc, const int *ent, int b
 // threads).  chat of the own column is read once per thread; the right
 // neighbour's comes from the next lane (one wavefront = one tile row).  The
 // z part runs first so that only Hz and u^k of the own rows stay live.
+// psi: psi'x^k there.
 template <bool NEAR, bool SNAP>
 __device__ __forceinline__ float fwd_xflux(const Ad2FwdArgs &a, const float *su, long long so, int x0, int z0, int r,
-                                           int h, float c0, float c1)
+                                           int h, float c0, float c1, float psi)
 {
     const Grid2 &g = a.g;
     const int iz = z0 + r, ix = x0 - 2 + h;
@@ -126,7 +181,7 @@ __device__ __forceinline__ float fwd_xflux(const Ad2FwdArgs &a, const float *su,
         const bool own = h >= 2 && h < TX + 2 && iz < g.NZ;
         float S = G;
         if constexpr (NEAR) {
-            const float p = fmaf(a.t.bhx[ix], a.psx[so + f], a.t.ahx[ix] * G);
+            const float p = fmaf(a.t.bhx[ix], psi, a.t.ahx[ix] * G);
             S = G + p;
             if (own) a.psxn[so + f] = p;
         }
@@ -138,12 +193,12 @@ __device__ __forceinline__ float fwd_xflux(const Ad2FwdArgs &a, const float *su,
     return q;
 }
 
-template <bool NEAR, bool SNAP, bool REC>
-__device__ __forceinline__ void fwd_tile(const Ad2FwdArgs &a, float *su, float *qx, int tile, int shot)
+template <int RW, bool NEAR, bool SNAP, bool REC>
+__device__ __forceinline__ void fwd_tile(const Ad2FwdArgs &a, float *su, float *qx, const Rows &o)
 {
+    constexpr int RPA = RW * TX / NTA;
     const Grid2 &g = a.g;
-    const int tz = tile / g.ntx, tx = tile - tz * g.ntx;
-    const int x0 = tx * TX, z0 = tz * TZ;
+    const int x0 = o.x0, z0 = o.z0, shot = o.shot;
     const long long so = (long long)shot * g.plane;
     const float *u = a.u + so;
     const float *ch = a.chat + (long long)(shot / a.shots_per_model) * g.plane;
@@ -153,7 +208,7 @@ __device__ __forceinline__ void fwd_tile(const Ad2FwdArgs &a, float *su, float *
     // lane and load into consecutive LDS words (item order is the row-major
     // order of su); every cell lies inside the zero frame
     {
-        constexpr int NV = AR * AW, K = (NV + NTA - 1) / NTA;
+        constexpr int NV = nodes(RW), K = (NV + NTA - 1) / NTA;
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             const int i = tid + k * NTA;
@@ -171,6 +226,29 @@ __device__ __forceinline__ void fwd_tile(const Ad2FwdArgs &a, float *su, float *
     float um[RPA];                        // u^{k-1} of the own rows, loaded early
 #pragma unroll
     for (int j = 0; j < RPA; ++j) um[j] = __builtin_nontemporal_load(a.um + so + fr(g, z0 + r0 + j, ix));
+    const int ntiles = g.ntx * g.ntz;
+    Entries src{}, rec{};
+    src.range(a.src_off, a.src_ent, o, ntiles);
+    if constexpr (REC) rec.range(a.rec_off, a.rec_ent, o, ntiles);
+    const float *w = a.wav + (long long)shot * a.nsrc * a.nt + a.k;
+    auto sample = [&](int e) { return w[(long long)src_node(e) * a.nt]; };
+    // layer memories: psi'z of the own column's half rows, psi'x of
+    // the own half nodes and of this thread's extra column, xi' of the own rows
+    float pz0[RPA + 3], px0[RPA], pxe = 0.f, xx0[RPA], xz0[RPA];
+    const int er = tid / 3, ee = tid - 3 * er, eh = ee == 2 ? TX + 2 : ee;   // extra column: row, half node
+    if constexpr (NEAR) {
+#pragma unroll
+        for (int m = 0; m < RPA + 3; ++m) pz0[m] = a.psz[so + fr(g, z0 + r0 - 2 + m, ix)];
+#pragma unroll
+        for (int j = 0; j < RPA; ++j) {
+            const long long f = so + fr(g, z0 + r0 + j, ix);
+            px0[j] = a.psx[f];
+            xx0[j] = __builtin_nontemporal_load(a.xix + f);
+            xz0[j] = __builtin_nontemporal_load(a.xiz + f);
+        }
+        if (tid < 3 * RW) pxe = a.psx[so + fr(g, z0 + er, x0 - 2 + eh)];
+    }
+    src.first(sample);
     __builtin_amdgcn_s_waitcnt(0);       // the tile's direct loads have landed in LDS
     __syncthreads();
 
@@ -191,7 +269,7 @@ __device__ __forceinline__ void fwd_tile(const Ad2FwdArgs &a, float *su, float *
                 const bool own = m >= 2 && m < RPA + 2 && ix < g.NX;
                 float S = G;
                 if constexpr (NEAR) {
-                    const float p = fmaf(a.t.bhz[iz], a.psz[so + f], a.t.ahz[iz] * G);
+                    const float p = fmaf(a.t.bhz[iz], pz0[m], a.t.ahz[iz] * G);
                     S = G + p;
                     if (own) a.pszn[so + f] = p;
                 }
@@ -213,22 +291,17 @@ __device__ __forceinline__ void fwd_tile(const Ad2FwdArgs &a, float *su, float *
         const float c0 = cz[j + 2];
         float c1 = __shfl_down(c0, 1, TX);
         if (lx == TX - 1) c1 = ch[fr(g, z0 + r0 + j, ix + 1)];
-        qx[(r0 + j) * QXW + lx + 2] = fwd_xflux<NEAR, SNAP>(a, su, so, x0, z0, r0 + j, lx + 2, c0, c1);
+        qx[(r0 + j) * QXW + lx + 2] = fwd_xflux<NEAR, SNAP>(a, su, so, x0, z0, r0 + j, lx + 2, c0, c1, px0[j]);
     }
-    if (tid < 3 * TZ) {
-        const int r = tid / 3, e = tid - 3 * r, h = e == 2 ? TX + 2 : e;
-        const long long f = fr(g, z0 + r, x0 - 2 + h);
-        qx[r * QXW + h] = fwd_xflux<NEAR, SNAP>(a, su, so, x0, z0, r, h, ch[f], ch[f + 1]);
+    if (tid < 3 * RW) {
+        const long long f = fr(g, z0 + er, x0 - 2 + eh);
+        qx[er * QXW + eh] = fwd_xflux<NEAR, SNAP>(a, su, so, x0, z0, er, eh, ch[f], ch[f + 1], pxe);
     }
     __syncthreads();                      // qx complete; su no longer read
 
-    const int ntiles = g.ntx * g.ntz;
-    const int *soff = a.src_off + (long long)shot * (ntiles + 1);
-    const int sb = soff[tile], se = soff[tile + 1];
-    if (sb < se) {                        // uniform over the block
-        const float *w = a.wav + (long long)shot * a.nsrc * a.nt + a.k;
-        gather_entries(su, a.src_ent, sb, se, [](int e) { return src_cell(e); },
-                       [&](int e) { return a.src_scale * w[(long long)src_node(e) * a.nt]; });
+    if (src.any()) {                      // uniform over the block
+        gather_entries<RW>(su, a.src_ent, src, o.sub, [](int e) { return src_cell(e); }, sample,
+                           [&](float v, float x) { return v + a.src_scale * x; });
     }
     float un[RPA];
 #pragma unroll
@@ -241,46 +314,44 @@ __device__ __forceinline__ void fwd_tile(const Ad2FwdArgs &a, float *su, float *
             const long long f = fr(g, iz, ix);
             float inc = Hx + hz[j];
             if constexpr (NEAR) {
-                const float xx = fmaf(a.t.b0x[ix], __builtin_nontemporal_load(a.xix + so + f), a.t.a0x[ix] * Hx);
-                const float xz = fmaf(a.t.b0z[iz], __builtin_nontemporal_load(a.xiz + so + f), a.t.a0z[iz] * hz[j]);
+                const float xx = fmaf(a.t.b0x[ix], xx0[j], a.t.a0x[ix] * Hx);
+                const float xz = fmaf(a.t.b0z[iz], xz0[j], a.t.a0z[iz] * hz[j]);
                 __builtin_nontemporal_store(xx, a.xix + so + f);
                 __builtin_nontemporal_store(xz, a.xiz + so + f);
                 inc += xx + xz;
             }
             inc += uc[j] - um[j];
-            if (sb < se) inc += su[r * TX + lx];
+            if (src.any()) inc += su[r * TX + lx];
             const float v = uc[j] + inc;
             __builtin_nontemporal_store(v, a.un + so + f);
             un[j] = v;
         }
     }
     if constexpr (REC) {
-        const int *off = a.rec_off + (long long)shot * (ntiles + 1);
-        const int b = off[tile], e = off[tile + 1];
-        if (b < e) {                      // uniform over the block
+        if (rec.any()) {                  // uniform over the block
             __syncthreads();
 #pragma unroll
             for (int j = 0; j < RPA; ++j) su[(r0 + j) * TX + lx] = un[j];
             __syncthreads();
-            for (int i = b + tid; i < e; i += NTA) {
-                const int ent = a.rec_ent[i];
-                a.seis[((long long)shot * a.nt + a.k) * a.nrec + rec_id(ent)] = su[rec_cell(ent)];
+            for (int i = rec.b + tid; i < rec.e; i += NTA) {
+                const int ent = i == rec.b + tid ? rec.ent : a.rec_ent[i];
+                const int own = rec_cell(ent) - o.sub * RW * TX;
+                if (own < 0 || own >= RW * TX) continue;
+                a.seis[((long long)shot * a.nt + a.k) * a.nrec + rec_id(ent)] = su[own];
             }
         }
     }
 }
 
-template <bool SNAP, bool REC>
+template <int RW, bool SNAP, bool REC>
 __global__ __launch_bounds__(NTA) __attribute__((amdgpu_waves_per_eu(8))) void ad2_fwd_kernel(Ad2FwdArgs a)
 {
-    __shared__ float su[AR * AW];
-    __shared__ float qx[TZ * QXW];
-    const int ntl = a.g.ntx * a.g.ntz;
-    const int w = xcd_id(ntl * a.nshots);
-    const int shot = w / ntl, tile = w - shot * ntl;
-    const int tz = tile / a.g.ntx, tx = tile - tz * a.g.ntx;
-    if (near_edge(a.g, tx * TX, tz * TZ)) fwd_tile<true, SNAP, REC>(a, su, qx, tile, shot);
-    else                                  fwd_tile<false, SNAP, REC>(a, su, qx, tile, shot);
+    __shared__ float su[nodes(RW)];
+    __shared__ float qx[RW * QXW];
+    const Rows o = rows_of<RW>(a.g, a.nshots);
+    if (o.z0 >= a.g.NZ) return;
+    if (near_edge<RW>(a.g, o.x0, o.z0)) fwd_tile<RW, true, SNAP, REC>(a, su, qx, o);
+    else                                fwd_tile<RW, false, SNAP, REC>(a, su, qx, o);
 }
 
 // ------------------------------------------------------------------ adjoint
@@ -290,9 +361,10 @@ __global__ __launch_bounds__(NTA) __attribute__((amdgpu_waves_per_eu(8))) void a
 // also takes the other half of its right half node (the chat beyond the
 // grid is its replica).  The x product of the half node left of a thread's
 // node comes from the neighbouring lane (lane 0: from the extra column).
+// z0v: Z_x^{k+2} there; sn: S'x there.
 template <bool NEAR, bool GRAD>
 __device__ __forceinline__ float adj_xflux(const Ad2AdjArgs &a, const float *hx, long long so, int x0, int z0, int r,
-                                           int h, float c0, float c1, bool want_p, float &p)
+                                           int h, float c0, float c1, bool want_p, float &p, float z0v, float sn)
 {
     const Grid2 &g = a.g;
     const int iz = z0 + r, ix = x0 - 2 + h;
@@ -306,24 +378,24 @@ __device__ __forceinline__ float adj_xflux(const Ad2AdjArgs &a, const float *hx,
         const float Sb = 0.5f * (c0 + c1) * qb;
         Gb = Sb;
         if constexpr (NEAR) {
-            const float z = fmaf(a.t.ahx[ix], Sb, a.t.bhx[ix] * a.zx[so + f]);
+            const float z = fmaf(a.t.ahx[ix], Sb, a.t.bhx[ix] * z0v);
             Gb = Sb + z;
             if (own) a.zxn[so + f] = z;
         }
         if constexpr (GRAD) {
-            if (want_p && iz < g.NZ) p = qb * a.snx[so + f];
+            if (want_p && iz < g.NZ) p = qb * sn;
         }
     }
     return Gb;
 }
 
-template <bool NEAR, bool GRAD>
-__device__ __forceinline__ void adj_tile(const Ad2AdjArgs &a, float *hx, float *hz, float *qx, float *pl, int tile,
-                                         int shot)
+template <int RW, bool NEAR, bool GRAD>
+__device__ __forceinline__ void adj_tile(const Ad2AdjArgs &a, float *hx, float *hz, float *qx, float *pl,
+                                         const Rows &o)
 {
+    constexpr int RPA = RW * TX / NTA;
     const Grid2 &g = a.g;
-    const int tz = tile / g.ntx, tx = tile - tz * g.ntx;
-    const int x0 = tx * TX, z0 = tz * TZ;
+    const int x0 = o.x0, z0 = o.z0, shot = o.shot;
     const long long so = (long long)shot * g.plane;
     const float *l1 = a.l1 + so;
     const float *ch = a.chat + (long long)(shot / a.shots_per_model) * g.plane;
@@ -334,7 +406,7 @@ __device__ __forceinline__ void adj_tile(const Ad2AdjArgs &a, float *hx, float *
         // away from the layer the x and z arrays are both lambda^{k+1} itself:
         // straight from global memory into LDS (4 bytes per lane and load,
         // item order = the row-major order of hx; every cell inside the frame)
-        constexpr int NV = AR * AW, K = (NV + NTA - 1) / NTA;
+        constexpr int NV = nodes(RW), K = (NV + NTA - 1) / NTA;
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             const int i = tid + k * NTA;
@@ -346,7 +418,7 @@ __device__ __forceinline__ void adj_tile(const Ad2AdjArgs &a, float *hx, float *
             }
         }
     }
-    for (int i = tid; NEAR && i < AR * AW; i += NTA) {
+    for (int i = tid; NEAR && i < nodes(RW); i += NTA) {
         const int r = i / AW, c = i - r * AW;
         const int iz = z0 - AH + r, jx = x0 - AH + c;
         const long long f = fr(g, iz, jx);
@@ -356,7 +428,7 @@ __device__ __forceinline__ void adj_tile(const Ad2AdjArgs &a, float *hx, float *
             if (iz >= 0 && iz < g.NZ && jx >= 0 && jx < g.NX) {
                 const float yx = fmaf(a.t.a0x[jx], l, a.t.b0x[jx] * a.yx[so + f]);
                 const float yz = fmaf(a.t.a0z[iz], l, a.t.b0z[iz] * a.yz[so + f]);
-                if (r >= AH && r < AH + TZ && c >= AH && c < AH + TX) {
+                if (r >= AH && r < AH + RW && c >= AH && c < AH + TX) {
                     a.yxn[so + f] = yx;
                     a.yzn[so + f] = yz;
                 }
@@ -381,6 +453,32 @@ __device__ __forceinline__ void adj_tile(const Ad2AdjArgs &a, float *hx, float *
             gacc[j] = iz < g.NZ && ix < g.NX ? __builtin_nontemporal_load(a.gn + so + fr(g, iz, ix)) : 0.f;
         }
     }
+    Entries rec{};
+    rec.range(a.rec_off, a.rec_ent, o, g.ntx * g.ntz);
+    const float *d = a.dJdd + ((long long)shot * a.nt + (a.k - 1)) * a.nrec;   // read for k >= 1 only
+    auto sample = [&](int en) { return d[rec_id(en)]; };
+    // Z and the snapshots of the own column's half rows, of the own x
+    // half nodes and of this thread's extra column
+    float zz0[RPA + 3], sz0[RPA + 3], zx0[RPA], sx0[RPA], zxe = 0.f, sxe = 0.f;
+    const int er = tid / 3, ee = tid - 3 * er, eh = ee == 2 ? TX + 2 : ee;   // extra column: row, half node
+#pragma unroll
+    for (int m = 0; m < RPA + 3; ++m) {
+        const long long f = so + fr(g, z0 + r0 - 2 + m, ix);
+        if constexpr (NEAR) zz0[m] = a.zz[f];
+        if constexpr (GRAD) sz0[m] = a.snz[f];
+    }
+#pragma unroll
+    for (int j = 0; j < RPA; ++j) {
+        const long long f = so + fr(g, z0 + r0 + j, ix);
+        zx0[j] = NEAR ? a.zx[f] : 0.f;
+        sx0[j] = GRAD ? a.snx[f] : 0.f;
+    }
+    if (tid < 3 * RW) {
+        const long long f = so + fr(g, z0 + er, x0 - 2 + eh);
+        if constexpr (NEAR) zxe = a.zx[f];
+        if constexpr (GRAD) sxe = a.snx[f];
+    }
+    if (a.k >= 1) rec.first(sample);
     if constexpr (!NEAR) __builtin_amdgcn_s_waitcnt(0);   // the tile's direct loads have landed in LDS
     __syncthreads();
     const float *hzz = NEAR ? hz : hx;
@@ -403,12 +501,12 @@ __device__ __forceinline__ void adj_tile(const Ad2AdjArgs &a, float *hx, float *
                 const float Sb = 0.5f * (cz[m] + cz[m + 1]) * qb;
                 Gb = Sb;
                 if constexpr (NEAR) {
-                    const float z = fmaf(a.t.ahz[iz], Sb, a.t.bhz[iz] * a.zz[so + f]);
+                    const float z = fmaf(a.t.ahz[iz], Sb, a.t.bhz[iz] * zz0[m]);
                     Gb = Sb + z;
                     if (own) a.zzn[so + f] = z;
                 }
                 if constexpr (GRAD) {
-                    if (m >= 1 && m < RPA + 2) pz[m] = qb * a.snz[so + f];
+                    if (m >= 1 && m < RPA + 2) pz[m] = qb * sz0[m];
                 }
             }
             gz[m] = Gb;
@@ -429,26 +527,23 @@ __device__ __forceinline__ void adj_tile(const Ad2AdjArgs &a, float *hx, float *
         float c1 = __shfl_down(c0, 1, TX);
         if (lx == TX - 1) c1 = ch[fr(g, z0 + r0 + j, ix + 1)];
         float pj;
-        qx[(r0 + j) * QXW + lx + 2] = adj_xflux<NEAR, GRAD>(a, hx, so, x0, z0, r0 + j, lx + 2, c0, c1, true, pj);
+        qx[(r0 + j) * QXW + lx + 2] = adj_xflux<NEAR, GRAD>(a, hx, so, x0, z0, r0 + j, lx + 2, c0, c1, true, pj,
+                                                                   zx0[j], sx0[j]);
         px[j] = pj;
     }
-    if (tid < 3 * TZ) {
-        const int r = tid / 3, e = tid - 3 * r, h = e == 2 ? TX + 2 : e;
-        const long long f = fr(g, z0 + r, x0 - 2 + h);
+    if (tid < 3 * RW) {
+        const long long f = fr(g, z0 + er, x0 - 2 + eh);
         float p = 0.f;
-        qx[r * QXW + h] = adj_xflux<NEAR, GRAD>(a, hx, so, x0, z0, r, h, ch[f], ch[f + 1], h == 1, p);
-        if (GRAD && h == 1) pl[r] = p;    // the half node left of the tile's first column
+        qx[er * QXW + eh] = adj_xflux<NEAR, GRAD>(a, hx, so, x0, z0, er, eh, ch[f], ch[f + 1], eh == 1, p, zxe,
+                                                         sxe);
+        if (GRAD && eh == 1) pl[er] = p;  // the half node left of the tile's first column
     }
     __syncthreads();                      // qx, pl complete; hx, hz no longer read
 
-    const int ntiles = g.ntx * g.ntz;
-    const int *off = a.rec_off + (long long)shot * (ntiles + 1);
-    const int b = off[tile], e = off[tile + 1];
-    const bool inj = a.k >= 1 && b < e;   // uniform over the block
+    const bool inj = a.k >= 1 && rec.any();   // uniform over the block
     if (inj) {
-        const float *d = a.dJdd + ((long long)shot * a.nt + (a.k - 1)) * a.nrec;
-        gather_entries(hx, a.rec_ent, b, e, [](int en) { return rec_cell(en); },
-                       [&](int en) { return d[rec_id(en)]; });
+        gather_entries<RW>(hx, a.rec_ent, rec, o.sub, [](int en) { return rec_cell(en); }, sample,
+                           [](float v, float x) { return v + x; });
     }
 #pragma unroll
     for (int j = 0; j < RPA; ++j) {
@@ -473,19 +568,17 @@ __device__ __forceinline__ void adj_tile(const Ad2AdjArgs &a, float *hx, float *
     }
 }
 
-template <bool GRAD>
+template <int RW, bool GRAD>
 __global__ __launch_bounds__(NTA) __attribute__((amdgpu_waves_per_eu(8))) void ad2_adj_kernel(Ad2AdjArgs a)
 {
-    __shared__ float hx[AR * AW];
-    __shared__ float hz[AR * AW];
-    __shared__ float qx[TZ * QXW];
-    __shared__ float pl[TZ];
-    const int ntl = a.g.ntx * a.g.ntz;
-    const int w = xcd_id(ntl * a.nshots);
-    const int shot = w / ntl, tile = w - shot * ntl;
-    const int tz = tile / a.g.ntx, tx = tile - tz * a.g.ntx;
-    if (near_edge(a.g, tx * TX, tz * TZ)) adj_tile<true, GRAD>(a, hx, hz, qx, pl, tile, shot);
-    else                                  adj_tile<false, GRAD>(a, hx, hz, qx, pl, tile, shot);
+    __shared__ float hx[nodes(RW)];
+    __shared__ float hz[nodes(RW)];
+    __shared__ float qx[RW * QXW];
+    __shared__ float pl[RW];
+    const Rows o = rows_of<RW>(a.g, a.nshots);
+    if (o.z0 >= a.g.NZ) return;
+    if (near_edge<RW>(a.g, o.x0, o.z0)) adj_tile<RW, true, GRAD>(a, hx, hz, qx, pl, o);
+    else                                adj_tile<RW, false, GRAD>(a, hx, hz, qx, pl, o);
 }
 
 // ------------------------------------------------------------------ model and gradient
@@ -547,24 +640,41 @@ int blocks_for(long long n) { return (int)std::min<long long>((n + 255) / 256, 6
 
 } // namespace
 
+// f(integral_constant<int, RW>) with the rows per workgroup.
+template <class F>
+static void with_rows(int tiles, F &&f)
+{
+    if (tiles <= 0) return;
+    if (tiles >= FILL_AD2) f(std::integral_constant<int, 16>{});
+    else f(std::integral_constant<int, 8>{});
+}
+
 void launch_ad2_fwd(const Ad2FwdArgs &a, hipStream_t s)
 {
-    const int n = a.g.ntx * a.g.ntz * a.nshots;
     const bool rec = a.seis && a.nrec > 0;
-    if (a.snx) {
-        if (rec) ad2_fwd_kernel<true, true><<<n, NTA, 0, s>>>(a);
-        else     ad2_fwd_kernel<true, false><<<n, NTA, 0, s>>>(a);
-    } else {
-        if (rec) ad2_fwd_kernel<false, true><<<n, NTA, 0, s>>>(a);
-        else     ad2_fwd_kernel<false, false><<<n, NTA, 0, s>>>(a);
-    }
+    const int tiles = a.g.ntx * a.g.ntz * a.nshots;
+    with_rows(tiles, [&](auto R) {
+        constexpr int RW = decltype(R)::value;
+        const int n = tiles * (TZ / RW);
+        if (a.snx) {
+            if (rec) ad2_fwd_kernel<RW, true, true><<<n, NTA, 0, s>>>(a);
+            else     ad2_fwd_kernel<RW, true, false><<<n, NTA, 0, s>>>(a);
+        } else {
+            if (rec) ad2_fwd_kernel<RW, false, true><<<n, NTA, 0, s>>>(a);
+            else     ad2_fwd_kernel<RW, false, false><<<n, NTA, 0, s>>>(a);
+        }
+    });
 }
 
 void launch_ad2_adj(const Ad2AdjArgs &a, hipStream_t s)
 {
-    const int n = a.g.ntx * a.g.ntz * a.nshots;
-    if (a.snx) ad2_adj_kernel<true><<<n, NTA, 0, s>>>(a);
-    else       ad2_adj_kernel<false><<<n, NTA, 0, s>>>(a);
+    const int tiles = a.g.ntx * a.g.ntz * a.nshots;
+    with_rows(tiles, [&](auto R) {
+        constexpr int RW = decltype(R)::value;
+        const int n = tiles * (TZ / RW);
+        if (a.snx) ad2_adj_kernel<RW, true><<<n, NTA, 0, s>>>(a);
+        else       ad2_adj_kernel<RW, false><<<n, NTA, 0, s>>>(a);
+    });
 }
 
 void launch_ad2_prep(const Grid2 &g, int nmodels, const float *vp, double dt, double dx, float *chat, float *cpad,
