@@ -47,18 +47,14 @@ static_assert(OFF_C6 + 9 * CH + 1 == CNN_NPARAMS, "parameter layout");
 
 __device__ __forceinline__ float bf2f(u16 h) { return __uint_as_float((unsigned)h << 16); }
 
-__device__ __forceinline__ u16 f2bf(float f)
-{
-    unsigned u = __float_as_uint(f);
-    if ((u & 0x7f800000u) == 0x7f800000u)                 // inf stays inf, NaN stays NaN
-        return (u16)((u >> 16) | ((u & 0xffffu) ? 0x40u : 0u));
-    u += 0x7fffu + ((u >> 16) & 1u);                      // round to nearest, ties to even
-    return (u16)(u >> 16);
-}
+// BF16 of an FP32 value, to nearest with ties to even (the hardware's
+// conversion; inf stays inf, NaN stays NaN).
+__device__ __forceinline__ u16 f2bf(float f) { return __builtin_bit_cast(u16, (__bf16)f); }
 
 __device__ __forceinline__ unsigned pack2(float a, float b)
 {
-    return (unsigned)f2bf(a) | ((unsigned)f2bf(b) << 16);
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(unsigned, bf16x2{(__bf16)a, (__bf16)b});
 }
 
 __device__ __forceinline__ f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c)
@@ -114,6 +110,16 @@ struct ConvArgs {
 // accesses instead of single 2- and 4-byte elements.
 constexpr int OS = CH + 4;                 // FP32 stride of an output pixel in LDS
 constexpr int CONV_LDS = LH * LW * 64 > 4 * TW * OS * 4 ? LH * LW * 64 : 4 * TW * OS * 4;
+
+// FRAG: the weights are stored in fragment order, element ((tap * 2 + nb) *
+// 64 + lane) * 8 + e, so that a fragment load is one contiguous KiB (the
+// network's own copies); else as [co][tap][ci] (the single-layer entry
+// point), where the 64 lanes' 16 bytes lie in 16 rows.  Those loads bounded
+// the kernel: about 85 cache accesses for each of a wavefront's 18.  With
+// them contiguous, the residual and gate loaded before the LDS pass and the
+// hardware's BF16 conversion, a launch on 8 x 256^2 pixels went from 33.2 to
+// 22.3 us (3.0 TB/s of activations read and written).
+template <bool FRAG>
 __global__ __launch_bounds__(NT) void conv3x3_mfma_kernel(ConvArgs a)
 {
     __shared__ __attribute__((aligned(16))) unsigned char lds_raw[CONV_LDS];
@@ -127,7 +133,8 @@ __global__ __launch_bounds__(NT) void conv3x3_mfma_kernel(ConvArgs a)
     for (int t = 0; t < 9; ++t)
 #pragma unroll
         for (int nb = 0; nb < 2; ++nb)
-            bw[t][nb] = __builtin_bit_cast(bf16x8, *(const u32x4 *)(a.w + ((16 * nb + r) * 9 + t) * CH + 8 * g));
+            bw[t][nb] = __builtin_bit_cast(bf16x8, *(const u32x4 *)(a.w + (FRAG ? ((t * 2 + nb) * 64 + lane) * 8
+                                                                               : ((16 * nb + r) * 9 + t) * CH + 8 * g)));
 
     dma_halo_swizzled(a.x, n, a.H, a.W, y0, x0, lds_raw);
     __builtin_amdgcn_s_waitcnt(0);         // this thread's direct loads have landed in LDS
@@ -149,6 +156,22 @@ __global__ __launch_bounds__(NT) void conv3x3_mfma_kernel(ConvArgs a)
         }
     }
 
+    // the residual and the gate of this lane's output items, in flight while
+    // the accumulators pass through LDS
+    const int y = y0 + wv;
+    const long long rowbase = ((long long)n * a.H + y) * a.W;
+    constexpr int NIT = TW * 4 / 64;       // items (8 channels of a pixel) per lane
+    u16x8 rv[NIT], gv[NIT];
+#pragma unroll
+    for (int it = 0; it < NIT; ++it) {
+        const int item = lane + 64 * it, px = item >> 2, q = item & 3;
+        rv[it] = gv[it] = u16x8{0, 0, 0, 0, 0, 0, 0, 0};
+        if (y >= a.H || x0 + px >= a.W) continue;
+        const long long idx = (rowbase + x0 + px) * CH + 8 * q;
+        if (a.res) rv[it] = *reinterpret_cast<const u16x8 *>(a.res + idx);
+        if (a.gate) gv[it] = *reinterpret_cast<const u16x8 *>(a.gate + idx);
+    }
+
     __syncthreads();                       // every wavefront is done with the input tile
     float *orow = reinterpret_cast<float *>(lds_raw) + wv * TW * OS;
 #pragma unroll
@@ -159,36 +182,43 @@ __global__ __launch_bounds__(NT) void conv3x3_mfma_kernel(ConvArgs a)
             for (int j = 0; j < 4; ++j) orow[(16 * mb + 4 * g + j) * OS + 16 * nb + r] = acc[mb][nb][j];
     __syncthreads();
 
-    const int y = y0 + wv;
     if (y >= a.H) return;
-    const long long rowbase = ((long long)n * a.H + y) * a.W;
+    const int q = lane & 3;                // every item of a lane: channels 8q .. 8q+7
+    f32x4 blo = {0.f, 0.f, 0.f, 0.f}, bhi = blo;
+    if (a.bias) {
 #pragma unroll
-    for (int it = 0; it < TW * 4 / 64; ++it) {
-        const int item = lane + 64 * it, px = item >> 2, q = item & 3;   // 8 channels 8q .. 8q+7 of pixel px
+        for (int k = 0; k < 4; ++k) {
+            blo[k] = a.bias[8 * q + k];
+            bhi[k] = a.bias[8 * q + 4 + k];
+        }
+    }
+#pragma unroll
+    for (int it = 0; it < NIT; ++it) {
+        const int px = (lane + 64 * it) >> 2;
         if (x0 + px >= a.W) continue;
         const long long idx = (rowbase + x0 + px) * CH + 8 * q;
         const f32x4 lo = *reinterpret_cast<const f32x4 *>(orow + px * OS + 8 * q);
         const f32x4 hi = *reinterpret_cast<const f32x4 *>(orow + px * OS + 8 * q + 4);
-        const float acc8[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-        u16x8 rv = {0, 0, 0, 0, 0, 0, 0, 0}, gv = {0, 0, 0, 0, 0, 0, 0, 0};
-        if (a.res) rv = *reinterpret_cast<const u16x8 *>(a.res + idx);
-        if (a.gate) gv = *reinterpret_cast<const u16x8 *>(a.gate + idx);
-        float v8[8];
-        u16x8 o;
+        float v[8];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const float b = a.bias ? a.bias[8 * q + k] : 0.f;
-            float v = acc8[k] + b;
-            if (a.res) v += bf2f(rv[k]);
-            if (a.relu) v = fmaxf(v, 0.f);
-            if (a.gate && !(bf2f(gv[k]) > 0.f)) v = 0.f;
-            v8[k] = v;
-            o[k] = f2bf(v);
+        for (int k = 0; k < 4; ++k) {
+            v[k] = lo[k] + blo[k];
+            v[4 + k] = hi[k] + bhi[k];
         }
-        *reinterpret_cast<u16x8 *>(a.y + idx) = o;
+        if (a.res)
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] += bf2f(rv[it][k]);
+        if (a.relu)
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = fmaxf(v[k], 0.f);
+        if (a.gate)
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = bf2f(gv[it][k]) > 0.f ? v[k] : 0.f;
+        *reinterpret_cast<u32x4 *>(a.y + idx) = u32x4{pack2(v[0], v[1]), pack2(v[2], v[3]), pack2(v[4], v[5]),
+                                                      pack2(v[6], v[7])};
         if (a.y32) {
-            *reinterpret_cast<f32x4 *>(a.y32 + idx) = f32x4{v8[0], v8[1], v8[2], v8[3]};
-            *reinterpret_cast<f32x4 *>(a.y32 + idx + 4) = f32x4{v8[4], v8[5], v8[6], v8[7]};
+            *reinterpret_cast<f32x4 *>(a.y32 + idx) = f32x4{v[0], v[1], v[2], v[3]};
+            *reinterpret_cast<f32x4 *>(a.y32 + idx + 4) = f32x4{v[4], v[5], v[6], v[7]};
         }
     }
 }
@@ -349,8 +379,14 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(const float *__res
     }
 }
 
-// BF16 copies of c2..c5: wf[L] as stored ([co][tap][ci]) and wt[L] flipped
-// and transposed ([ci][8 - tap][co]), the weights of the input gradient.
+// Element of the weight (out, tap, in) in fragment order (see conv3x3_mfma_kernel).
+__device__ __forceinline__ int frag_at(int out, int tap, int in)
+{
+    return ((tap * 2 + (out >> 4)) * 64 + (in >> 3) * 16 + (out & 15)) * 8 + (in & 7);
+}
+
+// BF16 copies of c2..c5 in fragment order: wf[L] as they are and wt[L]
+// flipped and transposed, the weights of the input gradient.
 __global__ void prep_weights_kernel(const float *__restrict__ params, u16 *__restrict__ wf, u16 *__restrict__ wt)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -358,8 +394,8 @@ __global__ void prep_weights_kernel(const float *__restrict__ params, u16 *__res
     const int L = i / WMID, k = i - L * WMID;
     const int co = k / (9 * CH), t = (k / CH) % 9, ci = k % CH;
     const u16 b = f2bf(params[OFF_C2 + L * PMID + k]);
-    wf[i] = b;
-    wt[L * WMID + (ci * 9 + (8 - t)) * CH + co] = b;
+    wf[L * WMID + frag_at(co, t, ci)] = b;
+    wt[L * WMID + frag_at(ci, 8 - t, co)] = b;
 }
 
 // ------------------------------------------------------------- thin layers
@@ -598,11 +634,22 @@ __global__ __launch_bounds__(256) void loss_partial_kernel(const float *__restri
                                                            double *__restrict__ part)
 {
     const long long i0 = blockIdx.x * per_wg, i1 = i0 + per_wg < n ? i0 + per_wg : n;
+    constexpr int U = 8;                   // loads of U elements in flight, added in order
     double s = 0.0, c = 0.0;
-    for (long long i = i0 + threadIdx.x; i < i1; i += 256) {
-        const double r = (double)p[i] - (double)t[i];
-        s += (double)m[i] * r * r;
-        c += (double)m[i];
+    for (long long ib = i0 + threadIdx.x; ib < i1; ib += 256 * U) {
+        float pv[U], tv[U], mv[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const long long i = min(ib + 256 * u, i1 - 1);
+            pv[u] = p[i]; tv[u] = t[i]; mv[u] = m[i];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (ib + 256 * u >= i1) break;
+            const double r = (double)pv[u] - (double)tv[u];
+            s += (double)mv[u] * r * r;
+            c += (double)mv[u];
+        }
     }
     block_sum2(s, c);
     if (threadIdx.x == 0) {
@@ -659,9 +706,19 @@ __global__ __launch_bounds__(256) void field_inv_rms_kernel(const float *__restr
     const bool valid = f >= 0 && f < nsrc;
     const long long n = (long long)fh * fw, base = (long long)f * n;
     double acc = 0.0, dummy = 0.0;
-    for (long long i = threadIdx.x; valid && i < n; i += 256) {
-        const float v = b ? a[base + i] - b[base + i] : a[base + i];
-        acc += (double)v * (double)v;
+    constexpr int U = 16;                  // loads of U elements in flight, added in order
+    for (long long ib = threadIdx.x; valid && ib < n; ib += 256 * U) {
+        float v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const long long i = base + min(ib + 256 * u, n - 1);
+            v[u] = b ? a[i] - b[i] : a[i];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (ib + 256 * u >= n) break;
+            acc += (double)v[u] * (double)v[u];
+        }
     }
     block_sum2(acc, dummy);
     if (threadIdx.x == 0) inv[s] = acc > 0 ? 1.0 / sqrt(acc / (double)n) : 0.0;
@@ -744,13 +801,14 @@ int check_dims(int n, int h, int w)
     return SG_OK;
 }
 
+template <bool FRAG>
 int launch_conv(const u16 *x, int n, int h, int w, const u16 *wgt, const float *bias, const u16 *res,
                 const u16 *gate, int relu, u16 *y, float *y32, hipStream_t s)
 {
     ConvArgs a{x, wgt, bias, res, gate, y, y32, n, h, w, relu};
     dim3 grid((w + TW - 1) / TW, (h + TH - 1) / TH, n);
     if (grid.y > 65535u || grid.z > 65535u) return fail(SG_EINVAL, "image batch too large for one launch");
-    conv3x3_mfma_kernel<<<grid, NT, 0, s>>>(a);
+    conv3x3_mfma_kernel<FRAG><<<grid, NT, 0, s>>>(a);
     HIPCHECK(hipGetLastError());
     return SG_OK;
 }
@@ -823,10 +881,10 @@ int cnn_forward(const float *params, const float *g, int32_t n, int32_t h, int32
     conv_in_kernel<<<blocks(pix, NT), NT, 0, s>>>(g, params, x1, n, h, w);
     HIPCHECK(hipGetLastError());
     const float *bias = params + OFF_C2 + WMID;
-    if (int e = launch_conv(x1, n, h, w, wf + 0 * WMID, bias + 0 * PMID, nullptr, nullptr, 1, a2, nullptr, s)) return e;
-    if (int e = launch_conv(a2, n, h, w, wf + 1 * WMID, bias + 1 * PMID, x1, nullptr, 1, x2, nullptr, s)) return e;
-    if (int e = launch_conv(x2, n, h, w, wf + 2 * WMID, bias + 2 * PMID, nullptr, nullptr, 1, a4, nullptr, s)) return e;
-    if (int e = launch_conv(a4, n, h, w, wf + 3 * WMID, bias + 3 * PMID, x2, nullptr, 1, x3, nullptr, s)) return e;
+    if (int e = launch_conv<true>(x1, n, h, w, wf + 0 * WMID, bias + 0 * PMID, nullptr, nullptr, 1, a2, nullptr, s)) return e;
+    if (int e = launch_conv<true>(a2, n, h, w, wf + 1 * WMID, bias + 1 * PMID, x1, nullptr, 1, x2, nullptr, s)) return e;
+    if (int e = launch_conv<true>(x2, n, h, w, wf + 2 * WMID, bias + 2 * PMID, nullptr, nullptr, 1, a4, nullptr, s)) return e;
+    if (int e = launch_conv<true>(a4, n, h, w, wf + 3 * WMID, bias + 3 * PMID, x2, nullptr, 1, x3, nullptr, s)) return e;
     conv_out_kernel<<<dim3((w + TW - 1) / TW, (h + TH - 1) / TH, n), NT, 0, s>>>(x3, g, params, p, n, h, w);
     HIPCHECK(hipGetLastError());
     return SG_OK;
@@ -854,13 +912,13 @@ int cnn_backward(const float *params, const float *g, const float *dp, int32_t n
     HIPCHECK(hipGetLastError());
     float *gm = grad + OFF_C2;
     if (int e = launch_wgrad(G0, a4, n, h, w, part, gm + 3 * PMID, s)) return e;
-    if (int e = launch_conv(G0, n, h, w, wt + 3 * WMID, nullptr, nullptr, a4, 0, G1, nullptr, s)) return e; // d pre(a4)
+    if (int e = launch_conv<true>(G0, n, h, w, wt + 3 * WMID, nullptr, nullptr, a4, 0, G1, nullptr, s)) return e; // d pre(a4)
     if (int e = launch_wgrad(G1, x2, n, h, w, part, gm + 2 * PMID, s)) return e;
-    if (int e = launch_conv(G1, n, h, w, wt + 2 * WMID, nullptr, G0, x2, 0, G2, nullptr, s)) return e;     // d pre(x2)
+    if (int e = launch_conv<true>(G1, n, h, w, wt + 2 * WMID, nullptr, G0, x2, 0, G2, nullptr, s)) return e;     // d pre(x2)
     if (int e = launch_wgrad(G2, a2, n, h, w, part, gm + 1 * PMID, s)) return e;
-    if (int e = launch_conv(G2, n, h, w, wt + 1 * WMID, nullptr, nullptr, a2, 0, G0, nullptr, s)) return e; // d pre(a2)
+    if (int e = launch_conv<true>(G2, n, h, w, wt + 1 * WMID, nullptr, nullptr, a2, 0, G0, nullptr, s)) return e; // d pre(a2)
     if (int e = launch_wgrad(G0, x1, n, h, w, part, gm + 0 * PMID, s)) return e;
-    if (int e = launch_conv(G0, n, h, w, wt + 0 * WMID, nullptr, G2, x1, 0, G1, nullptr, s)) return e;     // d pre(x1)
+    if (int e = launch_conv<true>(G0, n, h, w, wt + 0 * WMID, nullptr, G2, x1, 0, G1, nullptr, s)) return e;     // d pre(x1)
     if (int e = launch_wgrad_thin<false>(g, G1, n, h, w, part, grad + OFF_C1, s)) return e;
     return SG_OK;
 }
@@ -944,7 +1002,7 @@ int cnn_conv3x3(const uint16_t *x, int32_t n, int32_t h, int32_t w, const uint16
     if (!x || !wgt || !y) return fail(SG_EINVAL, "NULL pointer argument");
     if (!aligned16(x) || !aligned16(wgt) || !aligned16(res) || !aligned16(gate) || !aligned16(y) || !aligned16(y32))
         return fail(SG_EINVAL, "x, wgt, res, gate, y and y32 must be 16-byte aligned");
-    return launch_conv(x, n, h, w, wgt, bias, res, gate, relu, y, y32, (hipStream_t)stream);
+    return launch_conv<false>(x, n, h, w, wgt, bias, res, gate, relu, y, y32, (hipStream_t)stream);
 }
 
 int cnn_conv3x3_wgrad(const uint16_t *dy, const uint16_t *x, int32_t n, int32_t h, int32_t w, float *dw, void *ws,
