@@ -21,6 +21,7 @@
 
 #include <cmath>
 #include <cstdint>
+#include <type_traits>
 
 using sg::fail;
 
@@ -251,22 +252,81 @@ __device__ __forceinline__ void dma_tile(const u16 *__restrict__ x, int n, int H
 
 // Weight gradient, K = pixels.  Each wavefront owns one tile row (two
 // K-blocks of 32 pixels); K index 8g + e of a lane maps to pixel 4e + g of
-// the block, the same for both operands, so that the eight 2-byte LDS reads
-// of a fragment hit distinct banks across the lane groups.
+// the block, the same for both operands.  The fragments, eight pixels of one
+// channel per lane from tiles stored by pixel, come from two transposing LDS
+// reads each: of 16 lanes, lane 4e + c addresses channels 4c .. 4c+3 of row e
+// (here pixel 4e + g), and lane j receives channel j of rows 0 .. 3.  Pixel p
+// sits in pixel slot rot_slot(p), odd pixels with their channel halves
+// exchanged, so that the rows that 32 lanes read at once (pixels 0, 4, 8, 12
+// and 1, 5, 9, 13) cover all banks once.
+//
+// While a tile is multiplied, the next one is on its way: x alternates
+// between two LDS buffers; dy, whose row only its own wavefront loads and
+// reads, is taken into fragments first and its buffer refilled at once.
+// Registers (152 of accumulators) hold a CU to two workgroups, whose loads,
+// LDS reads and MFMAs ran in sequence before: 8 x 256^2 pixels 45.4 us (with
+// eight 2-byte reads per fragment), 43.7 (transposing reads alone), 24.2 now.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ int rot_slot(int p) { return (p & ~3) | ((p + (p >> 2)) & 3); }
+__device__ __forceinline__ int rot_pixel(int slot) { return (slot & ~3) | ((slot - (slot >> 2)) & 3); }
+constexpr int PXW = CH;                    // u16 stride of a pixel slot
+
+// A fragment at byte `at` of the LDS array (pixels 16 further on: 16 slots on).
+typedef __attribute__((address_space(3))) char lds_char;
+__device__ __forceinline__ bf16x8 tr_frag(lds_char *at)
+{
+    typedef __attribute__((address_space(3))) s16x4 lds4;
+    const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4 *)at);
+    const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4 *)(at + 16 * PXW * 2));
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+// Byte of pixel pix, channel ch of its lower half; the upper half: ^ HALF.
+constexpr unsigned HALF = 32;
+__device__ __forceinline__ unsigned tr_at(int pix, int ch)
+{
+    return (unsigned)(rot_slot(pix) * PXW * 2 + ((2 * ch) ^ ((pix & 1) << 5)));
+}
+
 struct WgradArgs {
     const u16 *dy, *x;
     float *part;  // [gridDim.x][PMID]
     int N, H, W, tx, ty, ntiles;
 };
 
+// Pixel slots [0, NV / 4) of a rows x COLS tile at (y0, x0), NV / 4 pixels,
+// by lanes first, first + step, ..: 16-byte direct loads, zeros outside the image.
+template <int COLS, int NV, int STEP>
+__device__ __forceinline__ void dma_rot(const u16 *__restrict__ x, int n, int H, int W, int y0, int x0, int first,
+                                        unsigned char *lds)
+{
+#pragma unroll
+    for (int k = 0; k < (NV + STEP - 1) / STEP; ++k) {
+        const int i = first + k * STEP;
+        if (i >= NV) continue;
+        const int pix = rot_pixel(i >> 2), q = (i & 3) ^ ((pix & 1) << 1);
+        const int rr = pix / COLS, c = pix - rr * COLS;
+        const int y = y0 + rr, xx = x0 + c;
+        if (y >= 0 && y < H && xx >= 0 && xx < W)
+            __builtin_amdgcn_global_load_lds((const void *)(x + (((long long)n * H + y) * W + xx) * CH + q * 8),
+                                             (void __attribute__((address_space(3))) *)(lds + __builtin_amdgcn_readfirstlane(i & ~63) * 16),
+                                             16, 0, 0);
+        else
+            *(u32x4 *)(lds + i * 16) = u32x4{0u, 0u, 0u, 0u};
+    }
+}
+
+constexpr int XTILE = LH * LW * PXW, YTILE = TH * TW * PXW;   // u16 of the two tiles
+constexpr int RS = CH + 4;                 // FP32 row stride of a tap in the reduction (distinct banks per lane group)
+static_assert(LH * LW % 4 == 0 && TW % 4 == 0, "whole groups of four pixels");
+static_assert((2 * XTILE + YTILE) * 2 >= 4 * 3 * CH * RS * 4 + 4 * CH * 4, "the reduction reuses the staging space");
+
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void wgrad3x3_mfma_kernel(WgradArgs a)
 {
-    constexpr int PW = 32;                 // u16 stride of a staged pixel (the slots of dma_tile)
-    __shared__ __attribute__((aligned(16))) u16 smem[LH * LW * PW + TH * TW * PW];
-    static_assert((LH * LW * PW + TH * TW * PW) * 2 >= PMID * 4, "the reduction reuses the staging space");
-    u16 *lx = smem, *lg = smem + LH * LW * PW;
+    __shared__ __attribute__((aligned(16))) u16 smem[2 * XTILE + YTILE];
+    u16 *lg = smem + 2 * XTILE;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int r = lane & 15, g = lane >> 4;
+    const int tp = 4 * (r >> 2) + g, tc = 4 * (r & 3);   // pixel and channel a lane addresses
     const bf16x8 ones = __builtin_bit_cast(bf16x8, u16x8{0x3f80, 0x3f80, 0x3f80, 0x3f80,
                                                          0x3f80, 0x3f80, 0x3f80, 0x3f80});
     f32x4 acc[9][2][2];
@@ -276,74 +336,100 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
         acc[t][0][0] = acc[t][0][1] = acc[t][1][0] = acc[t][1][1] = f32x4{0.f, 0.f, 0.f, 0.f};
     accb[0] = accb[1] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    for (int tile = blockIdx.x; tile < a.ntiles; tile += gridDim.x) {
+    auto load = [&](int tile, u16 *lx) {
         const int per = a.tx * a.ty;
         const int n = tile / per, rem = tile - n * per;
         const int y0 = (rem / a.tx) * TH, x0 = (rem - (rem / a.tx) * a.tx) * TW;
-        __syncthreads();
-        dma_tile<LH, LW, 1>(a.x, n, a.H, a.W, y0, x0, reinterpret_cast<unsigned char *>(lx));
-        dma_tile<TH, TW, 0>(a.dy, n, a.H, a.W, y0, x0, reinterpret_cast<unsigned char *>(lg));
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
+        // an opaque copy of the thread id: the pixels of its items are worked
+        // out again for each tile rather than kept in (spilled) registers
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        const int lane = tid & 63;
+        dma_rot<LW, LH * LW * 4, NT>(a.x, n, a.H, a.W, y0 - 1, x0 - 1, tid, (unsigned char *)lx);
+        dma_rot<TW, TW * 4, 64>(a.dy, n, a.H, a.W, y0 + wv, x0, lane, (unsigned char *)(lg + wv * TW * PXW));
+    };
+    // Bytes of this lane's rows.  A tap's pixel is 66 ky + kx on: the slot of
+    // 66 ky is 64 ky slots and 2 ky pixels, and 32 pixels are 32 slots, so
+    // seven addresses and constants serve the 36 fragments of a tile row.
+    static_assert(LW == 66, "the slot of a row below");
+    lds_char *sm = (lds_char *)(void *)smem;
+    unsigned xo[7];
+#pragma unroll
+    for (int d = 0; d < 7; ++d) xo[d] = tr_at(wv * LW + tp + d, tc);
+    const unsigned yo = (2 * XTILE + wv * TW * PXW) * 2 + tr_at(tp, tc);
+
+    auto step = [&](int tile, auto CUR) {
+        constexpr int cur = decltype(CUR)::value;
+        __builtin_amdgcn_s_waitcnt(0);     // this wavefront's loads have landed
+        __syncthreads();                   // all have; the other x buffer is free
+        bf16x8 A[2][2];
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb) {
-            u16x8 ga0, ga1;
+            A[kb][0] = tr_frag(sm + yo + kb * 32 * PXW * 2);
+            A[kb][1] = tr_frag(sm + (yo ^ HALF) + kb * 32 * PXW * 2);
+        }
+        __builtin_amdgcn_s_waitcnt(0xc07f);                // lgkmcnt(0): the fragments are in registers
+        __builtin_amdgcn_sched_barrier(0);
+        if (tile + (int)gridDim.x < a.ntiles) load(tile + gridDim.x, smem + (cur ^ 1) * XTILE);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const u16 *p = lg + (wv * TW + kb * 32 + 4 * e + g) * PW + r;
-                ga0[e] = p[0];
-                ga1[e] = p[16];
-            }
-            const bf16x8 A0 = __builtin_bit_cast(bf16x8, ga0), A1 = __builtin_bit_cast(bf16x8, ga1);
-            accb[0] = mfma(A0, ones, accb[0]);
-            accb[1] = mfma(A1, ones, accb[1]);
+        for (int kb = 0; kb < 2; ++kb) {
+            accb[0] = mfma(A[kb][0], ones, accb[0]);
+            accb[1] = mfma(A[kb][1], ones, accb[1]);
 #pragma unroll
             for (int t = 0; t < 9; ++t) {
                 const int ky = t / 3, kx = t - 3 * (t / 3);
-#pragma unroll
-                for (int ib = 0; ib < 2; ++ib) {
-                    u16x8 xb;
-#pragma unroll
-                    for (int e = 0; e < 8; ++e)
-                        xb[e] = lx[((wv + ky) * LW + kb * 32 + 4 * e + g + kx) * PW + 16 * ib + r];
-                    const bf16x8 B = __builtin_bit_cast(bf16x8, xb);
-                    acc[t][0][ib] = mfma(A0, B, acc[t][0][ib]);
-                    acc[t][1][ib] = mfma(A1, B, acc[t][1][ib]);
-                }
+                const int on = (cur * XTILE + (ky * 64 + kb * 32) * PXW) * 2;
+                const bf16x8 B0 = tr_frag(sm + xo[2 * ky + kx] + on), B1 = tr_frag(sm + (xo[2 * ky + kx] ^ HALF) + on);
+                acc[t][0][0] = mfma(A[kb][0], B0, acc[t][0][0]);
+                acc[t][1][0] = mfma(A[kb][1], B0, acc[t][1][0]);
+                acc[t][0][1] = mfma(A[kb][0], B1, acc[t][0][1]);
+                acc[t][1][1] = mfma(A[kb][1], B1, acc[t][1][1]);
             }
         }
+    };
+    load(blockIdx.x, smem);
+    for (int tile = blockIdx.x; tile < a.ntiles; tile += 2 * gridDim.x) {
+        step(tile, std::integral_constant<int, 0>{});
+        if (tile + (int)gridDim.x < a.ntiles) step(tile + gridDim.x, std::integral_constant<int, 1>{});
     }
 
-    // fixed-order sum over the four wavefronts in LDS, then one partial row
-    float *red = reinterpret_cast<float *>(smem);
-    for (int w = 0; w < 4; ++w) {
+    // fixed-order sum over the four wavefronts, three taps at a time through
+    // LDS ([wavefront][tap][co][ci]), into one partial row
+    float *red = reinterpret_cast<float *>(smem), *redb = red + 4 * 3 * CH * RS;
+    float *out = a.part + (long long)blockIdx.x * PMID;
+#pragma unroll
+    for (int t0 = 0; t0 < 9; t0 += 3) {
         __syncthreads();
-        if (wv == w) {
 #pragma unroll
-            for (int t = 0; t < 9; ++t)
+        for (int t = 0; t < 3; ++t)
 #pragma unroll
-                for (int cb = 0; cb < 2; ++cb)
+            for (int cb = 0; cb < 2; ++cb)
 #pragma unroll
-                    for (int ib = 0; ib < 2; ++ib)
+                for (int ib = 0; ib < 2; ++ib)
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) {
-                            const int co = 16 * cb + 4 * g + j, ci = 16 * ib + r;
-                            const int idx = (co * 9 + t) * CH + ci;
-                            red[idx] = (w == 0 ? 0.f : red[idx]) + acc[t][cb][ib][j];
-                        }
-            if (r == 0)
+                    for (int j = 0; j < 4; ++j)
+                        red[((wv * 3 + t) * CH + 16 * cb + 4 * g + j) * RS + 16 * ib + r] = acc[t0 + t][cb][ib][j];
+        if (t0 == 0 && r == 0)
 #pragma unroll
-                for (int cb = 0; cb < 2; ++cb)
+            for (int cb = 0; cb < 2; ++cb)
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const int idx = WMID + 16 * cb + 4 * g + j;
-                        red[idx] = (w == 0 ? 0.f : red[idx]) + accb[cb][j];
-                    }
+                for (int j = 0; j < 4; ++j) redb[wv * CH + 16 * cb + 4 * g + j] = accb[cb][j];
+        __syncthreads();
+        for (int i = threadIdx.x; i < 3 * CH * CH / 4; i += NT) {
+            const int ci = 4 * (i % (CH / 4)), co = i / (CH / 4) % CH, t = i / (CH * CH / 4);
+            f32x4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int w = 0; w < 4; ++w) v += *(const f32x4 *)(red + ((w * 3 + t) * CH + co) * RS + ci);
+            *(f32x4 *)(out + (co * 9 + t0 + t) * CH + ci) = v;
+        }
+        if (t0 == 0 && threadIdx.x < CH) {
+            float v = 0.f;
+#pragma unroll
+            for (int w = 0; w < 4; ++w) v += redb[w * CH + threadIdx.x];
+            out[WMID + threadIdx.x] = v;
         }
     }
-    __syncthreads();
-    float *out = a.part + (long long)blockIdx.x * PMID;
-    for (int i = threadIdx.x; i < PMID; i += NT) out[i] = red[i];
 }
 
 // out[i] = sum over b of part[b][i] in FP64, in a fixed order: lane l of
