@@ -115,28 +115,47 @@ void launch_dot(const float *x, const float *y, long long n, double *out, hipStr
 // Range check of a model's parameters on the device: the largest vp (as the
 // bits of a positive float, whose order is that of the integers) and which
 // checks fail.  Bound by the one read of the fields: 400^3 cells (256 MB) in
-// 0.07 ms, where copying them to the host and looping over them took about
-// 110 ms of every init_model and update_model.
+// 58 us, 128^3 in 16 (with two atomics per wavefront on the one result 158 and
+// 97), where copying them to the host and looping over them took about 110 ms
+// of every init_model and update_model.
 __global__ __launch_bounds__(256) void range_kernel(const float *vp, const float *vs, const float *rho, long long n,
                                                     ParamRange *out)
 {
     float top = 0.f;
     unsigned bad = 0u;
-    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
-         i += (long long)gridDim.x * blockDim.x) {
-        const float v = vp[i];
-        if (!(v > 0.f) || !isfinite(v)) bad |= PARAM_BAD_VP;
-        else top = fmaxf(top, v);
-        if (vs) {
-            const float s = vs[i], r = rho[i];
-            if (!(s > 0.f) || !(s < v) || !(r > 0.f) || !isfinite(r)) bad |= PARAM_BAD_ELASTIC;
+    constexpr int U = 8;                   // cells in flight per thread
+    const long long step = (long long)gridDim.x * 256;
+    for (long long ib = blockIdx.x * 256ll + threadIdx.x; ib < n; ib += U * step) {
+        float v[U], s[U], r[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const long long i = min(ib + u * step, n - 1);
+            v[u] = vp[i];
+            s[u] = vs ? vs[i] : 0.f;
+            r[u] = vs ? rho[i] : 0.f;
         }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {      // (the last cell may be taken more than once)
+            if (!(v[u] > 0.f) || !isfinite(v[u])) bad |= PARAM_BAD_VP;
+            else top = fmaxf(top, v[u]);
+            if (vs && (!(s[u] > 0.f) || !(s[u] < v[u]) || !(r[u] > 0.f) || !isfinite(r[u]))) bad |= PARAM_BAD_ELASTIC;
+        }
+    }
+    __shared__ float st[256];
+    __shared__ unsigned sb[256];
+    st[threadIdx.x] = top;
+    sb[threadIdx.x] = bad;
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
+    for (int w = 64; w < 256; w += 64) {
+        top = fmaxf(top, st[threadIdx.x + w]);
+        bad |= sb[threadIdx.x + w];
     }
     for (int o = 32; o > 0; o >>= 1) {
         top = fmaxf(top, __shfl_down(top, o, 64));
         bad |= __shfl_down(bad, o, 64);
     }
-    if ((threadIdx.x & 63) == 0) {
+    if (threadIdx.x == 0) {
         atomicMax(&out->vmax_bits, __float_as_uint(top));
         if (bad) atomicOr(&out->bad, bad);
     }
@@ -147,7 +166,7 @@ void launch_param_range(const float *vp, const float *vs, const float *rho, long
 {
     static_assert(sizeof(ParamRange) == 2 * sizeof(float), "cleared as floats");
     launch_fill(reinterpret_cast<float *>(out), 2, 0.f, s);
-    const int blocks = (int)std::min<long long>((n + 255) / 256, 2048);
+    const int blocks = (int)std::min<long long>((n + 2047) / 2048, 1024);
     range_kernel<<<blocks, 256, 0, s>>>(vp, vs, rho, n, out);
 }
 
