@@ -973,27 +973,29 @@ void ac3_adj_kernel(Ac3AdjArgs a)
     if (esw) stb(ee, esf, esn);
 }
 
-__global__ void ac3_prep_kernel(Grid3 g, int nmodels, const float *vp, double dt, double dx,
-                                float *chat, float *cpad)
+// A wavefront per frame row (a thread per cell divides three times by
+// run-time strides for its place: 400^3 395 us, by rows 237).
+__global__ __launch_bounds__(256) void ac3_prep_kernel(Grid3 g, int nmodels, const float *vp, double dt, double dx,
+                                                       float *chat, float *cpad)
 {
-    const long long n = (long long)nmodels * g.plane;
-    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
-         i += (long long)gridDim.x * blockDim.x) {
-        const long long m = i / g.plane, f = i - m * g.plane;
-        const int fz = (int)(f / g.sz);
-        const long long r = f - fz * g.sz;
-        const int fy = (int)(r / g.sy), fx = (int)(r - fy * g.sy);
-        const int iz = fz - OZ3, iy = fy - OY3, ix = fx - OX3;
-        float c = 0.f, ch = 0.f;
-        if (iz >= 0 && iz < g.NZ && iy >= 0 && iy < g.NY && ix >= 0 && ix < g.NX) {
-            const int pz = min(max(iz - g.P, 0), g.nz - 1), py = min(max(iy - g.P, 0), g.ny - 1),
-                      px = min(max(ix - g.P, 0), g.nx - 1);
-            c = vp[((m * g.nz + pz) * g.ny + py) * g.nx + px];
-            const double cd = c;
-            ch = (float)(dt * dt * cd * cd / (dx * dx));
+    const long long rows = (long long)nmodels * g.SZ * g.SY;
+    for (long long row = blockIdx.x * 4ll + threadIdx.x / 64; row < rows; row += gridDim.x * 4ll) {
+        const long long pl = row / g.SY, m = pl / g.SZ;
+        const int iz = (int)(pl - m * g.SZ) - OZ3, iy = (int)(row - pl * g.SY) - OY3;
+        const bool in = iz >= 0 && iz < g.NZ && iy >= 0 && iy < g.NY;
+        const int pz = min(max(iz - g.P, 0), g.nz - 1), py = min(max(iy - g.P, 0), g.ny - 1);
+        const float *vr = vp + ((m * g.nz + pz) * g.ny + py) * g.nx;
+        for (int fx = threadIdx.x & 63; fx < g.SX; fx += 64) {
+            const int ix = fx - OX3;
+            float c = 0.f, ch = 0.f;
+            if (in && ix >= 0 && ix < g.NX) {
+                c = vr[min(max(ix - g.P, 0), g.nx - 1)];
+                const double cd = c;
+                ch = (float)(dt * dt * cd * cd / (dx * dx));
+            }
+            chat[row * g.SX + fx] = ch;
+            cpad[row * g.SX + fx] = c;
         }
-        chat[i] = ch;
-        cpad[i] = c;
     }
 }
 
@@ -1009,30 +1011,102 @@ __global__ void ac3_sum_shots_kernel(Grid3 g, int nmodels, int spm, const float 
     }
 }
 
-// Fold the padded cells onto the physical cells they replicate, then the
-// chain rule dchat/dc = 2 dt^2 c / dx^2.
-__global__ void ac3_finalize_kernel(Grid3 g, int nmodels, const float *acc, const float *cpad,
-                                    double dt, double dx, float *g_vp)
+// Fold the padded cells onto the physical cells they replicate (their range
+// on one axis: cell i of n, N padded), then the chain rule
+// dchat/dc = 2 dt^2 c / dx^2.
+__device__ __forceinline__ void fold3(int P, int i, int n, int N, int &lo, int &hi)
 {
-    const long long nphys = (long long)g.nx * g.ny * g.nz;
-    const long long n = (long long)nmodels * nphys;
-    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
-         i += (long long)gridDim.x * blockDim.x) {
-        const long long m = i / nphys, rem = i - m * nphys;
-        const int iz = (int)(rem / ((long long)g.nx * g.ny));
-        const long long r2 = rem - (long long)iz * g.nx * g.ny;
-        const int iy = (int)(r2 / g.nx), ix = (int)(r2 - (long long)iy * g.nx);
-        const int zlo = iz == 0 ? 0 : iz + g.P, zhi = iz == g.nz - 1 ? g.NZ - 1 : iz + g.P;
-        const int ylo = iy == 0 ? 0 : iy + g.P, yhi = iy == g.ny - 1 ? g.NY - 1 : iy + g.P;
-        const int xlo = ix == 0 ? 0 : ix + g.P, xhi = ix == g.nx - 1 ? g.NX - 1 : ix + g.P;
+    lo = i == 0 ? 0 : i + P;
+    hi = i == n - 1 ? N - 1 : i + P;
+}
+
+__device__ __forceinline__ float chain3(const float *cpad, double dt, double dx)
+{
+    const double c = *cpad;
+    return (float)(2.0 * dt * dt * c / (dx * dx));
+}
+
+__device__ __forceinline__ double wave_sum(double v)
+{
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+    return v;
+}
+
+// A wavefront per row of cells (a thread per cell divides three times by
+// run-time sizes for its place, and the threads of the end cells in x sum
+// P + 1 cells each while their wavefront waits: 400^3 588 us, by rows 401).  With
+// a layer, the cells on an edge of the grid (end cells of two or three axes)
+// are left to ac3_fold_edges_kernel.
+__global__ __launch_bounds__(256) void ac3_finalize_kernel(Grid3 g, int nmodels, const float *acc, const float *cpad,
+                                                           double dt, double dx, float *g_vp)
+{
+    const int lane = threadIdx.x & 63;
+    const long long rows = (long long)nmodels * g.nz * g.ny;
+    for (long long row = blockIdx.x * 4ll + threadIdx.x / 64; row < rows; row += gridDim.x * 4ll) {
+        const long long pl = row / g.ny, m = pl / g.nz;
+        const int iz = (int)(pl - m * g.nz), iy = (int)(row - pl * g.ny);
+        const bool end = iz == 0 || iz == g.nz - 1 || iy == 0 || iy == g.ny - 1;
+        int zlo, zhi, ylo, yhi;
+        fold3(g.P, iz, g.nz, g.NZ, zlo, zhi);
+        fold3(g.P, iy, g.ny, g.NY, ylo, yhi);
+        if (g.P > 0 && zhi > zlo && yhi > ylo) continue;
         const float *am = acc + m * g.plane;
-        float v = 0.f;
-        for (int pz = zlo; pz <= zhi; ++pz)
-            for (int py = ylo; py <= yhi; ++py)
-                for (int px = xlo; px <= xhi; ++px) v += am[f3(g, pz, py, px)];
-        const double c = cpad[m * g.plane + f3(g, iz + g.P, iy + g.P, ix + g.P)];
-        g_vp[i] = (float)(2.0 * dt * dt * c / (dx * dx)) * v;
+        const float *cr = cpad + m * g.plane + f3(g, iz + g.P, iy + g.P, g.P);
+        for (int ix = lane; ix < g.nx; ix += 64) {
+            if (g.P > 0 && (ix == 0 || ix == g.nx - 1)) continue;
+            float v = 0.f;
+            for (int pz = zlo; pz <= zhi; ++pz)
+#pragma unroll 4
+                for (int py = ylo; py <= yhi; ++py) v += am[f3(g, pz, py, ix + g.P)];
+            g_vp[row * g.nx + ix] = chain3(cr + ix, dt, dx) * v;
+        }
+        if (g.P == 0 || end) continue;
+        for (int e = 0; e < 2; ++e) {          // (one cell in x: formed twice alike)
+            const int ix = e ? g.nx - 1 : 0;
+            int xlo, xhi;
+            fold3(g.P, ix, g.nx, g.NX, xlo, xhi);
+            double v = 0.0;
+            for (int px = xlo + lane; px <= xhi; px += 64) v += (double)am[f3(g, zlo, ylo, px)];
+            v = wave_sum(v);
+            if (lane == 0) g_vp[row * g.nx + ix] = chain3(cr + ix, dt, dx) * (float)v;
+        }
     }
+}
+
+// The cells on the grid's 12 edges, a workgroup each: an edge cell gathers
+// (P+1)^2 padded cells and a corner (P+1)^3, which one thread summed in turn
+// in 0.82 ms for P = 20 and 1.90 ms for P = 24; now 26 us for P = 20.  Threads take
+// every 256th cell, in FP64.  blockIdx.x: cell along the axis; y: axis and
+// which ends of the other two; z: model.  (A corner is formed alike by the
+// three edges that meet there.)
+__global__ __launch_bounds__(256) void ac3_fold_edges_kernel(Grid3 g, const float *acc, const float *cpad, double dt,
+                                                             double dx, float *g_vp)
+{
+    __shared__ double part[256];
+    const int axis = blockIdx.y >> 2;
+    const int ix = axis == 0 ? blockIdx.x : blockIdx.y & 1 ? g.nx - 1 : 0;
+    const int iy = axis == 1 ? blockIdx.x : (axis == 0 ? blockIdx.y & 1 : blockIdx.y & 2) ? g.ny - 1 : 0;
+    const int iz = axis == 2 ? blockIdx.x : blockIdx.y & 2 ? g.nz - 1 : 0;
+    if (ix >= g.nx || iy >= g.ny || iz >= g.nz) return;     // the grid is the longest axis wide
+    int xlo, xhi, ylo, yhi, zlo, zhi;
+    fold3(g.P, ix, g.nx, g.NX, xlo, xhi);
+    fold3(g.P, iy, g.ny, g.NY, ylo, yhi);
+    fold3(g.P, iz, g.nz, g.NZ, zlo, zhi);
+    const float *am = acc + blockIdx.z * g.plane;
+    const int wx = xhi - xlo + 1, wy = yhi - ylo + 1, cells = wx * wy * (zhi - zlo + 1);
+    double v = 0.0;
+#pragma unroll 4
+    for (int q = threadIdx.x; q < cells; q += 256) {
+        const int pz = q / (wx * wy), r = q - pz * wx * wy, py = r / wx;
+        v += (double)am[f3(g, zlo + pz, ylo + py, xlo + r - py * wx)];
+    }
+    part[threadIdx.x] = v;
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
+    v = wave_sum(((part[threadIdx.x] + part[threadIdx.x + 64]) + part[threadIdx.x + 128]) + part[threadIdx.x + 192]);
+    if (threadIdx.x == 0)
+        g_vp[(((long long)blockIdx.z * g.nz + iz) * g.ny + iy) * g.nx + ix] =
+            chain3(cpad + blockIdx.z * g.plane + f3(g, iz + g.P, iy + g.P, ix + g.P), dt, dx) * (float)v;
 }
 
 } // namespace
@@ -1096,20 +1170,21 @@ void launch_ac3_adj(const Ac3AdjArgs &a, hipStream_t s)
 void launch_ac3_prep(const Grid3 &g, int nmodels, const float *vp, double dt, double dx,
                      float *chat, float *cpad, hipStream_t s)
 {
-    const long long n = (long long)nmodels * g.plane;
-    const int blocks = (int)std::min<long long>((n + 255) / 256, 65536);
+    const int blocks = (int)std::min<long long>(((long long)nmodels * g.SZ * g.SY + 3) / 4, 65536);
     ac3_prep_kernel<<<blocks, 256, 0, s>>>(g, nmodels, vp, dt, dx, chat, cpad);
 }
 
 void launch_ac3_finalize(const Grid3 &g, int nmodels, int spm, const float *grad, float *acc,
                          const float *cpad, double dt, double dx, float *g_vp, hipStream_t s)
 {
-    long long n = (long long)nmodels * g.plane;
-    int blocks = (int)std::min<long long>((n + 255) / 256, 65536);
-    ac3_sum_shots_kernel<<<blocks, 256, 0, s>>>(g, nmodels, spm, grad, acc);
-    n = (long long)nmodels * g.nx * g.ny * g.nz;
-    blocks = (int)std::min<long long>((n + 255) / 256, 65536);
-    ac3_finalize_kernel<<<blocks, 256, 0, s>>>(g, nmodels, acc, cpad, dt, dx, g_vp);
+    int blocks = (int)std::min<long long>(((long long)nmodels * g.plane + 255) / 256, 65536);
+    const float *sum = spm == 1 ? grad : acc;               // one shot per model: its gradient is the sum
+    if (spm > 1) ac3_sum_shots_kernel<<<blocks, 256, 0, s>>>(g, nmodels, spm, grad, acc);
+    blocks = (int)std::min<long long>(((long long)nmodels * g.nz * g.ny + 3) / 4, 65536);
+    ac3_finalize_kernel<<<blocks, 256, 0, s>>>(g, nmodels, sum, cpad, dt, dx, g_vp);
+    for (int m0 = 0; g.P > 0 && m0 < nmodels; m0 += 65535)  // a launch's z extent
+        ac3_fold_edges_kernel<<<dim3(std::max({g.nx, g.ny, g.nz}), 12, std::min(65535, nmodels - m0)), 256, 0, s>>>(
+            g, sum + m0 * g.plane, cpad + m0 * g.plane, dt, dx, g_vp + (long long)m0 * g.nx * g.ny * g.nz);
 }
 
 } // namespace sg
