@@ -88,10 +88,10 @@ __device__ __forceinline__ int work_id()
 // grid holds band_blocks(ntl) workgroups per (shot, chunk); those past the
 // list return at once.
 __host__ __device__ __forceinline__ int band_per(int ntl) { return (ntl + NXCD - 1) / NXCD; }
-__device__ __forceinline__ bool band_item(int ntl, int &cs, int &t)
+__device__ __forceinline__ bool band_item(int b, int ntl, int &cs, int &t)
 {
     const int per = band_per(ntl);
-    const int b = (int)blockIdx.x, x = b % NXCD, s = b / NXCD;
+    const int x = b % NXCD, s = b / NXCD;
     cs = s / per;
     t = x * per + (s - cs * per);
     return t < ntl;
@@ -382,8 +382,7 @@ void ac3_phi_kernel(Ac3PhiArgs a)
 // halo and phi_y with its y halo in LDS planes, phi_z in a register window;
 // the other tiles read the few stencil points of their slab planes directly.
 template <bool SNAP, bool REC, bool LAYER>
-__global__ __launch_bounds__(NTH3) __attribute__((amdgpu_waves_per_eu(LAYER ? 4 : 8)))
-void ac3_fwd_kernel(Ac3FwdArgs a)
+__device__ __forceinline__ void fwd_tile(const Ac3FwdArgs &a, int b)
 {
     constexpr int W = TX3 + 8;
     constexpr int WX = TX3 + 8, WY = TX3;      // phi_x plane: TY3 rows of WX; phi_y: TY3 + 8 rows of WY
@@ -394,7 +393,7 @@ void ac3_fwd_kernel(Ac3FwdArgs a)
     const Grid3 &g = a.g;
     const int nzf = (g.NZ + g.zcf - 1) / g.zcf;
     int cs, ti;
-    if (!band_item(a.ntl, cs, ti)) return;
+    if (!band_item(b, a.ntl, cs, ti)) return;
     const int shot = cs / nzf, zc = cs - shot * nzf, tile = a.tiles[a.t0 + ti];
     const int nxy = g.ntx * g.nty;
     const int ty = tile / g.ntx, tx = tile - ty * g.ntx;
@@ -597,6 +596,23 @@ void ac3_fwd_kernel(Ac3FwdArgs a)
     if (psw) stb(psi, psf, psn);
 }
 
+template <bool SNAP, bool REC, bool LAYER>
+__global__ __launch_bounds__(NTH3) __attribute__((amdgpu_waves_per_eu(LAYER ? 4 : 8)))
+void ac3_fwd_kernel(Ac3FwdArgs a)
+{
+    fwd_tile<SNAP, REC, LAYER>(a, blockIdx.x);
+}
+
+// Both parts of a step in one launch: the layer tiles' nb workgroups, then the
+// others' (BOTH3_FWD says when).
+template <bool SNAP, bool REC>
+__global__ __launch_bounds__(NTH3) __attribute__((amdgpu_waves_per_eu(4)))
+void ac3_fwd_both_kernel(Ac3FwdArgs a, Ac3FwdArgs o, int nb)
+{
+    if ((int)blockIdx.x < nb) fwd_tile<SNAP, REC, true>(a, blockIdx.x);
+    else                      fwd_tile<SNAP, REC, false>(o, blockIdx.x - nb);
+}
+
 // ------------------------------------------------------------ adjoint pass A
 // Same work items and marching, on chat s^{k+2} (its factors one plane ahead).
 __global__ __launch_bounds__(NTH3) __attribute__((amdgpu_waves_per_eu(8)))
@@ -723,8 +739,7 @@ constexpr int APD = 1, ANB = APD + 1, AZR = 10;
 static_assert(AZR % ANB == 0 && 8 + APD < AZR, "ring sizes");
 
 template <bool LAYER>
-__global__ __launch_bounds__(NTH3) __attribute__((amdgpu_waves_per_eu(LAYER ? 4 : 8)))
-void ac3_adj_kernel(Ac3AdjArgs a)
+__device__ __forceinline__ void adj_tile(const Ac3AdjArgs &a, int b)
 {
     constexpr int W = TX3 + 8;
     constexpr int WX = TX3 + 8, WY = TX3;
@@ -736,7 +751,7 @@ void ac3_adj_kernel(Ac3AdjArgs a)
     const Grid3 &g = a.g;
     const int nxy = g.ntx * g.nty;
     int cs, ti;
-    if (!band_item(a.ntl, cs, ti)) return;
+    if (!band_item(b, a.ntl, cs, ti)) return;
     const int shot = cs / g.nzc, zc = cs - shot * g.nzc, tile = a.tiles[a.t0 + ti];
     const int ty = tile / g.ntx, tx = tile - ty * g.ntx;
     const int x0 = tx * TX3, y0 = ty * TY3, z0 = zc * g.zca, z1 = min(z0 + g.zca, g.NZ);
@@ -973,6 +988,18 @@ void ac3_adj_kernel(Ac3AdjArgs a)
     if (esw) stb(ee, esf, esn);
 }
 
+// Both parts in one launch, the layer tiles' nb workgroups first.  The layer
+// tiles' registers allow half the wavefronts that the others could have, which
+// costs the others nothing (the adjoint's streams keep enough loads in
+// flight), while two launches each waited for their own last tiles: 128^3 +
+// 20-cell layer 55 + 37 -> 75 us, 400^3 + 24 cells 326 + 539 -> 787.
+__global__ __launch_bounds__(NTH3) __attribute__((amdgpu_waves_per_eu(4)))
+void ac3_adj_kernel(Ac3AdjArgs a, Ac3AdjArgs o, int nb)
+{
+    if ((int)blockIdx.x < nb) adj_tile<true>(a, blockIdx.x);
+    else                      adj_tile<false>(o, blockIdx.x - nb);
+}
+
 // A wavefront per frame row (a thread per cell divides three times by
 // run-time strides for its place: 400^3 395 us, by rows 237).
 __global__ __launch_bounds__(256) void ac3_prep_kernel(Grid3 g, int nmodels, const float *vp, double dt, double dx,
@@ -1131,40 +1158,53 @@ void launch_ac3_phi_adj(const Ac3PhiAdjArgs &a, int nshots, hipStream_t s)
     ac3_phi_adj_kernel<<<a.nitems * nshots, NTH3, 0, s>>>(a);
 }
 
-template <bool LAYER>
-void launch_ac3_fwd_part(Ac3FwdArgs a, int t0, int ntl, hipStream_t s)
+// f(snapshot?, records?) of a forward launch as constants
+template <class F>
+void with_outputs(const Ac3FwdArgs &a, F &&f)
 {
-    a.t0 = t0;
-    a.ntl = ntl;
-    if (ntl == 0 || a.nshots == 0) return;
-    a.g.zcf = chunk3(a.g.zcf, TZCF_DEF, FILL3_FWD, ntl, a.g.NZ, a.nshots);
-    const int nb = band_per(ntl) * NXCD * ((a.g.NZ + a.g.zcf - 1) / a.g.zcf) * a.nshots;
-    const bool snap = a.snap != nullptr, rec = a.seis != nullptr;
-    if (snap) { if (rec) ac3_fwd_kernel<true, true, LAYER><<<nb, NTH3, 0, s>>>(a); else ac3_fwd_kernel<true, false, LAYER><<<nb, NTH3, 0, s>>>(a); }
-    else      { if (rec) ac3_fwd_kernel<false, true, LAYER><<<nb, NTH3, 0, s>>>(a); else ac3_fwd_kernel<false, false, LAYER><<<nb, NTH3, 0, s>>>(a); }
+    const bool rec = a.seis != nullptr;
+    if (a.snap) { if (rec) f(std::true_type(), std::true_type()); else f(std::true_type(), std::false_type()); }
+    else        { if (rec) f(std::false_type(), std::true_type()); else f(std::false_type(), std::false_type()); }
 }
 
 void launch_ac3_fwd(const Ac3FwdArgs &a, hipStream_t s)
 {
+    if (a.nshots == 0) return;
     const int nxy = a.g.ntx * a.g.nty;
-    launch_ac3_fwd_part<true>(a, 0, a.nnear, s);
-    launch_ac3_fwd_part<false>(a, a.nnear, nxy - a.nnear, s);
+    Ac3FwdArgs p[2] = {a, a};
+    int nb[2];
+    for (int part = 0; part < 2; ++part) {                  // the layer tiles, the others
+        p[part].t0 = part ? a.nnear : 0;
+        p[part].ntl = part ? nxy - a.nnear : a.nnear;
+        const int zc = p[part].g.zcf = chunk3(a.g.zcf, TZCF_DEF, FILL3_FWD, p[part].ntl, a.g.NZ, a.nshots);
+        nb[part] = band_per(p[part].ntl) * NXCD * ((a.g.NZ + zc - 1) / zc) * a.nshots;
+    }
+    with_outputs(a, [&](auto snap, auto rec) {
+        constexpr bool S = decltype(snap)::value, R = decltype(rec)::value;
+        if (nb[0] && nb[1] && nb[1] <= BOTH3_FWD) {
+            ac3_fwd_both_kernel<S, R><<<nb[0] + nb[1], NTH3, 0, s>>>(p[0], p[1], nb[0]);
+            return;
+        }
+        if (nb[0]) ac3_fwd_kernel<S, R, true><<<nb[0], NTH3, 0, s>>>(p[0]);
+        if (nb[1]) ac3_fwd_kernel<S, R, false><<<nb[1], NTH3, 0, s>>>(p[1]);
+    });
 }
 
 void launch_ac3_adj(const Ac3AdjArgs &a, hipStream_t s)
 {
+    if (a.nshots == 0) return;
     const int nxy = a.g.ntx * a.g.nty;
+    Ac3AdjArgs p[2] = {a, a};
+    int nb[2];
     for (int part = 0; part < 2; ++part) {
-        Ac3AdjArgs b = a;
-        b.t0 = part ? a.nnear : 0;
-        b.ntl = part ? nxy - a.nnear : a.nnear;
-        if (b.ntl == 0 || a.nshots == 0) continue;
-        b.g.zca = chunk3(a.g.zca, TZCA_DEF, FILL3_ADJ, b.ntl, a.g.NZ, a.nshots);
-        b.g.nzc = (a.g.NZ + b.g.zca - 1) / b.g.zca;
-        const int nb = band_per(b.ntl) * NXCD * b.g.nzc * a.nshots;
-        if (part) ac3_adj_kernel<false><<<nb, NTH3, 0, s>>>(b);
-        else ac3_adj_kernel<true><<<nb, NTH3, 0, s>>>(b);
+        p[part].t0 = part ? a.nnear : 0;
+        p[part].ntl = part ? nxy - a.nnear : a.nnear;
+        Grid3 &g = p[part].g;
+        g.zca = chunk3(a.g.zca, TZCA_DEF, FILL3_ADJ, p[part].ntl, g.NZ, a.nshots);
+        g.nzc = (g.NZ + g.zca - 1) / g.zca;
+        nb[part] = band_per(p[part].ntl) * NXCD * g.nzc * a.nshots;
     }
+    ac3_adj_kernel<<<nb[0] + nb[1], NTH3, 0, s>>>(p[0], p[1], nb[0]);
 }
 
 void launch_ac3_prep(const Grid3 &g, int nmodels, const float *vp, double dt, double dx,

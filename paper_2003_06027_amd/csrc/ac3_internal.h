@@ -36,6 +36,13 @@ static_assert(TZCF_DEF <= TZC && TZCI_DEF <= TZC && TZCA_DEF <= TZC && TZC_MIN <
 // 652 -> 628 us; 400^3 2359 -> 2343 us).
 constexpr int TZC_AUTO_MIN = 8;
 constexpr int FILL3_FWD = 512, FILL3_ADJ = 2048;
+// The forward's layer tiles and its others go out in one launch while the
+// others' workgroups are at most this many.  One launch fills the CUs that the
+// layer tiles' last workgroups leave idle, but gives the others the layer
+// tiles' register budget, half the wavefronts: per step 64^3 + 16-cell layer
+// 48 -> 39 us, 128^3 + 20 94 -> 89, 200^3 198 -> 183, 240 x 240 x 200 205 -> 201,
+// 320^3 478 -> 479 (2112 workgroups), 400^3 + 24 487 -> 501.
+constexpr int BOTH3_FWD = 2048;
 int chunk3(int setting, int def, int fill, int ntl, int NZ, int nshots);
 constexpr int OX3 = 32;  // x offset (128-byte aligned rows)
 constexpr int OY3 = 4;
