@@ -287,11 +287,10 @@ SG_API int set_time_blocking(sg_model *m, int32_t steps);
  *                          (3-D chunks: 16 to 64, multiples of 8; until set,
  *                          32 and 64 in the tile passes, shorter on grids
  *                          of few tiles, and 16);
- *   SG_TUNE_PAIR           2-D acoustic with time blocking: 1 (the default)
- *                          launches the step of the tiles by the layer with
- *                          the two-step launch of the blocked tiles as one
- *                          grid in sweeps that record no seismograms (the
- *                          recompute), 0 apart;
+ *   SG_TUNE_PAIR           2-D acoustic: 1 (the default) launches what a
+ *                          step computes (the tiles by the layer, the other
+ *                          one-step tiles, the blocked tiles) as one grid
+ *                          where that is faster, 0 apart;
  *   SG_TUNE_SHOT_GROUP     elastic: shots of one model per thread, 1, 2 or 4
  *                          (0: 4 if the shots per model divide by 4, else 2
  *                          if even, else 1; a value that does not divide the

@@ -132,12 +132,12 @@ __device__ __forceinline__ TileItem tile_item(const int *tiles, int ntl, int w)
 
 // Fill the (RW+8) x (TX+8) LDS tile: own cells by the caller, the 4-cell
 // halo here (value f(frame index)).
-template <int RW, class Fn>
+template <int RW, int NT, class Fn>
 __device__ __forceinline__ void load_halo(const Grid2 &g, float *lds, int x0, int z0, Fn f)
 {
     constexpr int H = 4, W = TX + 2 * H;
     constexpr int NH = 2 * H * W + 2 * RW * H;
-    for (int i = threadIdx.x; i < NH; i += NTH) {
+    for (int i = threadIdx.x; i < NH; i += NT) {
         int r, c;
         if (i < 2 * H * W) {
             const int s = i / W;
@@ -267,6 +267,29 @@ __device__ __forceinline__ float first_sample(const Ac2AdjArgs &a, const TileIte
                ? a.dJdd[((long long)it.shot * a.nt + a.k) * a.nrec + rec_id(rc.ent)] : 0.f;
 }
 
+// Several source nodes per shot: the wavelet gradient of the nodes on these
+// RW rows, scale * s^{k+1}; own(row offset j) is this thread's s^{k+1}, put
+// into LDS at at(row, column).  (As a launch of its own: 1.4 us of every step.)
+template <int RW, int NT, class Fo, class Fn>
+__device__ __forceinline__ void gather_nodes(const Ac2AdjArgs &a, const TileItem &it, Fo own, Fn at)
+{
+    if (a.nsrc <= 1 || !a.gwav) return;
+    const int *off = a.src_off + (long long)it.shot * (a.g.ntx * a.g.ntz + 1);
+    const int b = off[it.tile], e = off[it.tile + 1];
+    if (b >= e) return;                   // uniform over the block
+    constexpr int RPT = RW * TX / NT;
+    const int lx = threadIdx.x % TX, ly = threadIdx.x / TX;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < RPT; ++j) at(ly * RPT + j, lx) = own(j);
+    __syncthreads();
+    for (int i = b + threadIdx.x; i < e; i += NT) {
+        const int ent = a.src_ent[i], cell = src_cell(ent) - it.sub * RW * TX;
+        if (cell < 0 || cell >= RW * TX) continue;
+        a.gwav[((long long)it.shot * a.nsrc + src_node(ent)) * a.nt + a.k] = a.src_scale * at(cell / TX, cell % TX);
+    }
+}
+
 __global__ void ac2_src_gather_kernel(int nshots, int nsrc, long long plane, const long long *node_f,
                                       const float *s1, float *gw, int nt, int k, float scale)
 {
@@ -286,10 +309,10 @@ void launch_ac2_src_gather(int nshots, int nsrc, long long plane, const long lon
 // ------------------------------------------------------------ forward pass B
 // RW rows of a tile away from the layer (the interior update), u^k with a
 // 4-cell halo in LDS.
-template <int RW, bool SNAP, bool REC>
+template <int RW, int NT, bool SNAP, bool REC>
 __device__ __forceinline__ void fwd_tile(const Ac2FwdArgs &a, float *su, float *sadd, const TileItem &it)
 {
-    constexpr int H = 4, W = TX + 2 * H, RPT = RW / (NTH / TX);
+    constexpr int H = 4, W = TX + 2 * H, RPT = RW * TX / NT;
     const Grid2 &g = a.g;
     const int shot = it.shot;
     const int tz = it.tile / g.ntx, tx = it.tile - tz * g.ntx;
@@ -300,7 +323,7 @@ __device__ __forceinline__ void fwd_tile(const Ac2FwdArgs &a, float *su, float *
     const int tid = threadIdx.x, lx = tid % TX, ly = tid / TX;
     const int ix = x0 + lx;
 
-    NodeSources<RW, NTH> ns;
+    NodeSources<RW, NT> ns;
     ns.begin(a, it, sadd);
     TileRecs rc{};
     if constexpr (REC) rc.begin(a, it);
@@ -311,7 +334,7 @@ __device__ __forceinline__ void fwd_tile(const Ac2FwdArgs &a, float *su, float *
         uc[j] = u[fidx(g, z0 + r, ix)];
         su[(r + H) * W + lx + H] = uc[j];
     }
-    load_halo<RW>(g, su, x0, z0, [&](long long f) { return u[f]; });
+    load_halo<RW, NT>(g, su, x0, z0, [&](long long f) { return u[f]; });
     __syncthreads();
     ns.fill(a, it, sadd);
 
@@ -345,7 +368,7 @@ __device__ __forceinline__ void fwd_tile(const Ac2FwdArgs &a, float *su, float *
 #pragma unroll
             for (int j = 0; j < RPT; ++j) su[(ly * RPT + j + H) * W + lx + H] = un[j];
             __syncthreads();
-            record_tile<RW, NTH>(a, it, rc, [&](int r, int c) { return su[(r + H) * W + c + H]; });
+            record_tile<RW, NT>(a, it, rc, [&](int r, int c) { return su[(r + H) * W + c + H]; });
         }
     }
 }
@@ -357,15 +380,15 @@ __global__ __launch_bounds__(NTH) void ac2_fwd_kernel(Ac2FwdArgs a)
     __shared__ float su[(RW + 8) * (TX + 8)];
     extern __shared__ float sadd[];
     const int w = xcd_work_id(a.ntl * a.nshots * (TZ / RW));
-    fwd_tile<RW, SNAP, REC>(a, su, sadd, tile_item<RW>(a.tiles, a.ntl, w));
+    fwd_tile<RW, NTH, SNAP, REC>(a, su, sadd, tile_item<RW>(a.tiles, a.ntl, w));
 }
 
 // ------------------------------------------------------------ adjoint pass B
 // RW rows of a tile away from the layer, chat s^{k+2} with a 4-cell halo in LDS.
-template <int RW>
+template <int RW, int NT>
 __device__ __forceinline__ void adj_tile(const Ac2AdjArgs &a, float *sc, const TileItem &it)
 {
-    constexpr int H = 4, W = TX + 2 * H, RPT = RW / (NTH / TX);
+    constexpr int H = 4, W = TX + 2 * H, RPT = RW * TX / NT;
     const Grid2 &g = a.g;
     const int shot = it.shot;
     const int tz = it.tile / g.ntx, tx = it.tile - tz * g.ntx;
@@ -387,7 +410,7 @@ __device__ __forceinline__ void adj_tile(const Ac2AdjArgs &a, float *sc, const T
         sc2[j] = s2[f];
         sc[(r + H) * W + lx + H] = chat[f] * sc2[j];
     }
-    load_halo<RW>(g, sc, x0, z0, [&](long long f) { return chat[f] * s2[f]; });
+    load_halo<RW, NT>(g, sc, x0, z0, [&](long long f) { return chat[f] * s2[f]; });
     __syncthreads();
     const float d0 = first_sample(a, it, rc);
 
@@ -410,7 +433,7 @@ __device__ __forceinline__ void adj_tile(const Ac2AdjArgs &a, float *sc, const T
 #pragma unroll
         for (int j = 0; j < RPT; ++j) sc[(ly * RPT + j + H) * W + lx + H] = av[j];
         __syncthreads();
-        inject_tile<RW, NTH>(a, it, rc, d0, [&](int r, int c) -> float & { return sc[(r + H) * W + c + H]; });
+        inject_tile<RW, NT>(a, it, rc, d0, [&](int r, int c) -> float & { return sc[(r + H) * W + c + H]; });
         __syncthreads();
 #pragma unroll
         for (int j = 0; j < RPT; ++j) av[j] = sc[(ly * RPT + j + H) * W + lx + H];
@@ -428,6 +451,8 @@ __device__ __forceinline__ void adj_tile(const Ac2AdjArgs &a, float *sc, const T
             if (a.gwav && f == src) a.gwav[(long long)shot * a.nt + a.k] = s1 * a.src_scale;
         }
     }
+    gather_nodes<RW, NT>(a, it, [&](int j) { return av[j]; },
+                         [&](int r, int c) -> float & { return sc[(r + H) * W + c + H]; });
 }
 
 // (8 waves per SIMD: 64 VGPRs, no spill; measured 2 % faster than the
@@ -437,7 +462,7 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(8))) void a
 {
     __shared__ float sc[(RW + 8) * (TX + 8)];
     const int w = xcd_work_id(a.ntl * a.nshots * (TZ / RW));
-    adj_tile<RW>(a, sc, tile_item<RW>(a.tiles, a.ntl, w));
+    adj_tile<RW, NTH>(a, sc, tile_item<RW>(a.tiles, a.ntl, w));
 }
 
 // ---------------------------------------------------------- two-step kernels
@@ -639,15 +664,12 @@ __global__ __launch_bounds__(NTB) void ac2_fwd2_kernel(Ac2Fwd2Args a)
 // s^{k+1} on the tile + 4 from chat s^{k+2} on the tile + 8, then s^k on
 // the tile; the gradient gets s^{k+1} w~^k, then s^k w~^{k-1}, as in two
 // single steps.
-template <int RW>
-__global__ __launch_bounds__(NTH) void ac2_adj2_kernel(Ac2Adj2Args a)
+// p0: chat s^{k+2} on the rows + 8 (rows0 x W0), p1: chat s^{k+1} on the rows + 4 (rows1 x W1)
+template <int RW, int NT>
+__device__ __forceinline__ void adj2_tile(const Ac2Adj2Args &a, float *p0, float *p1, const TileItem &item)
 {
-    constexpr int RPT = RW / (NTH / TX), NRING = nring(RW), RING_IT = (NRING + NTH - 1) / NTH;
-    __shared__ __attribute__((aligned(16))) float p0[rows0(RW) * W0];   // chat s^{k+2} on the rows + 8
-    __shared__ float p1[rows1(RW) * W1];   // chat s^{k+1} on the rows + 4
+    constexpr int RPT = RW * TX / NT, NRING = nring(RW), RING_IT = (NRING + NT - 1) / NT;
     const Grid2 &g = a.g;
-    const int w = xcd_work_id(a.ntl * a.nshots * (TZ / RW));
-    const TileItem item = tile_item<RW>(a.tiles, a.ntl, w);
     const int shot = item.shot, tz = item.tile / g.ntx, tx = item.tile - tz * g.ntx;
     const int x0 = tx * TX, z0 = tz * TZ + item.sub * RW;
     const long long so = (long long)shot * g.plane;
@@ -670,7 +692,7 @@ __global__ __launch_bounds__(NTH) void ac2_adj2_kernel(Ac2Adj2Args a)
     float rch[RING_IT], rq2[RING_IT], rq3[RING_IT];
 #pragma unroll
     for (int it = 0; it < RING_IT; ++it) {
-        const int i = threadIdx.x + it * NTH;
+        const int i = threadIdx.x + it * NT;
         if (i < NRING) {
             int r, c;
             ring_cell<RW>(i, r, c);
@@ -680,11 +702,11 @@ __global__ __launch_bounds__(NTH) void ac2_adj2_kernel(Ac2Adj2Args a)
             rq3[it] = s3[f];
         }
     }
-    float4 cm[(rows0(RW) * (W0 / 4) + NTH - 1) / NTH];
-    dma_product_load<RW, NTH>(g, s2, chat, p0, x0, z0, cm);
+    float4 cm[(rows0(RW) * (W0 / 4) + NT - 1) / NT];
+    dma_product_load<RW, NT>(g, s2, chat, p0, x0, z0, cm);
     __builtin_amdgcn_s_waitcnt(0);       // the tile's direct loads have landed in LDS
     __syncthreads();
-    product_in_place<RW, NTH>(p0, cm);
+    product_in_place<RW, NT>(p0, cm);
     __syncthreads();
 
     // step k: s^{k+1} on the tile + 4
@@ -702,7 +724,7 @@ __global__ __launch_bounds__(NTH) void ac2_adj2_kernel(Ac2Adj2Args a)
     }
 #pragma unroll
     for (int it = 0; it < RING_IT; ++it) {
-        const int i = threadIdx.x + it * NTH;
+        const int i = threadIdx.x + it * NT;
         if (i < NRING) {
             int r, c;
             ring_cell<RW>(i, r, c);
@@ -725,6 +747,15 @@ __global__ __launch_bounds__(NTH) void ac2_adj2_kernel(Ac2Adj2Args a)
         __builtin_nontemporal_store(fmaf(v, w0[j], t), a.grad + so + f);
         if (a.gwav && f == src) a.gwav[(long long)shot * a.nt + a.k - 1] = v * a.src_scale;
     }
+}
+
+template <int RW>
+__global__ __launch_bounds__(NTH) void ac2_adj2_kernel(Ac2Adj2Args a)
+{
+    __shared__ __attribute__((aligned(16))) float p0[rows0(RW) * W0];
+    __shared__ float p1[rows1(RW) * W1];
+    const int w = xcd_work_id(a.ntl * a.nshots * (TZ / RW));
+    adj2_tile<RW, NTH>(a, p0, p1, tile_item<RW>(a.tiles, a.ntl, w));
 }
 
 // ---------------------------------------------------------------- near tiles
@@ -935,28 +966,33 @@ __global__ __launch_bounds__(NTN) __attribute__((amdgpu_waves_per_eu(8))) void a
     fwd_near_tile<RW, SNAP, REC>(a, su, sx, sz, sadd, tile_item<RW>(a.tiles, a.ntl, w));
 }
 
-// Step k of the tiles by the layer and steps k, k+1 of the blocked tiles in
-// one launch.  The two read only u^k, u^{k-1} (and phi~^{k-1}) and write
-// disjoint cells of u^{k+1} (and u^{k+2}, phi~^k, the seismograms), so they
-// need no order; one grid lets the near tiles fill the blocked launch's last
-// round instead of waiting for it.  The blocked tiles come first in the grid;
-// the two share one LDS buffer.
-constexpr int NPAIR_NEAR = nu8(TZ) + npx(TZ) + npz(TZ), NPAIR_BLK = rows0(TZ) * W0 + rows1(TZ) * W1;
-constexpr int NPAIR_LDS = NPAIR_NEAR > NPAIR_BLK ? NPAIR_NEAR : NPAIR_BLK;
-static_assert(NTN == NTB, "one block size for the pair");
-template <bool SNAP, bool REC>
-__global__ __launch_bounds__(NTN) __attribute__((amdgpu_waves_per_eu(8)))
-void ac2_fwd_pair_kernel(Ac2FwdArgs a, Ac2Fwd2Args b)
+// Everything that a forward step k launches in one grid: the blocked tiles'
+// steps k, k+1 (b), the tiles by the layer (a) and the other one-step tiles
+// (o).  They read only u^k, u^{k-1} (and phi~^{k-1}) and write disjoint cells
+// of u^{k+1} (and u^{k+2}, phi~^k, the seismograms), so they need no order.
+// They share one LDS buffer.
+constexpr int step_lds(int RW)
 {
-    __shared__ __attribute__((aligned(16))) float lds[NPAIR_LDS];
+    const int near = nu8(RW) + npx(RW) + npz(RW), blk = rows0(RW) * W0 + rows1(RW) * W1;
+    return near > blk ? near : blk;
+}
+static_assert(NTN == NTB, "one block size for the step");
+template <int RW, bool SNAP, bool REC, bool OTHER>
+__global__ __launch_bounds__(NTN) __attribute__((amdgpu_waves_per_eu(8)))
+void ac2_step_kernel(Ac2FwdArgs a, Ac2FwdArgs o, Ac2Fwd2Args b)
+{
+    constexpr int NS = TZ / RW;
+    __shared__ __attribute__((aligned(16))) float lds[step_lds(RW)];
     extern __shared__ float sadd[];
-    const int nb = b.ntl * b.nshots;
-    const int w = xcd_work_id(nb + a.ntl * a.nshots);
+    const int nb = b.ntl * b.nshots * NS, na = a.ntl * a.nshots * NS, no = o.ntl * o.nshots * NS;
+    const int w = xcd_work_id(nb + na + no);
     if (w < nb) {
-        fwd2_tile<TZ>(b, lds, lds + rows0(TZ) * W0, tile_item<TZ>(b.tiles, b.ntl, w));
-    } else {
-        fwd_near_tile<TZ, SNAP, REC>(a, lds, lds + nu8(TZ), lds + nu8(TZ) + npx(TZ), sadd,
-                                     tile_item<TZ>(a.tiles, a.ntl, w - nb));
+        fwd2_tile<RW>(b, lds, lds + rows0(RW) * W0, tile_item<RW>(b.tiles, b.ntl, w));
+    } else if (!OTHER || w < nb + na) {
+        fwd_near_tile<RW, SNAP, REC>(a, lds, lds + nu8(RW), lds + nu8(RW) + npx(RW), sadd,
+                                     tile_item<RW>(a.tiles, a.ntl, w - nb));
+    } else if constexpr (OTHER) {
+        fwd_tile<RW, NTN, SNAP, REC>(o, lds, sadd, tile_item<RW>(o.tiles, o.ntl, w - nb - na));
     }
 }
 
@@ -1124,8 +1160,11 @@ __device__ __forceinline__ void adj_near_tile(const Ac2AdjArgs &a, float *sc, fl
             __builtin_nontemporal_store(s1, s1o + f);
             __builtin_nontemporal_store(fmaf(s1, snv[j], grv[j]), a.grad + so + f);
             if (a.gwav && f == src) a.gwav[(long long)shot * a.nt + a.k] = s1 * a.src_scale;
+            av[j] = s1;
         }
     }
+    gather_nodes<RW, NTN>(a, it, [&](int j) { return av[j]; },
+                          [&](int r, int c) -> float & { return sc[(r + H2) * W0 + c + H2]; });
 }
 
 template <int RW>
@@ -1136,6 +1175,25 @@ __global__ __launch_bounds__(NTN) __attribute__((amdgpu_waves_per_eu(6))) void a
     __shared__ float sz[npz(RW)];
     const int w = xcd_work_id(a.ntl * a.nshots * (TZ / RW));
     adj_near_tile<RW>(a, sc, sx, sz, tile_item<RW>(a.tiles, a.ntl, w));
+}
+
+// The adjoint's step in one grid, as the forward's: steps k, k-1 of the
+// blocked tiles (b), step k of the tiles by the layer (a) and of the others (o).
+template <int RW, bool OTHER>
+__global__ __launch_bounds__(NTN) __attribute__((amdgpu_waves_per_eu(6)))
+void ac2_adj_step_kernel(Ac2AdjArgs a, Ac2AdjArgs o, Ac2Adj2Args b)
+{
+    constexpr int NS = TZ / RW;
+    __shared__ __attribute__((aligned(16))) float lds[step_lds(RW)];
+    const int nb = b.ntl * b.nshots * NS, na = a.ntl * a.nshots * NS, no = o.ntl * o.nshots * NS;
+    const int w = xcd_work_id(nb + na + no);
+    if (w < nb) {
+        adj2_tile<RW, NTN>(b, lds, lds + rows0(RW) * W0, tile_item<RW>(b.tiles, b.ntl, w));
+    } else if (!OTHER || w < nb + na) {
+        adj_near_tile<RW>(a, lds, lds + nu8(RW), lds + nu8(RW) + npx(RW), tile_item<RW>(a.tiles, a.ntl, w - nb));
+    } else if constexpr (OTHER) {
+        adj_tile<RW, NTN>(o, lds, tile_item<RW>(o.tiles, o.ntl, w - nb - na));
+    }
 }
 
 // ------------------------------------------------------------------ launchers
@@ -1161,67 +1219,100 @@ inline size_t node_lds(const Ac2FwdArgs &a, int RW)
     return a.nsrc > 1 ? sizeof(float) * RW * TX : 0;
 }
 
-void launch_ac2_fwd2(const Ac2Fwd2Args &a, hipStream_t s)
+// f(snapshot?, records?) of a forward launch as constants
+template <class F>
+void with_outputs(const Ac2FwdArgs &a, F &&f)
 {
-    const int nt = a.ntl * a.nshots;
-    with_rows(nt, [&](auto R) {
-        constexpr int RW = decltype(R)::value;
-        ac2_fwd2_kernel<RW><<<nt * (TZ / RW), NTB, 0, s>>>(a);
+    const bool rec = a.seis != nullptr;
+    if (a.snap) { if (rec) f(std::true_type(), std::true_type()); else f(std::true_type(), std::false_type()); }
+    else        { if (rec) f(std::false_type(), std::true_type()); else f(std::false_type(), std::false_type()); }
+}
+
+// One grid or several.  A step of fewer than FILL2 tiles is bound by the
+// latency of a launch, so its lists go out as one grid (260 x 160, 49 source
+// nodes: 38 -> 17 us per forward + recompute + adjoint step; 1000 x 500, one
+// shot: 31 -> 23).  From there on the other one-step tiles, few and in need of
+// a kernel of more registers, go apart; the tiles by the layer and the blocked
+// ones still share a grid, so that neither waits for the last workgroups of
+// the other: 1000 x 500, recording forward of 8 and 24 shots 21.0 -> 19.6 and
+// 47.8 -> 47.4 us per step (apart from STEP_REC tiles on: with 64 shots the whole
+// pass went from 454 to 457); adjoint, whole pass of 4, 16 and 64 shots 50.3 -> 47.1,
+// 133 -> 130 and 454 -> 451.
+constexpr int STEP_REC = 8192;
+
+void launch_ac2_step(const Ac2FwdArgs &a, const Ac2FwdArgs &o, const Ac2Fwd2Args &b, bool pair, hipStream_t s)
+{
+    const int na = a.ntl * a.nshots, no = o.ntl * o.nshots, nb = b.ntl * b.nshots, nt = na + no + nb;
+    const bool all = pair && nt < FILL2;
+    with_outputs(a, [&](auto snap, auto rec) {
+        constexpr bool S = decltype(snap)::value, R = decltype(rec)::value;
+        auto grid = [&](const Ac2FwdArgs &others) {
+            const int n = na + nb + others.ntl * others.nshots;
+            with_rows(n, [&](auto rows) {
+                constexpr int RW = decltype(rows)::value;
+                ac2_step_kernel<RW, S, R, (RW < TZ)><<<n * (TZ / RW), NTN, node_lds(a, RW), s>>>(a, others, b);
+            });
+        };
+        if (all && (na > 0) + (no > 0) + (nb > 0) > 1) {
+            grid(o);
+            return;
+        }
+        with_rows(no, [&](auto rows) {
+            constexpr int RW = decltype(rows)::value;
+            ac2_fwd_kernel<RW, S, R><<<no * (TZ / RW), NTH, node_lds(o, RW), s>>>(o);
+        });
+        if (pair && na > 0 && nb > 0 && (!R || na + nb < STEP_REC)) {
+            Ac2FwdArgs none = o;
+            none.ntl = 0;
+            grid(none);
+            return;
+        }
+        with_rows(na, [&](auto rows) {
+            constexpr int RW = decltype(rows)::value;
+            ac2_near_kernel<RW, S, R><<<na * (TZ / RW), NTN, node_lds(a, RW), s>>>(a);
+        });
+        with_rows(nb, [&](auto rows) {
+            constexpr int RW = decltype(rows)::value;
+            ac2_fwd2_kernel<RW><<<nb * (TZ / RW), NTB, 0, s>>>(b);
+        });
     });
 }
 
-void launch_ac2_adj2(const Ac2Adj2Args &a, hipStream_t s)
+void launch_ac2_adj_step(const Ac2AdjArgs &a, const Ac2AdjArgs &o, const Ac2Adj2Args &b, bool pair, hipStream_t s)
 {
-    const int nt = a.ntl * a.nshots;
-    with_rows(nt, [&](auto R) {
-        constexpr int RW = decltype(R)::value;
-        ac2_adj2_kernel<RW><<<nt * (TZ / RW), NTH, 0, s>>>(a);
+    const int na = a.ntl * a.nshots, no = o.ntl * o.nshots, nb = b.ntl * b.nshots, nt = na + no + nb;
+    const bool all = pair && nt < FILL2;
+    auto grid = [&](const Ac2AdjArgs &others) {
+        const int n = na + nb + others.ntl * others.nshots;
+        with_rows(n, [&](auto rows) {
+            constexpr int RW = decltype(rows)::value;
+            ac2_adj_step_kernel<RW, (RW < TZ)><<<n * (TZ / RW), NTN, 0, s>>>(a, others, b);
+        });
+    };
+    if (all && (na > 0) + (no > 0) + (nb > 0) > 1) {
+        grid(o);
+        return;
+    }
+    with_rows(no, [&](auto rows) {
+        constexpr int RW = decltype(rows)::value;
+        ac2_adj_kernel<RW><<<no * (TZ / RW), NTH, 0, s>>>(o);
+    });
+    if (pair && na > 0 && nb > 0) {
+        Ac2AdjArgs none = o;
+        none.ntl = 0;
+        grid(none);
+        return;
+    }
+    with_rows(na, [&](auto rows) {
+        constexpr int RW = decltype(rows)::value;
+        ac2_adj_near_kernel<RW><<<na * (TZ / RW), NTN, 0, s>>>(a);
+    });
+    with_rows(nb, [&](auto rows) {
+        constexpr int RW = decltype(rows)::value;
+        ac2_adj2_kernel<RW><<<nb * (TZ / RW), NTH, 0, s>>>(b);
     });
 }
 
-void launch_ac2_fwd_pair(const Ac2FwdArgs &a, const Ac2Fwd2Args &b, hipStream_t s)
-{
-    const int nb = a.ntl * a.nshots + b.ntl * b.nshots;
-    if (nb == 0) return;
-    const size_t lds = node_lds(a, TZ);
-    if (a.seis) { ac2_fwd_pair_kernel<false, true><<<nb, NTN, lds, s>>>(a, b); return; }
-    if (a.snap) ac2_fwd_pair_kernel<true, false><<<nb, NTN, lds, s>>>(a, b);
-    else ac2_fwd_pair_kernel<false, false><<<nb, NTN, lds, s>>>(a, b);
-}
-
-template <int RW, bool SNAP, bool REC>
-void launch_fwd_as(const Ac2FwdArgs &a, bool near, hipStream_t s)
-{
-    const int nb = a.ntl * a.nshots * (TZ / RW);
-    const size_t lds = node_lds(a, RW);
-    if (near) ac2_near_kernel<RW, SNAP, REC><<<nb, NTN, lds, s>>>(a);
-    else      ac2_fwd_kernel<RW, SNAP, REC><<<nb, NTH, lds, s>>>(a);
-}
-
-void launch_ac2_fwd(const Ac2FwdArgs &a, bool near, hipStream_t s)
-{
-    const bool snap = a.snap != nullptr, rec = a.seis != nullptr;
-    with_rows(a.ntl * a.nshots, [&](auto R) {
-        constexpr int RW = decltype(R)::value;
-        if (snap) { if (rec) launch_fwd_as<RW, true, true>(a, near, s); else launch_fwd_as<RW, true, false>(a, near, s); }
-        else      { if (rec) launch_fwd_as<RW, false, true>(a, near, s); else launch_fwd_as<RW, false, false>(a, near, s); }
-    });
-}
-
-void launch_ac2_adj(const Ac2AdjArgs &a, bool near, hipStream_t s)
-{
-    const int nt = a.ntl * a.nshots;
-    with_rows(nt, [&](auto R) {
-        constexpr int RW = decltype(R)::value;
-        const int nb = nt * (TZ / RW);
-        if (near) ac2_adj_near_kernel<RW><<<nb, NTN, 0, s>>>(a);
-        else      ac2_adj_kernel<RW><<<nb, NTH, 0, s>>>(a);
-    });
-}
-
-// ---------------------------------------------------------------- model prep
-// chat = dt^2 c^2 / dx^2 and the padded velocity on the frame (edge
-// replication of the physical model; zero outside the padded grid).
 __global__ void ac2_prep_kernel(Grid2 g, int nmodels, const float *vp, double dt, double dx,
                                 float *chat, float *cpad)
 {

@@ -273,7 +273,7 @@ struct sg_model {
     int n_near3 = 0;
     std::vector<int> h_tiles3;
     int steps_per_launch = 2;
-    bool pair = true;             // 2-D: near step k and blocked steps k, k+1 in one launch
+    bool pair = true;             // 2-D: the tile lists of a step in one launch where that is faster
     // snapshots of the last n_store checkpoint segments, written by a
     // checkpointed forward into the workspace beyond its minimum size
     float *store = nullptr;
@@ -921,13 +921,14 @@ inline float *ac2_aux(float *const *f, int t, int j)
     return f[((t & 1) ? 6 : 2) + j];
 }
 
-// The tile lists of a step: the one-step tiles within 4 cells of the layer
-// (pass A folded in), the other one-step tiles, the blocked tiles.
-enum TileSet { TS_LAYER, TS_OTHER, TS_BLOCKED };
+// The tile lists of a step: the tiles within 4 cells of the layer (pass A
+// folded in), the other one-step tiles, those and the blocked tiles (a step
+// that is not blocked; the lists lie one after the other).
+enum TileSet { TS_LAYER, TS_OTHER, TS_REST };
 inline const int *tile_set(const sg_model *m, TileSet t, int &n)
 {
-    n = t == TS_LAYER ? m->n_layer_near : t == TS_OTHER ? m->n_near - m->n_layer_near : m->n_blk;
-    return t == TS_LAYER ? m->tiles_near : t == TS_OTHER ? m->tiles_near + m->n_layer_near : m->tiles_blk;
+    n = t == TS_LAYER ? m->n_layer_near : m->n_near - m->n_layer_near + (t == TS_REST ? m->n_blk : 0);
+    return m->tiles_near + (t == TS_LAYER ? 0 : m->n_layer_near);
 }
 
 // One forward step k on a tile set.
@@ -963,23 +964,21 @@ Ac2FwdArgs ac2_args(const sg_model *m, int ns, const float *wav, int k, TileSet 
     return a;
 }
 
-void ac2_tiles(const sg_model *m, int ns, const float *wav, int k, TileSet ts, float *seis, float *snap,
-               hipStream_t s)
-{
-    launch_ac2_fwd(ac2_args(m, ns, wav, k, ts, seis, snap), ts == TS_LAYER, s);
-}
-
-// Forward step k, or steps k and k+1 when `two`: the one-step list step by
-// step, blocked tiles both steps in one launch (between the two one-step
-// launches, whose second step reads the blocked tiles' u^{k+1} in its halo).
+// Forward step k, or steps k and k+1 when `two`: the one-step lists step by
+// step, blocked tiles both steps with the first (the second step reads the
+// blocked tiles' u^{k+1} in its halo).
 void ac2_forward(const sg_model *m, int ns, const float *wav, int k, bool two, float *seis, float *snap0,
                  float *snap1, hipStream_t s)
 {
+    Ac2Fwd2Args b{};
+    auto step = [&](int kk, TileSet others, float *snap) {
+        launch_ac2_step(ac2_args(m, ns, wav, kk, TS_LAYER, seis, snap), ac2_args(m, ns, wav, kk, others, seis, snap),
+                        b, m->pair, s);
+    };
     if (!two) {
-        for (TileSet ts : {TS_LAYER, TS_OTHER, TS_BLOCKED}) ac2_tiles(m, ns, wav, k, ts, seis, snap0, s);
+        step(k, TS_REST, snap0);
         return;
     }
-    Ac2Fwd2Args b{};
     b.g = m->L.g2;
     b.nshots = ns;
     b.tiles = m->tiles_blk;
@@ -997,20 +996,9 @@ void ac2_forward(const sg_model *m, int ns, const float *wav, int k, bool two, f
     b.src_scale = src_scale(m);
     b.snap0 = snap0;
     b.snap1 = snap1;
-    int n_other = 0;
-    (void)tile_set(m, TS_OTHER, n_other);
-    if (m->pair && n_other == 0 && (!seis || m->geom_nrec == 0)) {
-        // the near tiles' step k and the blocked tiles' double step in one
-        // grid (sweeps that record seismograms keep them apart: paired, the
-        // C2 forward ran 2 % slower while the recompute gained 4 %)
-        launch_ac2_fwd_pair(ac2_args(m, ns, wav, k, TS_LAYER, seis, snap0), b, s);
-    } else {
-        ac2_tiles(m, ns, wav, k, TS_LAYER, seis, snap0, s);
-        ac2_tiles(m, ns, wav, k, TS_OTHER, seis, snap0, s);
-        launch_ac2_fwd2(b, s);
-    }
-    ac2_tiles(m, ns, wav, k + 1, TS_LAYER, seis, snap1, s);
-    ac2_tiles(m, ns, wav, k + 1, TS_OTHER, seis, snap1, s);
+    step(k, TS_OTHER, snap0);
+    b.ntl = 0;
+    step(k + 1, TS_OTHER, snap1);
 }
 
 // One forward step of the 3-D acoustic or 2-D elastic recursion.
@@ -1063,8 +1051,8 @@ void fwd_step(const sg_model *m, int ns, const float *wav, int cu, int k, float 
 }
 
 // One adjoint step k (s^{k+1} from s^{k+2}, s^{k+3}) on a tile set.
-void ac2_adj_tiles(const sg_model *m, int ns, int k, TileSet ts, const float *dJdd, float *gwav,
-                   const float *snap, hipStream_t s)
+Ac2AdjArgs ac2_adj_args(const sg_model *m, int ns, int k, TileSet ts, const float *dJdd, float *gwav,
+                        const float *snap)
 {
     Ac2AdjArgs b{};
     b.g = m->L.g2;
@@ -1089,29 +1077,27 @@ void ac2_adj_tiles(const sg_model *m, int ns, int k, TileSet ts, const float *dJ
     b.rec_ent = static_cast<const int *>(m->rec_ent);
     b.dJdd = dJdd;
     b.nrec = m->geom_nrec;
+    b.nsrc = m->geom_nsrc;
+    b.src_off = m->src_off;
+    b.src_ent = m->src_ent;
     b.snap = snap;
     b.grad = m->grad;
-    launch_ac2_adj(b, ts == TS_LAYER, s);
+    return b;
 }
 
 // Adjoint step k, or steps k and k-1 when `two` (snap1 = w~^k, snap0 = w~^{k-1}).
 void ac2_adjoint(const sg_model *m, int ns, int k, bool two, const float *dJdd, float *gwav, const float *snap1,
                  const float *snap0, hipStream_t s)
 {
-    const bool nodes = gwav && m->geom_nsrc > 1;
-    auto gather = [&](int kk) {
-        launch_ac2_src_gather(ns, m->geom_nsrc, m->L.plane, m->node_f, m->s4[(kk + 1) & 3], gwav, m->d.nt, kk,
-                              src_scale(m), s);
+    Ac2Adj2Args b{};
+    auto step = [&](int kk, TileSet others, const float *snap) {
+        launch_ac2_adj_step(ac2_adj_args(m, ns, kk, TS_LAYER, dJdd, gwav, snap),
+                            ac2_adj_args(m, ns, kk, others, dJdd, gwav, snap), b, m->pair, s);
     };
     if (!two) {
-        for (TileSet ts : {TS_LAYER, TS_OTHER, TS_BLOCKED}) ac2_adj_tiles(m, ns, k, ts, dJdd, gwav, snap1, s);
-        if (nodes) gather(k);
+        step(k, TS_REST, snap1);
         return;
     }
-    ac2_adj_tiles(m, ns, k, TS_LAYER, dJdd, gwav, snap1, s);
-    ac2_adj_tiles(m, ns, k, TS_OTHER, dJdd, gwav, snap1, s);
-    if (nodes) gather(k);
-    Ac2Adj2Args b{};
     b.g = m->L.g2;
     b.nshots = ns;
     b.tiles = m->tiles_blk;
@@ -1130,10 +1116,9 @@ void ac2_adjoint(const sg_model *m, int ns, int k, bool two, const float *dJdd, 
     b.snap1 = snap1;
     b.snap0 = snap0;
     b.grad = m->grad;
-    launch_ac2_adj2(b, s);
-    ac2_adj_tiles(m, ns, k - 1, TS_LAYER, dJdd, gwav, snap0, s);
-    ac2_adj_tiles(m, ns, k - 1, TS_OTHER, dJdd, gwav, snap0, s);
-    if (nodes) gather(k - 1);
+    step(k, TS_OTHER, snap1);
+    b.ntl = 0;
+    step(k - 1, TS_OTHER, snap0);
 }
 
 // One adjoint step k of the 3-D acoustic or 2-D elastic recursion:

@@ -79,9 +79,11 @@ struct Ac2AdjArgs {
     float *cx, *cz;         // c^{k+1} out (near tiles: their own layer cells; a different buffer)
     const float *hx, *hz, *px, *pz, *ihx, *ihz;
     const long long *src_f;
-    float *gwav;            // [shot][nt] or null
+    float *gwav;            // [shot][nsrc][nt] or null
     int nt, k;
     float src_scale;
+    int nsrc;               // > 1: source nodes by tile, as in the forward step
+    const int *src_off, *src_ent;
     const int *rec_off;
     const int *rec_ent;
     const float *dJdd;      // [shot][nt][nrec]
@@ -136,13 +138,11 @@ constexpr int BLK_HALO = 8;
 // Adjoint of several source nodes: gw[shot][j][k] = scale * s^{k+1}[node j].
 void launch_ac2_src_gather(int nshots, int nsrc, long long plane, const long long *node_f, const float *s1,
                            float *gw, int nt, int k, float scale, hipStream_t s);
-void launch_ac2_fwd2(const Ac2Fwd2Args &a, hipStream_t s);
-void launch_ac2_adj2(const Ac2Adj2Args &a, hipStream_t s);
-// near: the one-step list (pass A folded into its near tiles); else tiles away from the layer
-void launch_ac2_fwd(const Ac2FwdArgs &a, bool near, hipStream_t s);
-// the near tiles' step k (a) and the blocked tiles' steps k, k+1 (b) in one launch
-void launch_ac2_fwd_pair(const Ac2FwdArgs &a, const Ac2Fwd2Args &b, hipStream_t s);
-void launch_ac2_adj(const Ac2AdjArgs &a, bool near, hipStream_t s);
+// What one forward step launches: step k of the tiles by the layer (a) and of
+// the other one-step tiles (o), steps k, k+1 of the blocked tiles (b), in one
+// grid or a grid each (pair = false: always apart).  Any list may be empty.
+void launch_ac2_step(const Ac2FwdArgs &a, const Ac2FwdArgs &o, const Ac2Fwd2Args &b, bool pair, hipStream_t s);
+void launch_ac2_adj_step(const Ac2AdjArgs &a, const Ac2AdjArgs &o, const Ac2Adj2Args &b, bool pair, hipStream_t s);
 void launch_ac2_prep(const Grid2 &g, int nmodels, const float *vp, double dt, double dx,
                      float *chat, float *cpad, hipStream_t s);
 void launch_ac2_finalize(const Grid2 &g, int nmodels, int shots_per_model, const float *grad,
