@@ -44,17 +44,29 @@
 namespace sg {
 namespace {
 
-// A workgroup takes 16 rows of a 64 x 32 tile, 512 threads of 2 rows each,
-// at 8 waves per SIMD, or 8 rows in launches of fewer than FILL_AD2 tiles.
-// Whole tiles (4 rows per thread) leave no registers to load the layer
-// memories and snapshots before the first barrier, and a wavefront's longer
-// instruction stream bounds a launch of few tiles.  Forward + recompute +
-// adjoint, us per step, 32 / 16 / 8 rows: 36 tiles 34.1 / - / 21.7; 108 tiles
-// 39.1 / 25.1 / 26.2; 144 tiles 38.3 / 27.0 / 28.9; 864 tiles 80 / 71 / 95;
-// 19584 tiles (1000 x 500 + 32-cell layer, 64 shots) 1126 / 1103 / -.  A
-// thread's rows are uniform over its wavefront (TX lanes); taken through
+// A workgroup takes 16 rows of a 64 x 32 tile, 512 threads of 2 rows each, or
+// 8 rows in launches of few tiles; whole tiles (4 rows per thread) leave no
+// registers to load the layer memories and snapshots before the first
+// barrier.  A launch of few tiles is bound by the workgroups that one CU takes
+// in turn: 8 rows where 16 would not fill the CUs, and where 16 would give a
+// second workgroup to few of them (129 to 192 tiles: 3 of 8 rows per CU
+// instead of 2 of 16).  Forward + recompute + adjoint, us per step, 16 / 8
+// rows: 36 tiles 18.0 / 15.9; 72 tiles 18.4 / 17.4; 96 tiles 18.7 / 19.3; 128
+// tiles 18.7 / 19.6; 144 tiles 23.3 / 22.7; 180 tiles 24.2 / 24.0; 216 tiles
+// 25.0 / 28.0; 360 tiles 33.7 / 38.4; 32 rows: 108 tiles 39.1, 144 tiles 38.3.
+//
+// EARLY launches, of at most EARLY_AD2 16-row workgroups (two per CU) and those
+// of 8 rows, have every load in flight before the first barrier, in registers
+// that leave half the wavefronts; the others load chat beside the thread's
+// nodes and the layer's tables at their use, and the adjoint steps through the
+// nodes by the layer (a load behind the previous node's stores: 3 us of an
+// 11 us launch).  300 x 150 + 20-cell layer, late -> early: 1 shot 20.7 -> 16.0 us
+// per step, 4 shots 27.0 -> 22.7; 9 shots, 648 workgroups, 33.0 -> 34.2.
+// 1000 x 500 + 32-cell layer, 64 shots (late): 1066.
+//
+// A thread's rows are uniform over its wavefront (TX lanes); taken through
 // readfirstlane, they put the z tables in scalar registers.
-constexpr int FILL_AD2 = 96;
+constexpr int FILL_AD2 = 96, EARLY_AD2 = 512;
 constexpr int NTA = 512;
 static_assert(8 * TX % NTA == 0 && NTA % TX == 0, "whole rows per thread");
 constexpr int AH = 3;              // halo of the composite stencil Dm' khat Dp'
@@ -157,6 +169,74 @@ __device__ __forceinline__ void gather_entries(float *acc, const int *ent, const
     __syncthreads();
 }
 
+// chat beside a thread's nodes (right of the last lane's, beside the extra
+// column's half node) and the layer's tables at its half nodes and nodes.
+// EARLY: loaded with the other operands before the first barrier, so that no
+// load of the launch waits behind one; else, in fewer registers, at their use.
+template <int RW, bool EARLY, bool NEAR>
+struct Coefs {
+    static constexpr int RPA = RW * TX / NTA, NZH = NEAR && EARLY ? RPA + 3 : 1, NZN = NEAR && EARLY ? RPA : 1;
+    float cr[RPA], ce0, ce1, bx, ax, ebx, eax, b0, a0, bz[NZH], az[NZH], b0zr[NZN], a0zr[NZN];
+
+    __device__ __forceinline__ void right(const Grid2 &g, const float *ch, int j, int iz, int ix, int lx)
+    {
+        cr[j] = 0.f;
+        if (lx == TX - 1) cr[j] = ch[fr(g, iz, ix + 1)];
+    }
+    __device__ __forceinline__ void own_x(const Grid2 &g, const Ad2Cpml &t, int ix)
+    {
+        bx = ax = 0.f;
+        if constexpr (NEAR) {
+            const int i = min(ix, g.NX - 1);
+            bx = t.bhx[i];
+            ax = t.ahx[i];
+        }
+    }
+    __device__ __forceinline__ void extra(const Grid2 &g, const Ad2Cpml &t, const float *ch, int x0, int z0, int er,
+                                          int eh)
+    {
+        const long long f = fr(g, z0 + er, x0 - 2 + eh);
+        ce0 = ch[f];
+        ce1 = ch[f + 1];
+        ebx = eax = 0.f;
+        if constexpr (NEAR) {
+            const int i = min(max(x0 - 2 + eh, 0), g.NX - 1);
+            ebx = t.bhx[i];
+            eax = t.ahx[i];
+        }
+    }
+    __device__ __forceinline__ void load(const Grid2 &g, const Ad2Cpml &t, const float *ch, const Rows &o, int tid,
+                                         int er, int eh)
+    {
+        const int lx = tid % TX, r0 = __builtin_amdgcn_readfirstlane(tid / TX) * RPA, ix = o.x0 + lx;
+#pragma unroll
+        for (int j = 0; j < RPA; ++j) right(g, ch, j, o.z0 + r0 + j, ix, lx);
+        if (tid < 3 * RW) extra(g, t, ch, o.x0, o.z0, er, eh);
+        own_x(g, t, ix);
+        if constexpr (NEAR) {
+            b0 = t.b0x[min(ix, g.NX - 1)];
+            a0 = t.a0x[min(ix, g.NX - 1)];
+#pragma unroll
+            for (int m = 0; m < RPA + 3; ++m) {
+                const int i = min(max(o.z0 + r0 - 2 + m, 0), g.NZ - 1);
+                bz[m] = t.bhz[i];
+                az[m] = t.ahz[i];
+                if (m >= 2 && m < RPA + 2) {
+                    b0zr[m - 2] = t.b0z[i];
+                    a0zr[m - 2] = t.a0z[i];
+                }
+            }
+        }
+    }
+    // of the half row m (iz) of this thread, of its node row j (iz), of its node column
+    __device__ __forceinline__ float bhz(const Ad2Cpml &t, int m, int iz) const { return EARLY ? bz[EARLY ? m : 0] : t.bhz[iz]; }
+    __device__ __forceinline__ float ahz(const Ad2Cpml &t, int m, int iz) const { return EARLY ? az[EARLY ? m : 0] : t.ahz[iz]; }
+    __device__ __forceinline__ float b0z(const Ad2Cpml &t, int j, int iz) const { return EARLY ? b0zr[EARLY ? j : 0] : t.b0z[iz]; }
+    __device__ __forceinline__ float a0z(const Ad2Cpml &t, int j, int iz) const { return EARLY ? a0zr[EARLY ? j : 0] : t.a0z[iz]; }
+    __device__ __forceinline__ float b0x(const Ad2Cpml &t, int ix) const { return EARLY ? b0 : t.b0x[ix]; }
+    __device__ __forceinline__ float a0x(const Ad2Cpml &t, int ix) const { return EARLY ? a0 : t.a0x[ix]; }
+};
+
 // ------------------------------------------------------------------ forward
 // Work split of a tile: thread (lx, ly) owns column x0 + lx and rows
 // r0 = ly*RPA .. r0+RPA-1.  The z fluxes of its column (its own half rows and
@@ -169,7 +249,7 @@ __device__ __forceinline__ void gather_entries(float *acc, const int *ent, const
 // psi: psi'x^k there.
 template <bool NEAR, bool SNAP>
 __device__ __forceinline__ float fwd_xflux(const Ad2FwdArgs &a, const float *su, long long so, int x0, int z0, int r,
-                                           int h, float c0, float c1, float psi)
+                                           int h, float c0, float c1, float psi, float bh, float ah)
 {
     const Grid2 &g = a.g;
     const int iz = z0 + r, ix = x0 - 2 + h;
@@ -181,7 +261,7 @@ __device__ __forceinline__ float fwd_xflux(const Ad2FwdArgs &a, const float *su,
         const bool own = h >= 2 && h < TX + 2 && iz < g.NZ;
         float S = G;
         if constexpr (NEAR) {
-            const float p = fmaf(a.t.bhx[ix], psi, a.t.ahx[ix] * G);
+            const float p = fmaf(bh, psi, ah * G);
             S = G + p;
             if (own) a.psxn[so + f] = p;
         }
@@ -193,7 +273,7 @@ __device__ __forceinline__ float fwd_xflux(const Ad2FwdArgs &a, const float *su,
     return q;
 }
 
-template <int RW, bool NEAR, bool SNAP, bool REC>
+template <int RW, bool EARLY, bool NEAR, bool SNAP, bool REC>
 __device__ __forceinline__ void fwd_tile(const Ad2FwdArgs &a, float *su, float *qx, const Rows &o)
 {
     constexpr int RPA = RW * TX / NTA;
@@ -236,6 +316,8 @@ __device__ __forceinline__ void fwd_tile(const Ad2FwdArgs &a, float *su, float *
     // the own half nodes and of this thread's extra column, xi' of the own rows
     float pz0[RPA + 3], px0[RPA], pxe = 0.f, xx0[RPA], xz0[RPA];
     const int er = tid / 3, ee = tid - 3 * er, eh = ee == 2 ? TX + 2 : ee;   // extra column: row, half node
+    Coefs<RW, EARLY, NEAR> co;
+    if constexpr (EARLY) co.load(g, a.t, ch, o, tid, er, eh);
     if constexpr (NEAR) {
 #pragma unroll
         for (int m = 0; m < RPA + 3; ++m) pz0[m] = a.psz[so + fr(g, z0 + r0 - 2 + m, ix)];
@@ -269,7 +351,7 @@ __device__ __forceinline__ void fwd_tile(const Ad2FwdArgs &a, float *su, float *
                 const bool own = m >= 2 && m < RPA + 2 && ix < g.NX;
                 float S = G;
                 if constexpr (NEAR) {
-                    const float p = fmaf(a.t.bhz[iz], pz0[m], a.t.ahz[iz] * G);
+                    const float p = fmaf(co.bhz(a.t, m, iz), pz0[m], co.ahz(a.t, m, iz) * G);
                     S = G + p;
                     if (own) a.pszn[so + f] = p;
                 }
@@ -290,12 +372,15 @@ __device__ __forceinline__ void fwd_tile(const Ad2FwdArgs &a, float *su, float *
     for (int j = 0; j < RPA; ++j) {
         const float c0 = cz[j + 2];
         float c1 = __shfl_down(c0, 1, TX);
-        if (lx == TX - 1) c1 = ch[fr(g, z0 + r0 + j, ix + 1)];
-        qx[(r0 + j) * QXW + lx + 2] = fwd_xflux<NEAR, SNAP>(a, su, so, x0, z0, r0 + j, lx + 2, c0, c1, px0[j]);
+        if constexpr (!EARLY) co.right(g, ch, j, z0 + r0 + j, ix, lx);
+        if (lx == TX - 1) c1 = co.cr[j];
+        if constexpr (!EARLY) co.own_x(g, a.t, ix);
+        qx[(r0 + j) * QXW + lx + 2] = fwd_xflux<NEAR, SNAP>(a, su, so, x0, z0, r0 + j, lx + 2, c0, c1, px0[j], co.bx,
+                                                            co.ax);
     }
     if (tid < 3 * RW) {
-        const long long f = fr(g, z0 + er, x0 - 2 + eh);
-        qx[er * QXW + eh] = fwd_xflux<NEAR, SNAP>(a, su, so, x0, z0, er, eh, ch[f], ch[f + 1], pxe);
+        if constexpr (!EARLY) co.extra(g, a.t, ch, x0, z0, er, eh);
+        qx[er * QXW + eh] = fwd_xflux<NEAR, SNAP>(a, su, so, x0, z0, er, eh, co.ce0, co.ce1, pxe, co.ebx, co.eax);
     }
     __syncthreads();                      // qx complete; su no longer read
 
@@ -314,8 +399,8 @@ __device__ __forceinline__ void fwd_tile(const Ad2FwdArgs &a, float *su, float *
             const long long f = fr(g, iz, ix);
             float inc = Hx + hz[j];
             if constexpr (NEAR) {
-                const float xx = fmaf(a.t.b0x[ix], xx0[j], a.t.a0x[ix] * Hx);
-                const float xz = fmaf(a.t.b0z[iz], xz0[j], a.t.a0z[iz] * hz[j]);
+                const float xx = fmaf(co.b0x(a.t, ix), xx0[j], co.a0x(a.t, ix) * Hx);
+                const float xz = fmaf(co.b0z(a.t, j, iz), xz0[j], co.a0z(a.t, j, iz) * hz[j]);
                 __builtin_nontemporal_store(xx, a.xix + so + f);
                 __builtin_nontemporal_store(xz, a.xiz + so + f);
                 inc += xx + xz;
@@ -343,15 +428,16 @@ __device__ __forceinline__ void fwd_tile(const Ad2FwdArgs &a, float *su, float *
     }
 }
 
-template <int RW, bool SNAP, bool REC>
-__global__ __launch_bounds__(NTA) __attribute__((amdgpu_waves_per_eu(8))) void ad2_fwd_kernel(Ad2FwdArgs a)
+template <int RW, bool EARLY, bool SNAP, bool REC>
+__global__ __launch_bounds__(NTA) __attribute__((amdgpu_waves_per_eu(EARLY ? 4 : 8)))
+void ad2_fwd_kernel(Ad2FwdArgs a)
 {
     __shared__ float su[nodes(RW)];
     __shared__ float qx[RW * QXW];
     const Rows o = rows_of<RW>(a.g, a.nshots);
     if (o.z0 >= a.g.NZ) return;
-    if (near_edge<RW>(a.g, o.x0, o.z0)) fwd_tile<RW, true, SNAP, REC>(a, su, qx, o);
-    else                                fwd_tile<RW, false, SNAP, REC>(a, su, qx, o);
+    if (near_edge<RW>(a.g, o.x0, o.z0)) fwd_tile<RW, EARLY, true, SNAP, REC>(a, su, qx, o);
+    else                                fwd_tile<RW, EARLY, false, SNAP, REC>(a, su, qx, o);
 }
 
 // ------------------------------------------------------------------ adjoint
@@ -364,7 +450,8 @@ __global__ __launch_bounds__(NTA) __attribute__((amdgpu_waves_per_eu(8))) void a
 // z0v: Z_x^{k+2} there; sn: S'x there.
 template <bool NEAR, bool GRAD>
 __device__ __forceinline__ float adj_xflux(const Ad2AdjArgs &a, const float *hx, long long so, int x0, int z0, int r,
-                                           int h, float c0, float c1, bool want_p, float &p, float z0v, float sn)
+                                           int h, float c0, float c1, bool want_p, float &p, float z0v, float sn,
+                                           float ah, float bh)
 {
     const Grid2 &g = a.g;
     const int iz = z0 + r, ix = x0 - 2 + h;
@@ -378,7 +465,7 @@ __device__ __forceinline__ float adj_xflux(const Ad2AdjArgs &a, const float *hx,
         const float Sb = 0.5f * (c0 + c1) * qb;
         Gb = Sb;
         if constexpr (NEAR) {
-            const float z = fmaf(a.t.ahx[ix], Sb, a.t.bhx[ix] * z0v);
+            const float z = fmaf(ah, Sb, bh * z0v);
             Gb = Sb + z;
             if (own) a.zxn[so + f] = z;
         }
@@ -389,7 +476,7 @@ __device__ __forceinline__ float adj_xflux(const Ad2AdjArgs &a, const float *hx,
     return Gb;
 }
 
-template <int RW, bool NEAR, bool GRAD>
+template <int RW, bool EARLY, bool NEAR, bool GRAD>
 __device__ __forceinline__ void adj_tile(const Ad2AdjArgs &a, float *hx, float *hz, float *qx, float *pl,
                                          const Rows &o)
 {
@@ -418,25 +505,55 @@ __device__ __forceinline__ void adj_tile(const Ad2AdjArgs &a, float *hx, float *
             }
         }
     }
-    for (int i = tid; NEAR && i < nodes(RW); i += NTA) {
-        const int r = i / AW, c = i - r * AW;
-        const int iz = z0 - AH + r, jx = x0 - AH + c;
-        const long long f = fr(g, iz, jx);
-        const float l = l1[f];
-        if constexpr (NEAR) {
-            float bx = l, bz = l;
-            if (iz >= 0 && iz < g.NZ && jx >= 0 && jx < g.NX) {
-                const float yx = fmaf(a.t.a0x[jx], l, a.t.b0x[jx] * a.yx[so + f]);
-                const float yz = fmaf(a.t.a0z[iz], l, a.t.b0z[iz] * a.yz[so + f]);
-                if (r >= AH && r < AH + RW && c >= AH && c < AH + TX) {
-                    a.yxn[so + f] = yx;
-                    a.yzn[so + f] = yz;
-                }
-                bx = l + yx;
-                bz = l + yz;
+    // near the layer: y of one node from its operands, stored if it is its tile's
+    auto stage = [&](int i, float l, float yx0, float yz0, float ax, float bx, float az, float bz) {
+        const int r = i / AW, c = i - r * AW, iz = z0 - AH + r, jx = x0 - AH + c;
+        float vx = l, vz = l;
+        if (iz >= 0 && iz < g.NZ && jx >= 0 && jx < g.NX) {
+            const float yx = fmaf(ax, l, bx * yx0);
+            const float yz = fmaf(az, l, bz * yz0);
+            if (r >= AH && r < AH + RW && c >= AH && c < AH + TX) {
+                const long long f = fr(g, iz, jx);
+                a.yxn[so + f] = yx;
+                a.yzn[so + f] = yz;
             }
-            hx[i] = bx;
-            hz[i] = bz;
+            vx = l + yx;
+            vz = l + yz;
+        }
+        hx[i] = vx;
+        hz[i] = vz;
+    };
+    auto node = [&](int i, long long &f, int &tz, int &tx) {       // its place and table rows
+        const int r = i / AW, c = i - r * AW, iz = z0 - AH + r, jx = x0 - AH + c;
+        f = fr(g, iz, jx);
+        tz = min(max(iz, 0), g.NZ - 1);
+        tx = min(max(jx, 0), g.NX - 1);
+    };
+    constexpr int KN = NEAR && EARLY ? (nodes(RW) + NTA - 1) / NTA : 1;
+    float ln[KN], yx0[KN], yz0[KN], ax[KN], bx[KN], az[KN], bz[KN];
+    float lc[RPA];                        // lambda^{k+1} of the own rows
+    if constexpr (NEAR && EARLY) {
+#pragma unroll
+        for (int k = 0; k < KN; ++k) {
+            long long f;
+            int tz, tx;
+            node(min(tid + k * NTA, nodes(RW) - 1), f, tz, tx);
+            ln[k] = l1[f];
+            yx0[k] = a.yx[so + f];
+            yz0[k] = a.yz[so + f];
+            ax[k] = a.t.a0x[tx];
+            bx[k] = a.t.b0x[tx];
+            az[k] = a.t.a0z[tz];
+            bz[k] = a.t.b0z[tz];
+        }
+#pragma unroll
+        for (int j = 0; j < RPA; ++j) lc[j] = l1[fr(g, z0 + r0 + j, ix)];
+    } else if constexpr (NEAR) {
+        for (int i = tid; i < nodes(RW); i += NTA) {
+            long long f;
+            int tz, tx;
+            node(i, f, tz, tx);
+            stage(i, l1[f], a.yx[so + f], a.yz[so + f], a.t.a0x[tx], a.t.b0x[tx], a.t.a0z[tz], a.t.b0z[tz]);
         }
     }
     float cz[RPA + 4];
@@ -478,12 +595,19 @@ __device__ __forceinline__ void adj_tile(const Ad2AdjArgs &a, float *hx, float *
         if constexpr (NEAR) zxe = a.zx[f];
         if constexpr (GRAD) sxe = a.snx[f];
     }
+    Coefs<RW, EARLY, NEAR> co;
+    if constexpr (EARLY) co.load(g, a.t, ch, o, tid, er, eh);
     if (a.k >= 1) rec.first(sample);
+    if constexpr (NEAR && EARLY) {
+#pragma unroll
+        for (int k = 0; k < KN; ++k)
+            if (tid + k * NTA < nodes(RW)) stage(tid + k * NTA, ln[k], yx0[k], yz0[k], ax[k], bx[k], az[k], bz[k]);
+    }
     if constexpr (!NEAR) __builtin_amdgcn_s_waitcnt(0);   // the tile's direct loads have landed in LDS
     __syncthreads();
     const float *hzz = NEAR ? hz : hx;
 
-    float lam[RPA], dz[RPA], gnz[RPA];   // lambda^{k+1}, Dm' Gb_z and the z gradient of the own rows
+    float dz[RPA], gnz[RPA];              // Dm' Gb_z and the z gradient of the own rows
     {
         float hc[RPA + 6];
 #pragma unroll
@@ -501,7 +625,7 @@ __device__ __forceinline__ void adj_tile(const Ad2AdjArgs &a, float *hx, float *
                 const float Sb = 0.5f * (cz[m] + cz[m + 1]) * qb;
                 Gb = Sb;
                 if constexpr (NEAR) {
-                    const float z = fmaf(a.t.ahz[iz], Sb, a.t.bhz[iz] * zz0[m]);
+                    const float z = fmaf(co.ahz(a.t, m, iz), Sb, co.bhz(a.t, m, iz) * zz0[m]);
                     Gb = Sb + z;
                     if (own) a.zzn[so + f] = z;
                 }
@@ -514,7 +638,7 @@ __device__ __forceinline__ void adj_tile(const Ad2AdjArgs &a, float *hx, float *
 #pragma unroll
         for (int j = 0; j < RPA; ++j) {
             const int iz = z0 + r0 + j;
-            lam[j] = NEAR ? 0.f : hc[j + 3];
+            if constexpr (!NEAR) lc[j] = hc[j + 3];
             dz[j] = d4(gz[j], gz[j + 1], gz[j + 2], gz[j + 3]);
             gnz[j] = 0.5f * (pz[j + 1] + pz[j + 2]);
             if (iz == g.NZ - 1) gnz[j] += 0.5f * pz[j + 2];
@@ -525,17 +649,19 @@ __device__ __forceinline__ void adj_tile(const Ad2AdjArgs &a, float *hx, float *
     for (int j = 0; j < RPA; ++j) {
         const float c0 = cz[j + 2];
         float c1 = __shfl_down(c0, 1, TX);
-        if (lx == TX - 1) c1 = ch[fr(g, z0 + r0 + j, ix + 1)];
+        if constexpr (!EARLY) co.right(g, ch, j, z0 + r0 + j, ix, lx);
+        if (lx == TX - 1) c1 = co.cr[j];
+        if constexpr (!EARLY) co.own_x(g, a.t, ix);
         float pj;
         qx[(r0 + j) * QXW + lx + 2] = adj_xflux<NEAR, GRAD>(a, hx, so, x0, z0, r0 + j, lx + 2, c0, c1, true, pj,
-                                                                   zx0[j], sx0[j]);
+                                                                   zx0[j], sx0[j], co.ax, co.bx);
         px[j] = pj;
     }
     if (tid < 3 * RW) {
-        const long long f = fr(g, z0 + er, x0 - 2 + eh);
         float p = 0.f;
-        qx[er * QXW + eh] = adj_xflux<NEAR, GRAD>(a, hx, so, x0, z0, er, eh, ch[f], ch[f + 1], eh == 1, p, zxe,
-                                                         sxe);
+        if constexpr (!EARLY) co.extra(g, a.t, ch, x0, z0, er, eh);
+        qx[er * QXW + eh] = adj_xflux<NEAR, GRAD>(a, hx, so, x0, z0, er, eh, co.ce0, co.ce1, eh == 1, p, zxe, sxe,
+                                                  co.eax, co.ebx);
         if (GRAD && eh == 1) pl[er] = p;  // the half node left of the tile's first column
     }
     __syncthreads();                      // qx, pl complete; hx, hz no longer read
@@ -559,8 +685,8 @@ __device__ __forceinline__ void adj_tile(const Ad2AdjArgs &a, float *hx, float *
         }
         if (iz < g.NZ && ix < g.NX) {
             const long long f = fr(g, iz, ix);
-            const float lc = NEAR ? l1[f] : lam[j];
-            float v = lc + ((lc - l2[j]) - (Dx + dz[j]));
+            if constexpr (NEAR && !EARLY) lc[j] = l1[f];
+            float v = lc[j] + ((lc[j] - l2[j]) - (Dx + dz[j]));
             if (inj) v += hx[r * TX + lx];
             __builtin_nontemporal_store(v, a.l0 + so + f);
             if constexpr (GRAD) __builtin_nontemporal_store(gacc[j] + gn, a.gn + so + f);
@@ -568,8 +694,9 @@ __device__ __forceinline__ void adj_tile(const Ad2AdjArgs &a, float *hx, float *
     }
 }
 
-template <int RW, bool GRAD>
-__global__ __launch_bounds__(NTA) __attribute__((amdgpu_waves_per_eu(8))) void ad2_adj_kernel(Ad2AdjArgs a)
+template <int RW, bool EARLY, bool GRAD>
+__global__ __launch_bounds__(NTA) __attribute__((amdgpu_waves_per_eu(EARLY ? 4 : 8)))
+void ad2_adj_kernel(Ad2AdjArgs a)
 {
     __shared__ float hx[nodes(RW)];
     __shared__ float hz[nodes(RW)];
@@ -577,8 +704,8 @@ __global__ __launch_bounds__(NTA) __attribute__((amdgpu_waves_per_eu(8))) void a
     __shared__ float pl[RW];
     const Rows o = rows_of<RW>(a.g, a.nshots);
     if (o.z0 >= a.g.NZ) return;
-    if (near_edge<RW>(a.g, o.x0, o.z0)) adj_tile<RW, true, GRAD>(a, hx, hz, qx, pl, o);
-    else                                adj_tile<RW, false, GRAD>(a, hx, hz, qx, pl, o);
+    if (near_edge<RW>(a.g, o.x0, o.z0)) adj_tile<RW, EARLY, true, GRAD>(a, hx, hz, qx, pl, o);
+    else                                adj_tile<RW, EARLY, false, GRAD>(a, hx, hz, qx, pl, o);
 }
 
 // ------------------------------------------------------------------ model and gradient
@@ -640,40 +767,43 @@ int blocks_for(long long n) { return (int)std::min<long long>((n + 255) / 256, 6
 
 } // namespace
 
-// f(integral_constant<int, RW>) with the rows per workgroup.
+// f(integral_constant<int, RW>, early?, workgroups) with the rows per
+// workgroup of a launch over `tiles` tiles.
 template <class F>
 static void with_rows(int tiles, F &&f)
 {
+    constexpr std::integral_constant<int, 16> r16{};
+    constexpr std::integral_constant<int, 8> r8{};
     if (tiles <= 0) return;
-    if (tiles >= FILL_AD2) f(std::integral_constant<int, 16>{});
-    else f(std::integral_constant<int, 8>{});
+    const int n16 = tiles * (TZ / 16);
+    if (tiles < FILL_AD2 || (tiles > 128 && tiles <= 192)) f(r8, std::true_type(), tiles * (TZ / 8));
+    else if (n16 <= EARLY_AD2) f(r16, std::true_type(), n16);
+    else f(r16, std::false_type(), n16);
 }
 
 void launch_ad2_fwd(const Ad2FwdArgs &a, hipStream_t s)
 {
     const bool rec = a.seis && a.nrec > 0;
-    const int tiles = a.g.ntx * a.g.ntz * a.nshots;
-    with_rows(tiles, [&](auto R) {
+    with_rows(a.g.ntx * a.g.ntz * a.nshots, [&](auto R, auto early, int n) {
         constexpr int RW = decltype(R)::value;
-        const int n = tiles * (TZ / RW);
+        constexpr bool E = decltype(early)::value;
         if (a.snx) {
-            if (rec) ad2_fwd_kernel<RW, true, true><<<n, NTA, 0, s>>>(a);
-            else     ad2_fwd_kernel<RW, true, false><<<n, NTA, 0, s>>>(a);
+            if (rec) ad2_fwd_kernel<RW, E, true, true><<<n, NTA, 0, s>>>(a);
+            else     ad2_fwd_kernel<RW, E, true, false><<<n, NTA, 0, s>>>(a);
         } else {
-            if (rec) ad2_fwd_kernel<RW, false, true><<<n, NTA, 0, s>>>(a);
-            else     ad2_fwd_kernel<RW, false, false><<<n, NTA, 0, s>>>(a);
+            if (rec) ad2_fwd_kernel<RW, E, false, true><<<n, NTA, 0, s>>>(a);
+            else     ad2_fwd_kernel<RW, E, false, false><<<n, NTA, 0, s>>>(a);
         }
     });
 }
 
 void launch_ad2_adj(const Ad2AdjArgs &a, hipStream_t s)
 {
-    const int tiles = a.g.ntx * a.g.ntz * a.nshots;
-    with_rows(tiles, [&](auto R) {
+    with_rows(a.g.ntx * a.g.ntz * a.nshots, [&](auto R, auto early, int n) {
         constexpr int RW = decltype(R)::value;
-        const int n = tiles * (TZ / RW);
-        if (a.snx) ad2_adj_kernel<RW, true><<<n, NTA, 0, s>>>(a);
-        else       ad2_adj_kernel<RW, false><<<n, NTA, 0, s>>>(a);
+        constexpr bool E = decltype(early)::value;
+        if (a.snx) ad2_adj_kernel<RW, E, true><<<n, NTA, 0, s>>>(a);
+        else       ad2_adj_kernel<RW, E, false><<<n, NTA, 0, s>>>(a);
     });
 }
 
