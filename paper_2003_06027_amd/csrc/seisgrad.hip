@@ -424,6 +424,15 @@ int el_group(const sg_model *m, int spm)
     return m->el_gs > 0 && spm % m->el_gs == 0 ? m->el_gs : el2_group(spm);
 }
 
+// Zeros into fs floats of each of n consecutive fields: one launch if the
+// batch fills them.
+void clear_fields(float *f, int n, long long field, long long fs, hipStream_t s)
+{
+    if (fs == field) launch_fill(f, n * field, 0.f, s);
+    else
+        for (int i = 0; i < n; ++i) launch_fill(f + i * field, fs, 0.f, s);
+}
+
 int upload_geometry(sg_model *m, const sg_shots *sh, hipStream_t s)
 {
     const Layout &L = m->L;
@@ -1526,7 +1535,7 @@ int forward_shots(sg_model *m, const sg_shots *sh, float *seis, int32_t save_ckp
     const long long fs = (long long)ns * L.plane;  // floats of one field over the batch
     const bool ad2 = L.ad2;
     const bool ac2 = !L.elastic && !ad2 && m->d.ndim == 2;
-    for (int i = 0; i < (ad2 || ac2 ? nf + L.nxs : nf); ++i) launch_fill(m->fwd[i], fs, 0.f, s);
+    clear_fields(m->fwd[0], ad2 || ac2 ? nf + L.nxs : nf, L.field, fs, s);
     float *sp = sh->nrec > 0 ? seis : nullptr;
     // segments >= seg0 keep their adjoint snapshots (checkpointed forwards only)
     const int seg0 = save_ckpt ? L.nseg - m->n_store : L.nseg;
@@ -1535,21 +1544,24 @@ int forward_shots(sg_model *m, const sg_shots *sh, float *seis, int32_t save_ckp
         if (seg < seg0) return nullptr;
         return m->store + ((size_t)(seg - seg0) * K + (k - seg * K)) * L.nsnap * L.field;
     };
-    // one checkpoint segment: the checkpoint of its first state, then its steps
+    // one checkpoint segment: the checkpoint of its first state (unless its
+    // snapshots are kept: the adjoint then never restores it), then its steps
     auto issue = [&](int seg, hipStream_t st) -> int {
         const int k0 = seg * K, k1 = std::min(k0 + K, nt);
         int cu = k0 & 1;                  // 3-D / elastic: u^k in fwd[cu]
-        if (save_ckpt) {
+        if (save_ckpt && seg < seg0) {
             // state at the start of step k0: u^k, u^{k-1}, then the layer fields
             // (acoustic: u^k, u^{k-1} first; elastic: the fields in order)
             float *ck = m->ckpt + (size_t)seg * nf * L.field;
+            CopyFields c{};
             for (int i = 0; i < nf; ++i) {
                 const float *src = ad2 ? ad2_state(m, k0, i)
                                  : ac2 ? (i < 2 ? m->u4[(k0 + 4 - i) & 3] : ac2_aux(m->fwd, k0 - 1, i - 2))
                                  : L.elastic || i >= 2 ? m->fwd[i]
                                        : (i == 0 ? m->fwd[cu] : m->fwd[1 - cu]);
-                HIPCHECK(hipMemcpyAsync(ck + i * L.field, src, sizeof(float) * fs, hipMemcpyDeviceToDevice, st));
+                c.add(ck + i * L.field, src);
             }
+            launch_copy_fields(c, fs, st);
         }
         for (int k = k0; k < k1;) {
             if (ac2) {
@@ -1614,10 +1626,9 @@ int adjoint_gradient(sg_model *m, const sg_shots *sh, const float *dJ_dd, float 
     const long long fs = (long long)ns * L.plane;
     const bool ad2 = L.ad2;
     const bool ac2 = !L.elastic && !ad2 && m->d.ndim == 2;
-    for (int i = 0; i < (ad2 || ac2 ? nf + L.nxs : nf); ++i) launch_fill(m->adj[i], fs, 0.f, s);
-    for (int q = 0; q < L.ngrad; ++q) launch_fill(m->grad + q * L.field, fs, 0.f, s);
-    if (L.elastic)
-        for (int i = 0; i < 8; ++i) launch_fill(m->tmp[i], fs, 0.f, s);
+    clear_fields(m->adj[0], ad2 || ac2 ? nf + L.nxs : nf, L.field, fs, s);
+    clear_fields(m->grad, L.ngrad, L.field, fs, s);
+    if (L.elastic) clear_fields(m->tmp[0], 8, L.field, fs, s);
     if (ad2) ad2_adj_step(m, ns, nt, dJ_dd, nullptr, nullptr, s);   // lambda^nt
     const int seg0 = m->have_store ? L.nseg - m->n_store : L.nseg;
     const bool blk = ac2 && m->steps_per_launch == 2 && m->n_blk > 0;
@@ -1632,12 +1643,14 @@ int adjoint_gradient(sg_model *m, const sg_shots *sh, const float *dJ_dd, float 
         int span = -1;
         if (!kept) {
             const float *ck = m->ckpt + (size_t)seg * nf * L.field;
+            CopyFields c{};
             for (int i = 0; i < nf; ++i) {
                 float *dst = ad2 ? ad2_state(m, k0, i)
                            : ac2 ? (i < 2 ? m->u4[(k0 + 4 - i) & 3] : ac2_aux(m->fwd, k0 - 1, i - 2))
                                  : m->fwd[i];
-                HIPCHECK(hipMemcpyAsync(dst, ck + i * L.field, sizeof(float) * fs, hipMemcpyDeviceToDevice, st));
+                c.add(dst, ck + i * L.field);
             }
+            launch_copy_fields(c, fs, st);
             int cu = 0;
             if (spans) span = span_begin(m, 1, k1 - k0, st);
             for (int k = k0; k < k1;) {

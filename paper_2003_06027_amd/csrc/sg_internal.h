@@ -149,6 +149,15 @@ void launch_ac2_finalize(const Grid2 &g, int nmodels, int shots_per_model, const
                          float *acc, const float *cpad, double dt, double dx, float *g_vp,
                          hipStream_t s);
 void launch_fill(float *p, long long n, float v, hipStream_t s);
+// n floats (a multiple of 4, 16-byte aligned) of each of `count` fields
+struct CopyFields {
+    static constexpr int MAX = 16;
+    const float *src[MAX];
+    float *dst[MAX];
+    int count;
+    void add(float *d, const float *s) { dst[count] = d; src[count++] = s; }
+};
+void launch_copy_fields(const CopyFields &c, long long n, hipStream_t s);
 // Partial sums of the misfit reduction (a model's workspace slot, or the
 // static array of the allocation-free entry point).
 constexpr int NOALLOC_PARTS = 4096;

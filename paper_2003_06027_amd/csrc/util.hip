@@ -20,6 +20,44 @@ void launch_fill(float *p, long long n, float v, hipStream_t s)
     fill_kernel<<<blocks, 256, 0, s>>>(p, n, v);
 }
 
+// The fields of a state to or from a checkpoint in one launch, U items of 16
+// bytes in flight per thread (a copy per field: 2 us each at 101 x 101 with
+// 20-cell layer, 12 us for six, now 3; 300 x 150 with 4 shots 23 -> 4.6 us; 128^3
+// + 20 79 -> 55).  STREAM: more than the last-level cache holds, past it
+// (400^3 + 24 952 us as copies per field, 1007 cached, 863 streamed; 128^3 + 20
+// 55 cached, 64 streamed).
+template <bool STREAM>
+__global__ __launch_bounds__(256) void copy_fields_kernel(CopyFields c, long long n4)
+{
+    constexpr int U = 4;
+    // pointers out of an array: their address space has to be said
+    typedef float V4 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(1))) V4 *Global;
+    const Global src = (Global)c.src[blockIdx.y], dst = (Global)c.dst[blockIdx.y];
+    const long long i0 = blockIdx.x * (256ll * U) + threadIdx.x;
+    V4 v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const long long i = min(i0 + u * 256, n4 - 1);
+        v[u] = STREAM ? __builtin_nontemporal_load(src + i) : src[i];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (i0 + u * 256 < n4) {
+            if constexpr (STREAM) __builtin_nontemporal_store(v[u], dst + i0 + u * 256);
+            else dst[i0 + u * 256] = v[u];
+        }
+}
+
+void launch_copy_fields(const CopyFields &c, long long n, hipStream_t s)
+{
+    if (n <= 0 || c.count == 0) return;
+    const long long n4 = n / 4;            // whole frame rows: a multiple of 32 floats
+    const dim3 grid((unsigned)((n4 + 1023) / 1024), c.count);
+    if (n4 * 16 * c.count > 256ll << 20) copy_fields_kernel<true><<<grid, 256, 0, s>>>(c, n4);
+    else                                 copy_fields_kernel<false><<<grid, 256, 0, s>>>(c, n4);
+}
+
 // Ricker wavelet r(t) = (1 - 2 a) exp(-a), a = (pi f0 (t - t0))^2, in FP64.
 __global__ void ricker_kernel(double f0, double t0, double dt, int nt, float *out)
 {
