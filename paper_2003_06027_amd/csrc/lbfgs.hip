@@ -49,7 +49,7 @@ __device__ __forceinline__ double get_f64(const float *p)
 
 // s, y of the models that store a pair, and their sums (y.s, y.y).  Elements
 // are loaded NL at a time: with one in flight per thread a model of 10201
-// elements took ten memory latencies.  ONE: one workgroup per model, which
+// elements took ten memory latencies (20 models, 4 at a time 8.0 us, 10 7.8).  ONE: one workgroup per model, which
 // writes the sums.  Otherwise nb workgroups per model leave their two partial
 // sums in the first 4 nb elements of the stored y, which lbfgs_pair_kernel
 // adds up and then replaces by the elements.
@@ -59,7 +59,7 @@ __global__ __launch_bounds__(LB_THREADS) void lbfgs_push_kernel(int nmodels, lon
                                                                 const float *m_old, const float *g_new,
                                                                 const float *g_old, float *S, float *Y, double *ysyy)
 {
-    constexpr int NL = 4;
+    constexpr int NL = ONE ? 10 : 4;
     __shared__ double red[LB_THREADS / 64];
     const int b = blockIdx.x / nb, blk = blockIdx.x - b * nb;
     const int k = slot[b];
@@ -131,17 +131,18 @@ __global__ __launch_bounds__(LB_THREADS) void lbfgs_pair_kernel(int nmodels, lon
 // and p = -(gamma (g - sum alpha_j y_j) + sum (alpha_j - beta_j) s_j).  The
 // vectors are read twice, by every CU, instead of once per loop step by one
 // workgroup whose every step waits for the reduction before it (push +
-// direction, 8 pairs: 20 models of 10201 elements 76 -> 30 us, 200 models 129 ->
+// direction, 8 pairs: 20 models of 10201 elements 76 -> 27 us, 200 models 129 ->
 // 82 us, one model of 500000 4.85 ms -> 45 us).
 // The products are summed per chunk of elements and then over the chunks in
 // order.  The partial sums and then the coefficients live in p, which is
 // written last: the coefficients in its first LB_HEAD floats, whose elements
-// a launch of their own forms.
+// the workgroup forms that reads them last (a count of those that have read
+// them lies behind them; as a launch of its own 3.7 us).
 constexpr int LB_CMAX = 15;      // pairs: the columns (y of each, g) fill one matrix tile, the rows two
 constexpr int LB_SUB = 512;      // chunks are multiples of this many elements
 constexpr int LB_GT = 256;
 constexpr int LB_HEAD = 64;      // floats
-static_assert(2 * (2 * LB_CMAX + 1) <= LB_HEAD, "the coefficients fit the head");
+static_assert(2 * (2 * LB_CMAX + 1) < LB_HEAD, "the coefficients and the count fit the head");
 
 // Products of c pairs, newest first: s_i.g, y_i.g, then for j < i (j newer) s_i.y_j and y_i.y_j.
 __host__ __device__ constexpr int lb_dots(int c) { return c * c + c; }
@@ -300,31 +301,36 @@ __global__ __launch_bounds__(LB_THREADS) void lbfgs_scalars_kernel(int nmodels, 
         const double cj = __shfl(cs, j, 64);
         if (i < j) u += cj * dot[lb_sy(c, j, ic)];
     }
-    if (i == 0) put_f64(pm, -gamma);
+    if (i == 0) {
+        put_f64(pm, -gamma);
+        pm[LB_HEAD - 1] = __uint_as_float(0u);
+    }
     if (i < c) {
         put_f64(pm + 2 + 4 * i, -cs);
         put_f64(pm + 4 + 4 * i, gamma * al);
     }
 }
 
-// p of the elements after the head, or of the head alone (HEAD: one workgroup
-// per model, the coefficients read before any is overwritten).
-template <bool HEAD>
+// p: nb workgroups per model the elements after the head, the last of them to
+// have read the coefficients then the head.  (Which one that is does not
+// change a value.)
 __global__ __launch_bounds__(LB_GT) void lbfgs_combine_kernel(int nmodels, long long n, int mem, int nb,
                                                               const int *hist, const float *S, const float *Y,
                                                               const float *g, float *p)
 {
     __shared__ double co[2 * LB_CMAX + 1];
+    __shared__ unsigned before;
     const int b = blockIdx.x / nb;
     const LbHist h(hist, b, mem);
     const int c = h.count;
     const long long o = (long long)b * n;
     float *pm = p + o;
     if ((int)threadIdx.x < 2 * c + 1) co[threadIdx.x] = get_f64(pm + 2 * threadIdx.x);
-    __syncthreads();
-    const long long last = HEAD ? LB_HEAD : n;
-    for (long long i = (HEAD ? 0 : LB_HEAD) + (blockIdx.x - b * nb) * (long long)LB_GT + threadIdx.x; i < last;
-         i += nb * (long long)LB_GT) {
+    __syncthreads();                      // the coefficients have been read
+    if (threadIdx.x == 0)
+        before = __hip_atomic_fetch_add(reinterpret_cast<unsigned *>(pm + LB_HEAD - 1), 1u, __ATOMIC_RELAXED,
+                                        __HIP_MEMORY_SCOPE_AGENT);
+    auto element = [&](long long i) {
         double t = co[0] * g[o + i];
 #pragma unroll 4
         for (int j = 0; j < c; ++j) {
@@ -333,7 +339,11 @@ __global__ __launch_bounds__(LB_GT) void lbfgs_combine_kernel(int nmodels, long 
             t += co[2 + 2 * j] * Y[k];
         }
         pm[i] = (float)t;
-    }
+    };
+    for (long long i = LB_HEAD + (blockIdx.x - b * nb) * (long long)LB_GT + threadIdx.x; i < n; i += nb * (long long)LB_GT)
+        element(i);
+    __syncthreads();
+    if (before == (unsigned)nb - 1 && threadIdx.x < LB_HEAD) element(threadIdx.x);
 }
 
 // p = -H g for model b over hist[2b] pairs ending at ring slot hist[2b+1];
@@ -439,8 +449,7 @@ int lbfgs_direction(int32_t nmodels, int64_t n, int32_t mem, const int32_t *hist
             lbfgs_products_kernel<2><<<nmodels * nchunks, LB_GT, 0, st>>>(nmodels, n, mem, nchunks, chunk, hist, S, Y, g, p);
         lbfgs_scalars_kernel<<<nmodels, LB_THREADS, 0, st>>>(nmodels, n, mem, nchunks, hist, ysyy, p);
         const int nb = (int)std::min<long long>((n - LB_HEAD + LB_GT - 1) / LB_GT, std::max(1, 16384 / nmodels));
-        lbfgs_combine_kernel<false><<<nmodels * nb, LB_GT, 0, st>>>(nmodels, n, mem, nb, hist, S, Y, g, p);
-        lbfgs_combine_kernel<true><<<nmodels, LB_GT, 0, st>>>(nmodels, n, mem, 1, hist, S, Y, g, p);
+        lbfgs_combine_kernel<<<nmodels * nb, LB_GT, 0, st>>>(nmodels, n, mem, nb, hist, S, Y, g, p);
     } else {
         lbfgs_direction_kernel<<<nmodels, LB_THREADS, 0, st>>>(nmodels, n, mem, hist, S, Y, ysyy, g, p);
     }
