@@ -98,32 +98,25 @@ struct Cell {
 // remap gives each XCD a contiguous range of (block, shot) work, so the rows
 // that a block's z stencil shares with the blocks above and below it are
 // fetched into one L2.
-__device__ __forceinline__ int xcd_work_id(int nblocks)
+__device__ __forceinline__ int xcd_work_id(int b, int nblocks)
 {
-    const int b = blockIdx.x;
     const int per = nblocks / NXCD, rem = nblocks % NXCD;
     const int x = b % NXCD, j = b / NXCD;
     return x * per + min(x, rem) + j;
 }
 
-// Cell of this thread in a grid of EBX x (256 / EBX) cell blocks. XCD =
-// true: a 1-D grid over (block, shot) taken in xcd_work_id order; false: a
-// 2-D grid, blockIdx.y the shot.
+// Cell of this thread in a grid of EBX x (256 / EBX) cell blocks: a 1-D grid
+// over (block, shot) after `first` workgroups of other work; XCD = true: in
+// xcd_work_id order.
 template <int EBX, bool XCD>
-__device__ __forceinline__ Cell cell_of(const Grid2 &g, int spm)
+__device__ __forceinline__ Cell cell_of(const Grid2 &g, int spm, int first = 0)
 {
     constexpr int EBZ = 256 / EBX;
     Cell c;
     const int ntxe = (g.NX + EBX - 1) / EBX, nblk = ntxe * ((g.NZ + EBZ - 1) / EBZ);
-    int r;
-    if (XCD) {
-        const int w = xcd_work_id((int)gridDim.x);
-        c.shot = w / nblk;
-        r = w - c.shot * nblk;
-    } else {
-        c.shot = blockIdx.y;
-        r = blockIdx.x;
-    }
+    const int b = (int)blockIdx.x - first, w = XCD ? xcd_work_id(b, (int)gridDim.x - first) : b;
+    c.shot = w / nblk;
+    const int r = w - c.shot * nblk;
     const int bz = r / ntxe, bx = r - bz * ntxe;
     c.ix = bx * EBX + (int)(threadIdx.x % EBX);
     c.iz = bz * EBZ + (int)(threadIdx.x / EBX);
@@ -135,12 +128,45 @@ __device__ __forceinline__ Cell cell_of(const Grid2 &g, int spm)
     return c;
 }
 
-template <int EBX, bool XCD>
-dim3 cell_grid(const Grid2 &g, int nshots)
+template <int EBX>
+int cell_blocks(const Grid2 &g, int nshots)
 {
     constexpr int EBZ = 256 / EBX;
-    const int nblk = ((g.NX + EBX - 1) / EBX) * ((g.NZ + EBZ - 1) / EBZ);
-    return XCD ? dim3(nblk * nshots) : dim3(nblk, nshots);
+    return ((g.NX + EBX - 1) / EBX) * ((g.NZ + EBZ - 1) / EBZ) * nshots;
+}
+
+// The step's receiver work rides in the first workgroups of a launch that
+// neither reads nor writes what it writes (launches of their own took 4.8 and
+// 4.9 us of every step): the record of v^{n+1} with the stress update, the
+// injection with pass 1.
+__device__ __forceinline__ void record_receiver(const El2RecArgs &a, int i)
+{
+    if (i >= a.nshots * a.nrec) return;
+    const int shot = i / a.nrec, r = i - shot * a.nrec;
+    const long long f = (long long)shot * a.plane + a.rec_f[i];
+    a.seis[((long long)(shot * 2) * a.nt + a.k) * a.nrec + r] = a.vx[f];
+    a.seis[((long long)(shot * 2 + 1) * a.nt + a.k) * a.nrec + r] = a.vz[f];
+}
+
+// R^T dJ/dd of sample k into the velocity adjoints: one thread per unique
+// receiver cell, summing its receivers in a fixed order.
+__device__ __forceinline__ void inject_receiver(const El2RecArgs &a, int i)
+{
+    if (i >= a.nshots * a.nuniq_max) return;
+    const int shot = i / a.nuniq_max, u = i - shot * a.nuniq_max;
+    const int *off = a.uoff + (long long)shot * (a.nuniq_max + 1);
+    const int b = off[u], e = off[u + 1];
+    if (b >= e) return;
+    const float *dx = a.dJdd + ((long long)(shot * 2) * a.nt + a.k) * a.nrec;
+    const float *dz = a.dJdd + ((long long)(shot * 2 + 1) * a.nt + a.k) * a.nrec;
+    float sx = 0.f, sz = 0.f;
+    for (int j = b; j < e; ++j) {
+        sx += dx[a.uid[j]];
+        sz += dz[a.uid[j]];
+    }
+    const long long f = (long long)shot * a.plane + a.rec_f[(long long)shot * a.nrec + a.uid[b]];
+    a.ax[f] += sx;
+    a.az[f] += sz;
 }
 
 // Shots per thread in the step passes: the shots of a group belong to one
@@ -180,10 +206,14 @@ __global__ __launch_bounds__(256) void el2_vel_kernel(El2Args a)
 }
 
 template <int GSH, int EBX>
-__global__ __launch_bounds__(256) void el2_str_kernel(El2Args a)
+__global__ __launch_bounds__(256) void el2_str_kernel(El2Args a, El2RecArgs rec)
 {
     const Grid2 &g = a.g;
-    const Cell c = cell_of<EBX, XCD_FWD>(g, a.shots_per_model / GSH);   // c.shot: the group
+    if ((int)blockIdx.x < rec.blocks) {
+        record_receiver(rec, (int)(blockIdx.x * 256 + threadIdx.x));
+        return;
+    }
+    const Cell c = cell_of<EBX, XCD_FWD>(g, a.shots_per_model / GSH, rec.blocks);   // c.shot: the group
     if (!c.valid) return;
     const long long SX = g.SX;
     const float lam = a.m[M_LAM][c.mo + c.f], mu = a.m[M_MU][c.mo + c.f], muxz = a.m[M_MUXZ][c.mo + c.f];
@@ -220,39 +250,6 @@ __global__ __launch_bounds__(256) void el2_str_kernel(El2Args a)
         }
     }
 }
-
-__global__ void el2_record_kernel(El2RecArgs a)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= a.nshots * a.nrec) return;
-    const int shot = i / a.nrec, r = i - shot * a.nrec;
-    const long long f = (long long)shot * a.plane + a.rec_f[i];
-    a.seis[((long long)(shot * 2) * a.nt + a.k) * a.nrec + r] = a.vx[f];
-    a.seis[((long long)(shot * 2 + 1) * a.nt + a.k) * a.nrec + r] = a.vz[f];
-}
-
-// R^T dJ/dd of sample k into the velocity adjoints: one thread per unique
-// receiver cell, summing its receivers in a fixed order.
-__global__ void el2_inject_kernel(El2RecArgs a)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= a.nshots * a.nuniq_max) return;
-    const int shot = i / a.nuniq_max, u = i - shot * a.nuniq_max;
-    const int *off = a.uoff + (long long)shot * (a.nuniq_max + 1);
-    const int b = off[u], e = off[u + 1];
-    if (b >= e) return;
-    const float *dx = a.dJdd + ((long long)(shot * 2) * a.nt + a.k) * a.nrec;
-    const float *dz = a.dJdd + ((long long)(shot * 2 + 1) * a.nt + a.k) * a.nrec;
-    float sx = 0.f, sz = 0.f;
-    for (int j = b; j < e; ++j) {
-        sx += dx[a.uid[j]];
-        sz += dz[a.uid[j]];
-    }
-    const long long f = (long long)shot * a.plane + a.rec_f[(long long)shot * a.nrec + a.uid[b]];
-    a.ax[f] += sx;
-    a.az[f] += sz;
-}
-
 
 // Pass 1 at one cell of one shot, from its stress adjoints sxx, szz, sxz:
 // the adjoints e1..e4 of the velocity differences (with the CPML memories),
@@ -304,10 +301,14 @@ __device__ __forceinline__ void adj3_cell(const El2AdjArgs &a, const Grid2 &g, l
 }
 
 template <int GSH, int EBX>
-__global__ __launch_bounds__(256) void el2_adj1_kernel(El2AdjArgs a)
+__global__ __launch_bounds__(256) void el2_adj1_kernel(El2AdjArgs a, El2RecArgs rec)
 {
     const Grid2 &g = a.g;
-    const Cell c = cell_of<EBX, XCD_ADJ>(g, a.shots_per_model / GSH);   // c.shot: the group
+    if ((int)blockIdx.x < rec.blocks) {
+        inject_receiver(rec, (int)(blockIdx.x * 256 + threadIdx.x));
+        return;
+    }
+    const Cell c = cell_of<EBX, XCD_ADJ>(g, a.shots_per_model / GSH, rec.blocks);   // c.shot: the group
     if (!c.valid) return;
     const float lam = a.m[M_LAM][c.mo + c.f], mu = a.m[M_MU][c.mo + c.f], muxz = a.m[M_MUXZ][c.mo + c.f];
     float g0 = 0.f, g1 = 0.f, g2 = 0.f;
@@ -328,10 +329,14 @@ __global__ __launch_bounds__(256) void el2_adj1_kernel(El2AdjArgs a)
 // which pass 3 has just formed there, so one read and write of them serve
 // both.
 template <int GSH, int EBX>
-__global__ __launch_bounds__(256) void el2_adj31_kernel(El2AdjArgs a)
+__global__ __launch_bounds__(256) void el2_adj31_kernel(El2AdjArgs a, El2RecArgs rec)
 {
     const Grid2 &g = a.g;
-    const Cell c = cell_of<EBX, XCD_ADJ>(g, a.shots_per_model / GSH);   // c.shot: the group
+    if ((int)blockIdx.x < rec.blocks) {
+        inject_receiver(rec, (int)(blockIdx.x * 256 + threadIdx.x));
+        return;
+    }
+    const Cell c = cell_of<EBX, XCD_ADJ>(g, a.shots_per_model / GSH, rec.blocks);   // c.shot: the group
     if (!c.valid) return;
     const float lam = a.m[M_LAM][c.mo + c.f], mu = a.m[M_MU][c.mo + c.f], muxz = a.m[M_MUXZ][c.mo + c.f];
     float g0 = 0.f, g1 = 0.f, g2 = 0.f;
@@ -536,46 +541,47 @@ int blocks_for(long long n) { return (int)std::min<long long>((n + 255) / 256, 6
 
 } // namespace
 
-// Launch kernel K<GSH, EBX> for the args' group size and block width.
-#define EL2_DISPATCH(K, a, XCD, s)                                                                    \
+// Launch kernel K<GSH, EBX> for the args' group size and block width, after
+// `extra` workgroups of receiver work; further arguments behind.
+#define EL2_DISPATCH(K, a, extra, s, ...)                                                             \
     do {                                                                                              \
         const int gs_ = (a).gs, n_ = (a).nshots / gs_;                                                \
         if ((a).ebx == 64) {                                                                          \
-            const dim3 grid_ = cell_grid<64, XCD>((a).g, n_);                                         \
-            if (gs_ == 4) K<4, 64><<<grid_, 256, 0, s>>>(a);                                          \
-            else if (gs_ == 2) K<2, 64><<<grid_, 256, 0, s>>>(a);                                     \
-            else K<1, 64><<<grid_, 256, 0, s>>>(a);                                                   \
+            const int grid_ = cell_blocks<64>((a).g, n_) + (extra);                                   \
+            if (gs_ == 4) K<4, 64><<<grid_, 256, 0, s>>>(__VA_ARGS__);                                \
+            else if (gs_ == 2) K<2, 64><<<grid_, 256, 0, s>>>(__VA_ARGS__);                           \
+            else K<1, 64><<<grid_, 256, 0, s>>>(__VA_ARGS__);                                         \
         } else {                                                                                      \
-            const dim3 grid_ = cell_grid<32, XCD>((a).g, n_);                                         \
-            if (gs_ == 4) K<4, 32><<<grid_, 256, 0, s>>>(a);                                          \
-            else if (gs_ == 2) K<2, 32><<<grid_, 256, 0, s>>>(a);                                     \
-            else K<1, 32><<<grid_, 256, 0, s>>>(a);                                                   \
+            const int grid_ = cell_blocks<32>((a).g, n_) + (extra);                                   \
+            if (gs_ == 4) K<4, 32><<<grid_, 256, 0, s>>>(__VA_ARGS__);                                \
+            else if (gs_ == 2) K<2, 32><<<grid_, 256, 0, s>>>(__VA_ARGS__);                           \
+            else K<1, 32><<<grid_, 256, 0, s>>>(__VA_ARGS__);                                         \
         }                                                                                             \
     } while (0)
 
-void launch_el2_vel(const El2Args &a, hipStream_t s) { EL2_DISPATCH(el2_vel_kernel, a, XCD_FWD, s); }
-void launch_el2_str(const El2Args &a, hipStream_t s) { EL2_DISPATCH(el2_str_kernel, a, XCD_FWD, s); }
-void launch_el2_adj1(const El2AdjArgs &a, hipStream_t s) { EL2_DISPATCH(el2_adj1_kernel, a, XCD_ADJ, s); }
-void launch_el2_adj2(const El2AdjArgs &a, hipStream_t s) { EL2_DISPATCH(el2_adj2_kernel, a, XCD_ADJ, s); }
-void launch_el2_adj31(const El2AdjArgs &a, hipStream_t s) { EL2_DISPATCH(el2_adj31_kernel, a, XCD_ADJ, s); }
+void launch_el2_vel(const El2Args &a, hipStream_t s) { EL2_DISPATCH(el2_vel_kernel, a, 0, s, a); }
+void launch_el2_str(const El2Args &a, El2RecArgs rec, hipStream_t s)
+{
+    rec.blocks = (rec.nshots * rec.nrec + 255) / 256;
+    EL2_DISPATCH(el2_str_kernel, a, rec.blocks, s, a, rec);
+}
+void launch_el2_adj1(const El2AdjArgs &a, El2RecArgs rec, hipStream_t s)
+{
+    rec.blocks = (rec.nshots * rec.nuniq_max + 255) / 256;
+    EL2_DISPATCH(el2_adj1_kernel, a, rec.blocks, s, a, rec);
+}
+void launch_el2_adj2(const El2AdjArgs &a, hipStream_t s) { EL2_DISPATCH(el2_adj2_kernel, a, 0, s, a); }
+void launch_el2_adj31(const El2AdjArgs &a, El2RecArgs rec, hipStream_t s)
+{
+    rec.blocks = (rec.nshots * rec.nuniq_max + 255) / 256;
+    EL2_DISPATCH(el2_adj31_kernel, a, rec.blocks, s, a, rec);
+}
 void launch_el2_adj3(const El2AdjArgs &a, hipStream_t s)
 {
-    if (a.ebx == 64) el2_adj3_kernel<64><<<cell_grid<64, XCD_ADJ>(a.g, a.nshots), 256, 0, s>>>(a);
-    else el2_adj3_kernel<32><<<cell_grid<32, XCD_ADJ>(a.g, a.nshots), 256, 0, s>>>(a);
+    if (a.ebx == 64) el2_adj3_kernel<64><<<cell_blocks<64>(a.g, a.nshots), 256, 0, s>>>(a);
+    else el2_adj3_kernel<32><<<cell_blocks<32>(a.g, a.nshots), 256, 0, s>>>(a);
 }
 #undef EL2_DISPATCH
-
-void launch_el2_record(const El2RecArgs &a, hipStream_t s)
-{
-    const int n = a.nshots * a.nrec;
-    if (n > 0) el2_record_kernel<<<(n + 255) / 256, 256, 0, s>>>(a);
-}
-
-void launch_el2_inject(const El2RecArgs &a, hipStream_t s)
-{
-    const int n = a.nshots * a.nuniq_max;
-    if (n > 0) el2_inject_kernel<<<(n + 255) / 256, 256, 0, s>>>(a);
-}
 
 void launch_el2_prep(const Grid2 &g, int nmodels, const float *vp, const float *vs, const float *rho,
                      float *const *model, float *const *phys_pad, hipStream_t s)

@@ -68,8 +68,10 @@ struct El2AdjArgs {
     float src_scale;
 };
 
+// The receivers' part of a launch (none: nshots = 0).
 struct El2RecArgs {
     int nshots, nrec, nt, k;
+    int blocks;                // workgroups of it, set by the launcher
     const long long *rec_f;    // [shot][nrec] frame index
     long long plane;
     const float *vx, *vz;
@@ -83,14 +85,14 @@ struct El2RecArgs {
 };
 
 void launch_el2_vel(const El2Args &a, hipStream_t s);
-void launch_el2_str(const El2Args &a, hipStream_t s);
-void launch_el2_record(const El2RecArgs &a, hipStream_t s);
-void launch_el2_inject(const El2RecArgs &a, hipStream_t s);
-void launch_el2_adj1(const El2AdjArgs &a, hipStream_t s);
+// rec: the velocities to record
+void launch_el2_str(const El2Args &a, El2RecArgs rec, hipStream_t s);
+// rec: the residuals to inject into the velocity adjoints before pass 2
+void launch_el2_adj1(const El2AdjArgs &a, El2RecArgs rec, hipStream_t s);
 void launch_el2_adj2(const El2AdjArgs &a, hipStream_t s);
 void launch_el2_adj3(const El2AdjArgs &a, hipStream_t s);
-// pass 3 of step k with pass 1 of step k - 1 (a: the arguments of step k - 1)
-void launch_el2_adj31(const El2AdjArgs &a, hipStream_t s);
+// pass 3 of step k with pass 1 of step k - 1 (a, rec: the arguments of step k - 1)
+void launch_el2_adj31(const El2AdjArgs &a, El2RecArgs rec, hipStream_t s);
 void launch_el2_prep(const Grid2 &g, int nmodels, const float *vp, const float *vs, const float *rho,
                      float *const *model, float *const *phys_pad, hipStream_t s);
 void launch_el2_finalize(const Grid2 &g, int nmodels, int spm, int gs, const float *grad, long long grad_stride,

@@ -740,7 +740,7 @@ El2Tabs el_tabs(const sg_model *m)
     return t;
 }
 
-// One elastic step: velocity update, receiver record, stress update (+ source).
+// One elastic step: velocity update, stress update (+ source) with the receiver record.
 void el_fwd_step(const sg_model *m, int ns, const float *wav, int k, float *seis, float *snap, hipStream_t s)
 {
     El2Args a{};
@@ -762,22 +762,21 @@ void el_fwd_step(const sg_model *m, int ns, const float *wav, int k, float *seis
     a.k = k;
     a.src_scale = (float)(m->d.dt / (m->d.dx * m->d.dx));
     launch_el2_vel(a, s);
+    El2RecArgs r{};
     if (seis && m->geom_nrec > 0) {
-        El2RecArgs r{};
         r.nshots = ns; r.nrec = m->geom_nrec; r.nt = m->d.nt; r.k = k;
         r.rec_f = static_cast<const long long *>(m->rec_ent);
         r.plane = m->L.plane;
         r.vx = m->fwd[E_VX]; r.vz = m->fwd[E_VZ];
         r.seis = seis;
-        launch_el2_record(r, s);
     }
-    launch_el2_str(a, s);
+    launch_el2_str(a, r, s);
 }
 
-// Elastic adjoint step k: pass 1 (unless the previous launch ran it: first =
-// false), the receiver injection, pass 2, and pass 3 -- with the next step's
-// pass 1 when that step's snapshots are at hand (snap_next, step k - 1 of
-// the same segment).
+// Elastic adjoint step k: pass 1 with the receiver injection (unless the
+// previous launch ran them: first = false), pass 2, and pass 3 -- with the
+// next step's pass 1 and injection when that step's snapshots are at hand
+// (snap_next, step k - 1 of the same segment).
 void el_adj_step(const sg_model *m, int ns, int k, const float *dJdd, float *gwav, const float *snap, hipStream_t s,
                  bool first = true, const float *snap_next = nullptr)
 {
@@ -802,23 +801,23 @@ void el_adj_step(const sg_model *m, int ns, int k, const float *dJdd, float *gwa
     a.nt = m->d.nt;
     a.k = k;
     a.src_scale = (float)(m->d.dt / (m->d.dx * m->d.dx));
-    if (first) launch_el2_adj1(a, s);
+    El2RecArgs r{};
     if (m->geom_nrec > 0) {
-        El2RecArgs r{};
         r.nshots = ns; r.nrec = m->geom_nrec; r.nt = m->d.nt; r.k = k;
         r.rec_f = static_cast<const long long *>(m->rec_ent);
         r.plane = m->L.plane;
         r.uoff = m->uoff; r.uid = m->uid; r.nuniq_max = m->nuniq_max;
         r.dJdd = dJdd;
         r.ax = m->adj[E_VX]; r.az = m->adj[E_VZ];
-        launch_el2_inject(r, s);
     }
+    if (first) launch_el2_adj1(a, r, s);
     launch_el2_adj2(a, s);
     if (snap_next) {
         El2AdjArgs b = a;
         b.k = k - 1;
         b.snap = snap_next;
-        launch_el2_adj31(b, s);
+        r.k = k - 1;
+        launch_el2_adj31(b, r, s);
     } else {
         launch_el2_adj3(a, s);
     }
