@@ -1344,8 +1344,7 @@ void launch_ac2_prep(const Grid2 &g, int nmodels, const float *vp, double dt, do
 
 // ------------------------------------------------------------ grad finalize
 // Pass 1: per padded cell, sum dJ/dchat over the model's shots in shot order
-// (coalesced over cells).  Pass 2: per physical cell, sum the padded cells
-// that replicate it and apply the chain rule dchat/dc = 2 dt^2 c / dx^2.
+// (coalesced over cells).  Pass 2: the fold with the chain rule.
 __global__ void ac2_sum_shots_kernel(Grid2 g, int nmodels, int spm, const float *grad, float *acc)
 {
     const long long n = (long long)nmodels * g.plane;
@@ -1358,36 +1357,17 @@ __global__ void ac2_sum_shots_kernel(Grid2 g, int nmodels, int spm, const float 
     }
 }
 
-__global__ void ac2_finalize_kernel(Grid2 g, int nmodels, const float *acc, const float *cpad,
-                                    double dt, double dx, float *g_vp)
-{
-    const long long n = (long long)nmodels * g.nz * g.nx;
-    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
-         i += (long long)gridDim.x * blockDim.x) {
-        const long long m = i / ((long long)g.nz * g.nx);
-        const long long rem = i - m * g.nz * g.nx;
-        const int iz = (int)(rem / g.nx), ix = (int)(rem - (long long)iz * g.nx);
-        const int zlo = iz == 0 ? 0 : iz + g.P, zhi = iz == g.nz - 1 ? g.NZ - 1 : iz + g.P;
-        const int xlo = ix == 0 ? 0 : ix + g.P, xhi = ix == g.nx - 1 ? g.NX - 1 : ix + g.P;
-        const float *am = acc + m * g.plane;
-        float v = 0.f;
-        for (int pz = zlo; pz <= zhi; ++pz)
-            for (int px = xlo; px <= xhi; ++px)
-                v += am[(long long)(pz + OZ) * g.SX + px + OX];
-        const double c = cpad[m * g.plane + (long long)(iz + g.P + OZ) * g.SX + ix + g.P + OX];
-        g_vp[i] = (float)(2.0 * dt * dt * c / (dx * dx)) * v;
-    }
-}
-
 void launch_ac2_finalize(const Grid2 &g, int nmodels, int spm, const float *grad, float *acc,
                          const float *cpad, double dt, double dx, float *g_vp, hipStream_t s)
 {
-    long long n = (long long)nmodels * g.plane;
-    int blocks = (int)std::min<long long>((n + 255) / 256, 65536);
-    ac2_sum_shots_kernel<<<blocks, 256, 0, s>>>(g, nmodels, spm, grad, acc);
-    n = (long long)nmodels * g.nz * g.nx;
-    blocks = (int)std::min<long long>((n + 255) / 256, 65536);
-    ac2_finalize_kernel<<<blocks, 256, 0, s>>>(g, nmodels, acc, cpad, dt, dx, g_vp);
+    const float *sum = grad;               // one shot per model: its gradient is the sum
+    if (spm > 1) {
+        const long long n = (long long)nmodels * g.plane;
+        const int blocks = (int)std::min<long long>((n + 255) / 256, 65536);
+        ac2_sum_shots_kernel<<<blocks, 256, 0, s>>>(g, nmodels, spm, grad, acc);
+        sum = acc;
+    }
+    launch_fold2(g, nmodels, sum, cpad, dt, dx, g_vp, s);
 }
 
 } // namespace sg

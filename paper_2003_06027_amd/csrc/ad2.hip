@@ -742,27 +742,6 @@ __global__ void ad2_sum_shots_kernel(Grid2 g, int nmodels, int spm, const float 
     }
 }
 
-// dJ/dc per physical cell: the padded nodes replicating it, times
-// dchat/dc = 2 dt^2 c / dx^2.
-__global__ void ad2_fold_kernel(Grid2 g, int nmodels, const float *acc, const float *cpad, double dt, double dx,
-                                float *g_vp)
-{
-    const long long n = (long long)nmodels * g.nz * g.nx;
-    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
-        const long long m = i / ((long long)g.nz * g.nx);
-        const long long rem = i - m * g.nz * g.nx;
-        const int iz = (int)(rem / g.nx), ix = (int)(rem - (long long)iz * g.nx);
-        const int zlo = iz == 0 ? 0 : iz + g.P, zhi = iz == g.nz - 1 ? g.NZ - 1 : iz + g.P;
-        const int xlo = ix == 0 ? 0 : ix + g.P, xhi = ix == g.nx - 1 ? g.NX - 1 : ix + g.P;
-        const float *am = acc + m * g.plane;
-        float v = 0.f;
-        for (int pz = zlo; pz <= zhi; ++pz)
-            for (int px = xlo; px <= xhi; ++px) v += am[fr(g, pz, px)];
-        const double c = cpad[m * g.plane + fr(g, iz + g.P, ix + g.P)];
-        g_vp[i] = (float)(2.0 * dt * dt * c / (dx * dx)) * v;
-    }
-}
-
 int blocks_for(long long n) { return (int)std::min<long long>((n + 255) / 256, 65536); }
 
 } // namespace
@@ -816,8 +795,8 @@ void launch_ad2_prep(const Grid2 &g, int nmodels, const float *vp, double dt, do
 void launch_ad2_finalize(const Grid2 &g, int nmodels, int spm, const float *gn, float *acc, const float *cpad,
                          double dt, double dx, float *g_vp, hipStream_t s)
 {
-    ad2_sum_shots_kernel<<<blocks_for((long long)nmodels * g.plane), 256, 0, s>>>(g, nmodels, spm, gn, acc);
-    ad2_fold_kernel<<<blocks_for((long long)nmodels * g.nz * g.nx), 256, 0, s>>>(g, nmodels, acc, cpad, dt, dx, g_vp);
+    if (spm > 1) ad2_sum_shots_kernel<<<blocks_for((long long)nmodels * g.plane), 256, 0, s>>>(g, nmodels, spm, gn, acc);
+    launch_fold2(g, nmodels, spm > 1 ? acc : gn, cpad, dt, dx, g_vp, s);   // one shot per model is its own sum
 }
 
 } // namespace sg

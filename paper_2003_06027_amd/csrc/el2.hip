@@ -512,31 +512,6 @@ __global__ void el2_chain_kernel(Grid2 g, int nmodels, const float *acc, const f
     }
 }
 
-__global__ void el2_fold_kernel(Grid2 g, int nmodels, const float *pad, float *g_vp, float *g_vs, float *g_rho)
-{
-    const long long np = (long long)nmodels * g.plane;
-    const long long n = (long long)nmodels * g.nz * g.nx;
-    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
-         i += (long long)gridDim.x * blockDim.x) {
-        const long long m = i / ((long long)g.nz * g.nx);
-        const long long rem = i - m * g.nz * g.nx;
-        const int iz = (int)(rem / g.nx), ix = (int)(rem - (long long)iz * g.nx);
-        const int zlo = iz == 0 ? 0 : iz + g.P, zhi = iz == g.nz - 1 ? g.NZ - 1 : iz + g.P;
-        const int xlo = ix == 0 ? 0 : ix + g.P, xhi = ix == g.nx - 1 ? g.NX - 1 : ix + g.P;
-        float v0 = 0.f, v1 = 0.f, v2 = 0.f;
-        for (int pz = zlo; pz <= zhi; ++pz)
-            for (int px = xlo; px <= xhi; ++px) {
-                const long long q = m * g.plane + (long long)(pz + OZ) * g.SX + px + OX;
-                v0 += pad[q];
-                v1 += pad[np + q];
-                v2 += pad[2 * np + q];
-            }
-        g_vp[i] = v0;
-        g_vs[i] = v1;
-        g_rho[i] = v2;
-    }
-}
-
 int blocks_for(long long n) { return (int)std::min<long long>((n + 255) / 256, 65536); }
 
 } // namespace
@@ -601,8 +576,8 @@ void launch_el2_finalize(const Grid2 &g, int nmodels, int spm, int gs, const flo
     el2_sum_shots_kernel<<<blocks_for(n), 256, 0, s>>>(g, nmodels, spm / gs, grad, grad_stride, acc);
     el2_chain_kernel<<<blocks_for(n), 256, 0, s>>>(g, nmodels, acc, model[2], model[1], model[3], model[4],
                                                     phys_pad[0], phys_pad[1], phys_pad[2], pad);
-    el2_fold_kernel<<<blocks_for((long long)nmodels * g.nz * g.nx), 256, 0, s>>>(g, nmodels, pad, g_vp, g_vs,
-                                                                                 g_rho);
+    float *const out[3] = {g_vp, g_vs, g_rho};
+    for (int q = 0; q < 3; ++q) launch_fold2(g, nmodels, pad + q * n, nullptr, 0.0, 0.0, out[q], s);
 }
 
 } // namespace sg

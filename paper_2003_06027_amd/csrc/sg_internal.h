@@ -149,6 +149,9 @@ void launch_ac2_finalize(const Grid2 &g, int nmodels, int shots_per_model, const
                          float *acc, const float *cpad, double dt, double dx, float *g_vp,
                          hipStream_t s);
 void launch_fill(float *p, long long n, float v, hipStream_t s);
+// out = the fold of the padded 2-D field acc onto the physical cells, times dchat/dc (cpad; null: 1)
+void launch_fold2(const Grid2 &g, int nmodels, const float *acc, const float *cpad, double dt, double dx, float *out,
+                  hipStream_t s);
 // n floats (a multiple of 4, 16-byte aligned) of each of `count` fields
 struct CopyFields {
     static constexpr int MAX = 16;

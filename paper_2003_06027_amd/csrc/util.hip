@@ -58,6 +58,84 @@ void launch_copy_fields(const CopyFields &c, long long n, hipStream_t s)
     else                                 copy_fields_kernel<false><<<grid, 256, 0, s>>>(c, n4);
 }
 
+// Fold the padded cells of 2-D models onto the physical cells that they
+// replicate: each cell's sum over its padded cells in z, x order, times
+// dchat/dc = 2 dt^2 c / dx^2 if cpad is given.  A workgroup per row: two
+// wavefronts the columns between the ends, one each end cell, whose P + 1
+// (corner: (P + 1)^2) cells it loads 64 at a time and adds up lane by lane (a
+// thread that loaded and added them one by one took 38 us for P = 20, 84 us
+// for P = 32; now 15 for P = 20).
+__global__ __launch_bounds__(256) void fold2_kernel(Grid2 g, const float *acc, const float *cpad, double dt, double dx,
+                                                    float *out)
+{
+    constexpr int U = 8;                   // loads in flight
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const long long m = blockIdx.x / g.nz;
+    const int iz = (int)(blockIdx.x - m * g.nz);
+    const int zlo = iz == 0 ? 0 : iz + g.P, zhi = iz == g.nz - 1 ? g.NZ - 1 : iz + g.P;
+    const float *am = acc + m * g.plane;
+    auto at = [&](int pz, int px) { return (long long)(pz + OZ) * g.SX + px + OX; };
+    auto store = [&](int ix, float v) {
+        if (cpad) {
+            const double c = cpad[m * g.plane + at(iz + g.P, ix + g.P)];
+            v = (float)(2.0 * dt * dt * c / (dx * dx)) * v;
+        }
+        out[(m * g.nz + iz) * g.nx + ix] = v;
+    };
+    if (wv >= 2) {
+        for (int ix = 1 + (wv - 2) * 64 + lane; ix < g.nx - 1; ix += 128) {
+            float v = 0.f;
+            for (int p0 = zlo; p0 <= zhi; p0 += U) {
+                float x[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) x[u] = am[at(min(p0 + u, zhi), ix + g.P)];
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (p0 + u <= zhi) v += x[u];
+            }
+            store(ix, v);
+        }
+        return;
+    }
+    const int ix = wv ? g.nx - 1 : 0;
+    if (wv && g.nx == 1) return;           // the one column is the first wavefront's
+    const int xlo = ix == 0 ? 0 : ix + g.P, xhi = ix == g.nx - 1 ? g.NX - 1 : ix + g.P;
+    const int nch = (xhi - xlo) / 64 + 1, items = (zhi - zlo + 1) * nch;   // runs of up to 64 cells, in order
+    float v = 0.f;
+    for (int q0 = 0; q0 < items; q0 += U) {
+        float x[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int q = min(q0 + u, items - 1), r = q / nch, b = xlo + (q - r * nch) * 64;
+            const float xv = am[at(zlo + r, min(b + lane, xhi))];
+            x[u] = b + lane <= xhi ? xv : 0.f;             // (zeros added behind a run change nothing)
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int q = q0 + u, b = xlo + (q % nch) * 64, cnt = q < items ? min(64, xhi - b + 1) : 0;
+            for (int l = 0; l < cnt; l += 8) {
+                float y[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) y[e] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x[u]), l + e));
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v += y[e];
+            }
+        }
+    }
+    if (lane == 0) store(ix, v);
+}
+
+void launch_fold2(const Grid2 &g, int nmodels, const float *acc, const float *cpad, double dt, double dx, float *out,
+                  hipStream_t s)
+{
+    for (int m0 = 0; m0 < nmodels;) {      // a launch's workgroups are an int
+        const int k = (int)std::min<long long>(nmodels - m0, std::max(1, (1 << 30) / g.nz));
+        fold2_kernel<<<(unsigned)(k * g.nz), 256, 0, s>>>(g, acc + m0 * g.plane, cpad ? cpad + m0 * g.plane : nullptr, dt,
+                                                          dx, out + (long long)m0 * g.nz * g.nx);
+        m0 += k;
+    }
+}
+
 // Ricker wavelet r(t) = (1 - 2 a) exp(-a), a = (pi f0 (t - t0))^2, in FP64.
 __global__ void ricker_kernel(double f0, double t0, double dt, int nt, float *out)
 {
