@@ -230,7 +230,7 @@ SG_API int adjoint_gradient(sg_model *m, const sg_shots *sh, const float *dJ_dd,
 
 /* misfit() for callers that cannot allocate device memory (code under HIP
  * graph capture, tight serving loops, harnesses that forbid allocation):
- * the reduction a model's misfit runs -- 4096 workgroup partial sums in
+ * the reduction a model's misfit runs -- at most 4096 workgroup partial sums in
  * FP64, added in a fixed order -- with the partial sums in a static device
  * array of the library instead of a model's workspace, so J_dev and resid
  * are bitwise those of misfit(m, ...).  The array holds 4096 doubles
