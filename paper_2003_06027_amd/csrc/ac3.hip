@@ -376,7 +376,7 @@ void ac3_phi_kernel(Ac3PhiArgs a)
 }
 
 // ------------------------------------------------------------ forward pass B
-// Two launches over (xy tile, z chunk, shot): the tiles within 4 cells of the
+// Two parts, over (xy tile, z chunk, shot): the tiles within 4 cells of the
 // layer in x or y (LAYER: every plane takes the layer terms) and the others
 // (only the z slabs do; their cells are interior in x and y, hx = hy = 0).
 // In LAYER tiles the layer auxiliaries are staged like u: phi_x with its x
@@ -724,7 +724,7 @@ void ac3_phi_adj_kernel(Ac3PhiAdjArgs a)
 }
 
 // ------------------------------------------------------------ adjoint pass B
-// Two launches as in the forward: LAYER tiles take the layer terms on every
+// Two parts as in the forward: LAYER tiles take the layer terms on every
 // plane; in the others only the z slabs do, with hx = hy = 0 (their x and y
 // neighbours are interior too: h = 0, 1/(1+h) = 1), where e is constant.
 // The layer terms of axis j need D~_j of r_j = b_j / (1 + h_j) and of
