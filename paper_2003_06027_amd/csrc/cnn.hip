@@ -473,10 +473,10 @@ __device__ __forceinline__ int frag_at(int out, int tap, int in)
 
 // BF16 copies of c2..c5 in fragment order: wf[L] as they are and wt[L]
 // flipped and transposed, the weights of the input gradient.
-__global__ void prep_weights_kernel(const float *__restrict__ params, u16 *__restrict__ wf, u16 *__restrict__ wt)
+// (Weight i of the 4 WMID.)
+__device__ __forceinline__ void prep_weight(int i, const float *__restrict__ params, u16 *__restrict__ wf,
+                                            u16 *__restrict__ wt)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= 4 * WMID) return;
     const int L = i / WMID, k = i - L * WMID;
     const int co = k / (9 * CH), t = (k / CH) % 9, ci = k % CH;
     const u16 b = f2bf(params[OFF_C2 + L * PMID + k]);
@@ -510,11 +510,20 @@ __device__ __forceinline__ void store_pixels(const unsigned char *lds, long long
     }
 }
 
+// The first PREP_WG workgroups form the weight copies that the following
+// launches read (as a launch of its own 2.5 us).
+constexpr int PREP_WG = 4 * WMID / NT;
+static_assert(4 * WMID % NT == 0, "whole workgroups");
 __global__ __launch_bounds__(NT) void conv_in_kernel(const float *__restrict__ g, const float *__restrict__ params,
-                                                     u16 *__restrict__ x1, int N, int H, int W)
+                                                     u16 *__restrict__ x1, int N, int H, int W,
+                                                     u16 *__restrict__ wf, u16 *__restrict__ wt)
 {
     __shared__ __attribute__((aligned(16))) unsigned char lds[NT * 64];
-    const long long total = (long long)N * H * W, p0 = (long long)blockIdx.x * NT, p = p0 + threadIdx.x;
+    if (blockIdx.x < PREP_WG) {
+        prep_weight((int)(blockIdx.x * NT + threadIdx.x), params, wf, wt);
+        return;
+    }
+    const long long total = (long long)N * H * W, p0 = (long long)(blockIdx.x - PREP_WG) * NT, p = p0 + threadIdx.x;
     if (p < total) {
         int y, x;
         pixel_of((unsigned)p, H, W, y, x);
@@ -1011,9 +1020,7 @@ int cnn_forward(const float *params, const float *g, int32_t n, int32_t h, int32
     u16 *x1 = (u16 *)(base + L.act[0]), *a2 = (u16 *)(base + L.act[1]), *x2 = (u16 *)(base + L.act[2]);
     u16 *a4 = (u16 *)(base + L.act[3]), *x3 = (u16 *)(base + L.act[4]);
     const long long pix = (long long)n * h * w;
-    prep_weights_kernel<<<blocks(4 * WMID), 256, 0, s>>>(params, wf, wt);
-    HIPCHECK(hipGetLastError());
-    conv_in_kernel<<<blocks(pix, NT), NT, 0, s>>>(g, params, x1, n, h, w);
+    conv_in_kernel<<<PREP_WG + blocks(pix, NT), NT, 0, s>>>(g, params, x1, n, h, w, wf, wt);
     HIPCHECK(hipGetLastError());
     const float *bias = params + OFF_C2 + WMID;
     if (int e = launch_conv<true>(x1, n, h, w, wf + 0 * WMID, bias + 0 * PMID, nullptr, nullptr, 1, a2, nullptr, s)) return e;
