@@ -92,6 +92,45 @@ __device__ __forceinline__ void dma_halo_swizzled(const u16 *__restrict__ x, int
     }
 }
 
+// out[i] = sum over b of part[b][i] in FP64, in a fixed order: lane l of
+// output i sums rows b = l, l + 16, ... in ascending order, then the 16 lane
+// sums are added in lane order.  256 threads = 16 outputs x 16 lanes.  A lane
+// issues the loads of 16 of its rows before adding them, so that a chain of
+// nb / 16 rows costs nb / 256 memory latencies.  The reduction of a layer's
+// weight gradient rides in the first workgroups of the launch that forms its
+// input gradient (4.6 to 7 us of each layer as a launch of its own).
+struct Reduce {
+    const float *part;
+    int nb, stride, count;
+    float *out;
+    int blocks() const { return (count + 15) / 16; }
+};
+__device__ __forceinline__ void reduce_partials(const Reduce &a, int block, double (*red)[17])
+{
+    constexpr int U = 16;
+    const int o = threadIdx.x & 15, l = threadIdx.x >> 4;
+    const int i = block * 16 + o;
+    double s = 0.0;
+    if (i < a.count) {
+        int b = l;
+        for (; b + 16 * (U - 1) < a.nb; b += 16 * U) {
+            float v[U];
+#pragma unroll
+            for (int k = 0; k < U; ++k) v[k] = a.part[(long long)(b + 16 * k) * a.stride + i];
+#pragma unroll
+            for (int k = 0; k < U; ++k) s += (double)v[k];
+        }
+        for (; b < a.nb; b += 16) s += (double)a.part[(long long)b * a.stride + i];
+    }
+    red[l][o] = s;
+    __syncthreads();
+    if (l == 0 && i < a.count) {
+        double t = red[0][o];
+        for (int k = 1; k < 16; ++k) t += red[k][o];
+        a.out[i] = (float)t;
+    }
+}
+
 // ------------------------------------------------------------ 32 -> 32 layer
 struct ConvArgs {
     const u16 *x, *w;
@@ -100,6 +139,8 @@ struct ConvArgs {
     u16 *y;
     float *y32;
     int N, H, W, relu;
+    Reduce red;                            // of the first nred grid slices
+    int nred;
 };
 
 // grid (ceil(W/64), ceil(H/4), N).  Lane l of a wavefront: r = l % 16 is the
@@ -125,7 +166,14 @@ __global__ __launch_bounds__(NT) void conv3x3_mfma_kernel(ConvArgs a)
 {
     __shared__ __attribute__((aligned(16))) unsigned char lds_raw[CONV_LDS];
     u16 *lds = reinterpret_cast<u16 *>(lds_raw);
-    const int n = blockIdx.z, y0 = blockIdx.y * TH, x0 = blockIdx.x * TW;
+    if constexpr (FRAG) {
+        if ((int)blockIdx.z < a.nred) {
+            const int b = (int)((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x);
+            reduce_partials(a.red, b, reinterpret_cast<double (*)[17]>(lds_raw));   // (past the last output: nothing)
+            return;
+        }
+    }
+    const int n = (int)blockIdx.z - (FRAG ? a.nred : 0), y0 = blockIdx.y * TH, x0 = blockIdx.x * TW;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int r = lane & 15, g = lane >> 4;
 
@@ -432,37 +480,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     }
 }
 
-// out[i] = sum over b of part[b][i] in FP64, in a fixed order: lane l of
-// output i sums rows b = l, l + 16, ... in ascending order, then the 16 lane
-// sums are added in lane order.  256 threads = 16 outputs x 16 lanes.  A lane
-// issues the loads of 16 of its rows before adding them, so that a chain of
-// nb / 16 rows costs nb / 256 memory latencies.
-__global__ __launch_bounds__(256) void reduce_partials_kernel(const float *__restrict__ part, int nb, int stride,
-                                                              int count, float *__restrict__ out)
+__global__ __launch_bounds__(256) void reduce_partials_kernel(Reduce r)
 {
-    constexpr int U = 16;
     __shared__ double red[16][17];
-    const int o = threadIdx.x & 15, l = threadIdx.x >> 4;
-    const int i = blockIdx.x * 16 + o;
-    double s = 0.0;
-    if (i < count) {
-        int b = l;
-        for (; b + 16 * (U - 1) < nb; b += 16 * U) {
-            float v[U];
-#pragma unroll
-            for (int k = 0; k < U; ++k) v[k] = part[(long long)(b + 16 * k) * stride + i];
-#pragma unroll
-            for (int k = 0; k < U; ++k) s += (double)v[k];
-        }
-        for (; b < nb; b += 16) s += (double)part[(long long)b * stride + i];
-    }
-    red[l][o] = s;
-    __syncthreads();
-    if (l == 0 && i < count) {
-        double t = red[0][o];
-        for (int k = 1; k < 16; ++k) t += red[k][o];
-        out[i] = (float)t;
-    }
+    reduce_partials(r, (int)blockIdx.x, red);
 }
 
 // Element of the weight (out, tap, in) in fragment order (see conv3x3_mfma_kernel).
@@ -590,12 +611,17 @@ __global__ __launch_bounds__(NT) void conv_out_kernel(const u16 *__restrict__ x3
 }
 
 // Input gradient of c6 gated by x3 > 0: G[pix][ci] = [x3 > 0] sum_t w[t][ci] dp[pix - off_t].
+// The first nred workgroups reduce c6's weight gradient.
 __global__ __launch_bounds__(NT) void dgrad_out_kernel(const float *__restrict__ dp, const u16 *__restrict__ x3,
                                                        const float *__restrict__ params, u16 *__restrict__ G,
-                                                       int N, int H, int W)
+                                                       int N, int H, int W, Reduce red, int nred)
 {
     __shared__ __attribute__((aligned(16))) unsigned char lds[NT * 64];
-    const long long total = (long long)N * H * W, p0 = (long long)blockIdx.x * NT, p = p0 + threadIdx.x;
+    if ((int)blockIdx.x < nred) {
+        reduce_partials(red, (int)blockIdx.x, reinterpret_cast<double (*)[17]>(lds));
+        return;
+    }
+    const long long total = (long long)N * H * W, p0 = (long long)(blockIdx.x - nred) * NT, p = p0 + threadIdx.x;
     // the gates x3 of the run, straight into the swizzled slots (16 bytes per lane and load)
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -947,17 +973,29 @@ int check_dims(int n, int h, int w)
 
 template <bool FRAG>
 int launch_conv(const u16 *x, int n, int h, int w, const u16 *wgt, const float *bias, const u16 *res,
-                const u16 *gate, int relu, u16 *y, float *y32, hipStream_t s)
+                const u16 *gate, int relu, u16 *y, float *y32, hipStream_t s, const Reduce *red = nullptr)
 {
-    ConvArgs a{x, wgt, bias, res, gate, y, y32, n, h, w, relu};
+    ConvArgs a{x, wgt, bias, res, gate, y, y32, n, h, w, relu, {}, 0};
     dim3 grid((w + TW - 1) / TW, (h + TH - 1) / TH, n);
     if (grid.y > 65535u || grid.z > 65535u) return fail(SG_EINVAL, "image batch too large for one launch");
+    if (red) {
+        const long long slice = (long long)grid.x * grid.y, slices = (red->blocks() + slice - 1) / slice;
+        if (n + slices <= 65535) {
+            a.red = *red;
+            a.nred = (int)slices;
+            grid.z += a.nred;
+        } else {                           // no room in the grid
+            reduce_partials_kernel<<<red->blocks(), 256, 0, s>>>(*red);
+            HIPCHECK(hipGetLastError());
+        }
+    }
     conv3x3_mfma_kernel<FRAG><<<grid, NT, 0, s>>>(a);
     HIPCHECK(hipGetLastError());
     return SG_OK;
 }
 
-int launch_wgrad(const u16 *dy, const u16 *x, int n, int h, int w, float *part, float *out, hipStream_t s)
+// The partial sums of a weight gradient; red: their reduction, still to be launched.
+int launch_wgrad(const u16 *dy, const u16 *x, int n, int h, int w, float *part, float *out, Reduce &red, hipStream_t s)
 {
     WgradArgs a;
     a.dy = dy;
@@ -974,13 +1012,20 @@ int launch_wgrad(const u16 *dy, const u16 *x, int n, int h, int w, float *part, 
     const int nwg = a.ntiles < MAX_WG_WGRAD ? a.ntiles : MAX_WG_WGRAD;
     wgrad3x3_mfma_kernel<<<nwg, NT, 0, s>>>(a);
     HIPCHECK(hipGetLastError());
-    reduce_partials_kernel<<<(PMID + 15) / 16, 256, 0, s>>>(part, nwg, PMID, PMID, out);
+    red = Reduce{part, nwg, PMID, PMID, out};
+    return SG_OK;
+}
+
+int launch_reduce(const Reduce &red, hipStream_t s)
+{
+    reduce_partials_kernel<<<red.blocks(), 256, 0, s>>>(red);
     HIPCHECK(hipGetLastError());
     return SG_OK;
 }
 
 template <bool OUT>
-int launch_wgrad_thin(const float *img, const u16 *act, int n, int h, int w, float *part, float *out, hipStream_t s)
+int launch_wgrad_thin(const float *img, const u16 *act, int n, int h, int w, float *part, float *out, Reduce &red,
+                      hipStream_t s)
 {
     const int tx = (w + TW - 1) / TW, ty = (h + TH - 1) / TH;
     const long long nt = (long long)tx * ty * n;
@@ -988,9 +1033,7 @@ int launch_wgrad_thin(const float *img, const u16 *act, int n, int h, int w, flo
     const int nwg = nt < MAX_WG_THIN ? (int)nt : MAX_WG_THIN;
     wgrad_thin_kernel<OUT><<<nwg, NT, 0, s>>>(img, act, part, h, w, tx, ty, (int)nt);
     HIPCHECK(hipGetLastError());
-    const int count = OUT ? 9 * CH + 1 : 9 * CH + CH;
-    reduce_partials_kernel<<<(count + 15) / 16, 256, 0, s>>>(part, nwg, THIN_STRIDE, count, out);
-    HIPCHECK(hipGetLastError());
+    red = Reduce{part, nwg, THIN_STRIDE, OUT ? 9 * CH + 1 : 9 * CH + CH, out};
     return SG_OK;
 }
 
@@ -1049,20 +1092,22 @@ int cnn_backward(const float *params, const float *g, const float *dp, int32_t n
     float *part = (float *)(base + L.part);
     const long long pix = (long long)n * h * w;
 
-    if (int e = launch_wgrad_thin<true>(dp, x3, n, h, w, part, grad + OFF_C6, s)) return e;
-    dgrad_out_kernel<<<blocks(pix, NT), NT, 0, s>>>(dp, x3, params, G0, n, h, w);           // G0 = d pre(x3)
+    Reduce red;
+    if (int e = launch_wgrad_thin<true>(dp, x3, n, h, w, part, grad + OFF_C6, red, s)) return e;
+    dgrad_out_kernel<<<red.blocks() + blocks(pix, NT), NT, 0, s>>>(dp, x3, params, G0, n, h, w, red, red.blocks()); // G0 = d pre(x3)
     HIPCHECK(hipGetLastError());
     float *gm = grad + OFF_C2;
-    if (int e = launch_wgrad(G0, a4, n, h, w, part, gm + 3 * PMID, s)) return e;
-    if (int e = launch_conv<true>(G0, n, h, w, wt + 3 * WMID, nullptr, nullptr, a4, 0, G1, nullptr, s)) return e; // d pre(a4)
-    if (int e = launch_wgrad(G1, x2, n, h, w, part, gm + 2 * PMID, s)) return e;
-    if (int e = launch_conv<true>(G1, n, h, w, wt + 2 * WMID, nullptr, G0, x2, 0, G2, nullptr, s)) return e;     // d pre(x2)
-    if (int e = launch_wgrad(G2, a2, n, h, w, part, gm + 1 * PMID, s)) return e;
-    if (int e = launch_conv<true>(G2, n, h, w, wt + 1 * WMID, nullptr, nullptr, a2, 0, G0, nullptr, s)) return e; // d pre(a2)
-    if (int e = launch_wgrad(G0, x1, n, h, w, part, gm + 0 * PMID, s)) return e;
-    if (int e = launch_conv<true>(G0, n, h, w, wt + 0 * WMID, nullptr, G2, x1, 0, G1, nullptr, s)) return e;     // d pre(x1)
-    if (int e = launch_wgrad_thin<false>(g, G1, n, h, w, part, grad + OFF_C1, s)) return e;
-    return SG_OK;
+    // layer L: its weight gradient's partial sums, then its input gradient with their reduction
+    auto layer = [&](int L, const u16 *dy, const u16 *x, const u16 *res, u16 *dx) -> int {
+        if (int e = launch_wgrad(dy, x, n, h, w, part, gm + L * PMID, red, s)) return e;
+        return launch_conv<true>(dy, n, h, w, wt + L * WMID, nullptr, res, x, 0, dx, nullptr, s, &red);
+    };
+    if (int e = layer(3, G0, a4, nullptr, G1)) return e;   // d pre(a4)
+    if (int e = layer(2, G1, x2, G0, G2)) return e;        // d pre(x2)
+    if (int e = layer(1, G2, a2, nullptr, G0)) return e;   // d pre(a2)
+    if (int e = layer(0, G0, x1, G2, G1)) return e;        // d pre(x1)
+    if (int e = launch_wgrad_thin<false>(g, G1, n, h, w, part, grad + OFF_C1, red, s)) return e;
+    return launch_reduce(red, s);
 }
 
 int cnn_loss(const float *p, const float *t, const float *mask, int64_t count, double *L_dev, float *dp, void *ws,
@@ -1157,7 +1202,9 @@ int cnn_conv3x3_wgrad(const uint16_t *dy, const uint16_t *x, int32_t n, int32_t 
     if (!aligned16(dy) || !aligned16(x)) return fail(SG_EINVAL, "dy and x must be 16-byte aligned");
     const CnnLayout L = cnn_layout(1, 1, 1);
     if (ws_bytes < L.total) return fail(SG_EINVAL, "workspace too small (%zu < %zu bytes)", ws_bytes, L.total);
-    return launch_wgrad(dy, x, n, h, w, (float *)((char *)ws + L.part), dw, (hipStream_t)stream);
+    Reduce red;
+    if (int e = launch_wgrad(dy, x, n, h, w, (float *)((char *)ws + L.part), dw, red, (hipStream_t)stream)) return e;
+    return launch_reduce(red, (hipStream_t)stream);
 }
 
 } // extern "C"
