@@ -63,7 +63,7 @@ __device__ __forceinline__ f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c)
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
-// The 6 x 66 halo tile (pixels y0-1 .. y0+4, x0-1 .. x0+64 of image n) straight
+// The 6 x COLS halo tile (pixels y0-1 .. y0+4, x0-1 .. x0+COLS-2 of image n) straight
 // from global memory into LDS, 16 bytes (8 channels) per lane and load: item
 // i = (pixel i / 4, slot i % 4) fills 16-byte slot i, which holds chunk
 // (i % 4) ^ sw(pixel) of the pixel.  The swizzle sw(p) = (p / 4) % 4 puts the
@@ -72,16 +72,17 @@ __device__ __forceinline__ f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c)
 // The caller waits for the loads and synchronises.
 __device__ __forceinline__ int halo_slot(int pix, int q) { return pix * 4 + (q ^ ((pix >> 2) & 3)); }
 
+template <int COLS>
 __device__ __forceinline__ void dma_halo_swizzled(const u16 *__restrict__ x, int n, int H, int W, int y0, int x0,
                                                   unsigned char *lds)
 {
-    constexpr int NV = LH * LW * 4, K = (NV + NT - 1) / NT;
+    constexpr int NV = LH * COLS * 4, K = (NV + NT - 1) / NT;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         const int i = threadIdx.x + k * NT;
         if (i >= NV) continue;
         const int pix = i >> 2, q = (i & 3) ^ ((pix >> 2) & 3);
-        const int rr = pix / LW, c = pix - rr * LW;
+        const int rr = pix / COLS, c = pix - rr * COLS;
         const int y = y0 - 1 + rr, xx = x0 - 1 + c;
         if (y >= 0 && y < H && xx >= 0 && xx < W)
             __builtin_amdgcn_global_load_lds((const void *)(x + (((long long)n * H + y) * W + xx) * CH + q * 8),
@@ -143,7 +144,7 @@ struct ConvArgs {
     int nred;
 };
 
-// grid (ceil(W/64), ceil(H/4), N).  Lane l of a wavefront: r = l % 16 is the
+// grid (ceil(W/(16 MB)), ceil(H/4), N).  Lane l of a wavefront: r = l % 16 is the
 // fragment row (a pixel for A, an output channel for B), g = l / 16 selects
 // the 8 channels 8g .. 8g+7 of the K-block; the accumulator holds output
 // pixels 4g .. 4g+3 of each 16-pixel block for output channel r.  The
@@ -151,7 +152,11 @@ struct ConvArgs {
 // reads and writes 8 channels of a pixel per lane in 16- and 32-byte
 // accesses instead of single 2- and 4-byte elements.
 constexpr int OS = CH + 4;                 // FP32 stride of an output pixel in LDS
-constexpr int CONV_LDS = LH * LW * 64 > 4 * TW * OS * 4 ? LH * LW * 64 : 4 * TW * OS * 4;
+constexpr int conv_lds(int MB)
+{
+    const int in = LH * (16 * MB + 2) * 64, out = 4 * 16 * MB * OS * 4;
+    return in > out ? in : out;
+}
 
 // FRAG: the weights are stored in fragment order, element ((tap * 2 + nb) *
 // 64 + lane) * 8 + e, so that a fragment load is one contiguous KiB (the
@@ -161,10 +166,13 @@ constexpr int CONV_LDS = LH * LW * 64 > 4 * TW * OS * 4 ? LH * LW * 64 : 4 * TW 
 // them contiguous, the residual and gate loaded before the LDS pass and the
 // hardware's BF16 conversion, a launch on 8 x 256^2 pixels went from 33.2 to
 // 22.3 us (3.0 TB/s of activations read and written).
-template <bool FRAG>
+//
+// MB: 16-pixel blocks per wavefront, a tile of 4 x 16 MB pixels.
+template <bool FRAG, int MB>
 __global__ __launch_bounds__(NT) void conv3x3_mfma_kernel(ConvArgs a)
 {
-    __shared__ __attribute__((aligned(16))) unsigned char lds_raw[CONV_LDS];
+    constexpr int TW = 16 * MB, LW = TW + 2;
+    __shared__ __attribute__((aligned(16))) unsigned char lds_raw[conv_lds(MB)];
     u16 *lds = reinterpret_cast<u16 *>(lds_raw);
     if constexpr (FRAG) {
         if ((int)blockIdx.z < a.nred) {
@@ -185,19 +193,19 @@ __global__ __launch_bounds__(NT) void conv3x3_mfma_kernel(ConvArgs a)
             bw[t][nb] = __builtin_bit_cast(bf16x8, *(const u32x4 *)(a.w + (FRAG ? ((t * 2 + nb) * 64 + lane) * 8
                                                                                : ((16 * nb + r) * 9 + t) * CH + 8 * g)));
 
-    dma_halo_swizzled(a.x, n, a.H, a.W, y0, x0, lds_raw);
+    dma_halo_swizzled<LW>(a.x, n, a.H, a.W, y0, x0, lds_raw);
     __builtin_amdgcn_s_waitcnt(0);         // this thread's direct loads have landed in LDS
     __syncthreads();
 
-    f32x4 acc[4][2];
+    f32x4 acc[MB][2];
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb)
+    for (int mb = 0; mb < MB; ++mb)
         acc[mb][0] = acc[mb][1] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int t = 0; t < 9; ++t) {
         const int ky = t / 3, kx = t - 3 * (t / 3);
 #pragma unroll
-        for (int mb = 0; mb < 4; ++mb) {
+        for (int mb = 0; mb < MB; ++mb) {
             const u16 *p = lds + halo_slot((wv + ky) * LW + 16 * mb + r + kx, g) * 8;
             const bf16x8 av = __builtin_bit_cast(bf16x8, *(const u32x4 *)p);
             acc[mb][0] = mfma(av, bw[t][0], acc[mb][0]);
@@ -224,7 +232,7 @@ __global__ __launch_bounds__(NT) void conv3x3_mfma_kernel(ConvArgs a)
     __syncthreads();                       // every wavefront is done with the input tile
     float *orow = reinterpret_cast<float *>(lds_raw) + wv * TW * OS;
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb)
+    for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
         for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
@@ -584,7 +592,7 @@ __global__ __launch_bounds__(NT) void conv_out_kernel(const u16 *__restrict__ x3
     __shared__ __attribute__((aligned(16))) unsigned char lds[LH * LW * 64];
     const int n = blockIdx.z, y0 = blockIdx.y * TH, x0 = blockIdx.x * TW;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    dma_halo_swizzled(x3, n, H, W, y0, x0, lds);
+    dma_halo_swizzled<LW>(x3, n, H, W, y0, x0, lds);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     const int y = y0 + wv, x = x0 + lane;
@@ -971,12 +979,26 @@ int check_dims(int n, int h, int w)
     return SG_OK;
 }
 
+// Tiles 32 instead of 64 pixels wide up to one wide tile per compute unit: there a
+// layer lasts as long as one wavefront's instruction stream, which is half as long.
+// On fuller grids the wider tile's smaller halo counts.  Forward + backward of the network,
+// 64 / 32 wide, us: 1 x 64^2 (16 tiles) 35.5 + 80.3 / 29.5 + 73.3; 1 x 200^2 (200) 40.5 +
+// 99.5 / 38.0 + 98.6; 1 x 256^2 (256) 42.4 + 102.0 / 37.8 + 100.2; 4 x 142^2 (432) 45.6 + 117.0 /
+// 41.3 + 122.7; 3 x 256^2 (768) 59.3 + 152.1 / 61.8 + 151.1; 8 x 256^2 (2048) 112.8 + 259.4 /
+// 123.1 + 262.3.
+bool conv_half(int n, int h, int w)
+{
+    return (long long)((w + TW - 1) / TW) * ((h + TH - 1) / TH) * n <= 256;
+}
+
 template <bool FRAG>
 int launch_conv(const u16 *x, int n, int h, int w, const u16 *wgt, const float *bias, const u16 *res,
                 const u16 *gate, int relu, u16 *y, float *y32, hipStream_t s, const Reduce *red = nullptr)
 {
     ConvArgs a{x, wgt, bias, res, gate, y, y32, n, h, w, relu, {}, 0};
-    dim3 grid((w + TW - 1) / TW, (h + TH - 1) / TH, n);
+    const bool half = conv_half(n, h, w);
+    const int tw = half ? TW / 2 : TW;
+    dim3 grid((w + tw - 1) / tw, (h + TH - 1) / TH, n);
     if (grid.y > 65535u || grid.z > 65535u) return fail(SG_EINVAL, "image batch too large for one launch");
     if (red) {
         const long long slice = (long long)grid.x * grid.y, slices = (red->blocks() + slice - 1) / slice;
@@ -989,7 +1011,8 @@ int launch_conv(const u16 *x, int n, int h, int w, const u16 *wgt, const float *
             HIPCHECK(hipGetLastError());
         }
     }
-    conv3x3_mfma_kernel<FRAG><<<grid, NT, 0, s>>>(a);
+    if (half) conv3x3_mfma_kernel<FRAG, 2><<<grid, NT, 0, s>>>(a);
+    else      conv3x3_mfma_kernel<FRAG, 4><<<grid, NT, 0, s>>>(a);
     HIPCHECK(hipGetLastError());
     return SG_OK;
 }
