@@ -38,7 +38,12 @@
 
 // Multiply-adds are fused only where written as fmaf: whether the compiler
 // would fuse the others depends on the rows per workgroup, and a shot's
-// values must not.
+// values must not.  Where a product is rounded is part of those values: ahead of
+// a wavefront they are differences of denormal numbers, which another rounding
+// changes in their leading digits.  It follows groups of four rows of a 32-row
+// tile: a row's place in its group (0 .. 3) and a half row's (M = 0 .. 6, from two
+// above the first row), whatever rows a thread takes.  Four plane waves on
+// 300x150, 450 steps: 9.84 ms, 9.78 with every product rounded.
 #pragma clang fp contract(off)
 
 namespace sg {
@@ -86,6 +91,26 @@ __device__ __forceinline__ long long fr(const Grid2 &g, int iz, int ix)
 __device__ __forceinline__ float d4(float a, float b, float c, float d)
 {
     return fmaf(S1, c - b, S2 * (d - a));
+}
+
+// The same from the inner difference c - b and the outer one d - a.
+__device__ __forceinline__ float d4(float inner, float outer)
+{
+    return fmaf(S1, inner, S2 * outer);
+}
+
+// Place of a row of the tile in its group of four.
+__device__ __forceinline__ int quad_row(int r) { return r & 3; }
+
+// Outer difference d - a of z fluxes, a = ka sa and d = kd sd: in a tile away from
+// the layer (whole), a group's first row takes the product a unrounded and its last row
+// the product d.
+__device__ __forceinline__ float outer(bool whole, int row, float a, float ka, float sa, float d, float kd, float sd)
+{
+    float o = d - a;
+    if (whole && row == 0) o = fmaf(-ka, sa, d);
+    if (whole && row == 3) o = fmaf(kd, sd, -a);
+    return o;
 }
 
 // Consecutive work ids on one XCD (workgroups are dealt to the 8 XCDs
@@ -283,6 +308,7 @@ __device__ __forceinline__ void fwd_tile(const Ad2FwdArgs &a, float *su, float *
     const float *u = a.u + so;
     const float *ch = a.chat + (long long)(shot / a.shots_per_model) * g.plane;
     const int tid = threadIdx.x, lx = tid % TX, ly = __builtin_amdgcn_readfirstlane(tid / TX), r0 = ly * RPA, ix = x0 + lx;
+    const bool whole = !NEAR && !near_edge<TZ>(g, x0, z0 - o.sub * RW);
 
     // u^k on the tile + 3 straight from global memory into LDS: 4 bytes per
     // lane and load into consecutive LDS words (item order is the row-major
@@ -340,7 +366,7 @@ __device__ __forceinline__ void fwd_tile(const Ad2FwdArgs &a, float *su, float *
         float uz[RPA + 6];
 #pragma unroll
         for (int m = 0; m < RPA + 6; ++m) uz[m] = su[(r0 + m) * AW + lx + AH];
-        float qz[RPA + 3];
+        float qz[RPA + 3], kz[RPA + 3], sz[RPA + 3];      // the fluxes and their factors
 #pragma unroll
         for (int m = 0; m < RPA + 3; ++m) {
             const int iz = z0 + r0 - 2 + m;
@@ -358,14 +384,18 @@ __device__ __forceinline__ void fwd_tile(const Ad2FwdArgs &a, float *su, float *
                 if constexpr (SNAP) {
                     if (own) __builtin_nontemporal_store(S, a.snz + so + f);
                 }
-                q = 0.5f * (cz[m] + cz[m + 1]) * S;
+                kz[m] = 0.5f * (cz[m] + cz[m + 1]);
+                sz[m] = S;
+                q = kz[m] * S;
             }
             qz[m] = q;
         }
 #pragma unroll
         for (int j = 0; j < RPA; ++j) {
             uc[j] = uz[j + 3];
-            hz[j] = d4(qz[j], qz[j + 1], qz[j + 2], qz[j + 3]);
+            if constexpr (NEAR) hz[j] = d4(qz[j], qz[j + 1], qz[j + 2], qz[j + 3]);
+            else hz[j] = d4(qz[j + 2] - qz[j + 1], outer(whole, quad_row(r0 + j), qz[j], kz[j], sz[j], qz[j + 3],
+                                                         kz[j + 3], sz[j + 3]));
         }
     }
 #pragma unroll
@@ -386,7 +416,7 @@ __device__ __forceinline__ void fwd_tile(const Ad2FwdArgs &a, float *su, float *
 
     if (src.any()) {                      // uniform over the block
         gather_entries<RW>(su, a.src_ent, src, o.sub, [](int e) { return src_cell(e); }, sample,
-                           [&](float v, float x) { return v + a.src_scale * x; });
+                           [&](float v, float x) { return fmaf(a.src_scale, x, v); });
     }
     float un[RPA];
 #pragma unroll
@@ -466,7 +496,7 @@ __device__ __forceinline__ float adj_xflux(const Ad2AdjArgs &a, const float *hx,
         Gb = Sb;
         if constexpr (NEAR) {
             const float z = fmaf(ah, Sb, bh * z0v);
-            Gb = Sb + z;
+            Gb = !GRAD || (h >= 2 && h < TX + 2) ? fmaf(0.5f * (c0 + c1), qb, z) : Sb + z;
             if (own) a.zxn[so + f] = z;
         }
         if constexpr (GRAD) {
@@ -487,6 +517,7 @@ __device__ __forceinline__ void adj_tile(const Ad2AdjArgs &a, float *hx, float *
     const float *l1 = a.l1 + so;
     const float *ch = a.chat + (long long)(shot / a.shots_per_model) * g.plane;
     const int tid = threadIdx.x, lx = tid % TX, ly = __builtin_amdgcn_readfirstlane(tid / TX), r0 = ly * RPA, ix = x0 + lx;
+    const bool whole = !NEAR && !near_edge<TZ>(g, x0, z0 - o.sub * RW);
 
     // Hb = lambda^{k+1} + Y^{k+1} per axis on the tile and its halo
     if constexpr (!NEAR) {
@@ -612,7 +643,7 @@ __device__ __forceinline__ void adj_tile(const Ad2AdjArgs &a, float *hx, float *
         float hc[RPA + 6];
 #pragma unroll
         for (int m = 0; m < RPA + 6; ++m) hc[m] = hzz[(r0 + m) * AW + lx + AH];
-        float gz[RPA + 3], pz[RPA + 3];
+        float gz[RPA + 3], pz[RPA + 3], kz[RPA + 3], qz[RPA + 3];
 #pragma unroll
         for (int m = 0; m < RPA + 3; ++m) {
             const int iz = z0 + r0 - 2 + m;
@@ -622,11 +653,14 @@ __device__ __forceinline__ void adj_tile(const Ad2AdjArgs &a, float *hx, float *
             if (!NEAR || (iz >= 0 && iz < g.NZ)) {
                 const long long f = fr(g, iz, ix);
                 const bool own = m >= 2 && m < RPA + 2 && ix < g.NX;
-                const float Sb = 0.5f * (cz[m] + cz[m + 1]) * qb;
+                kz[m] = 0.5f * (cz[m] + cz[m + 1]);
+                qz[m] = qb;
+                const float Sb = kz[m] * qb;
                 Gb = Sb;
                 if constexpr (NEAR) {
                     const float z = fmaf(co.ahz(a.t, m, iz), Sb, co.bhz(a.t, m, iz) * zz0[m]);
-                    Gb = Sb + z;
+                    const int M = quad_row(r0) + m;
+                    Gb = !GRAD || M < 2 || M == 6 ? fmaf(kz[m], qb, z) : Sb + z;
                     if (own) a.zzn[so + f] = z;
                 }
                 if constexpr (GRAD) {
@@ -639,9 +673,16 @@ __device__ __forceinline__ void adj_tile(const Ad2AdjArgs &a, float *hx, float *
         for (int j = 0; j < RPA; ++j) {
             const int iz = z0 + r0 + j;
             if constexpr (!NEAR) lc[j] = hc[j + 3];
-            dz[j] = d4(gz[j], gz[j + 1], gz[j + 2], gz[j + 3]);
-            gnz[j] = 0.5f * (pz[j + 1] + pz[j + 2]);
-            if (iz == g.NZ - 1) gnz[j] += 0.5f * pz[j + 2];
+            if constexpr (NEAR) dz[j] = d4(gz[j], gz[j + 1], gz[j + 2], gz[j + 3]);
+            else dz[j] = d4(gz[j + 2] - gz[j + 1], outer(whole, quad_row(r0 + j), gz[j], kz[j], qz[j], gz[j + 3],
+                                                         kz[j + 3], qz[j + 3]));
+            float pp = pz[j + 1] + pz[j + 2];
+            if constexpr (!NEAR && GRAD) {
+                if (whole && quad_row(r0 + j) == 0) pp = fmaf(qz[j + 1], sz0[j + 1], pz[j + 2]);
+                if (whole && quad_row(r0 + j) == 3) pp = fmaf(qz[j + 2], sz0[j + 2], pz[j + 1]);
+            }
+            gnz[j] = 0.5f * pp;
+            if (iz == g.NZ - 1) gnz[j] = fmaf(0.5f, pz[j + 2], gnz[j]);
         }
     }
     float px[RPA];                        // x products at the own half column
@@ -680,8 +721,8 @@ __device__ __forceinline__ void adj_tile(const Ad2AdjArgs &a, float *hx, float *
         if constexpr (GRAD) {
             float left = __shfl_up(px[j], 1, TX);
             if (lx == 0) left = pl[r];
-            gn = 0.5f * (left + px[j]) + gnz[j];
-            if (ix == g.NX - 1) gn += 0.5f * px[j];
+            gn = fmaf(0.5f, left + px[j], gnz[j]);
+            if (ix == g.NX - 1) gn = fmaf(0.5f, px[j], gn);
         }
         if (iz < g.NZ && ix < g.NX) {
             const long long f = fr(g, iz, ix);
