@@ -42,8 +42,9 @@
 // a wavefront they are differences of denormal numbers, which another rounding
 // changes in their leading digits.  It follows groups of four rows of a 32-row
 // tile: a row's place in its group (0 .. 3) and a half row's (M = 0 .. 6, from two
-// above the first row), whatever rows a thread takes.  Four plane waves on
-// 300x150, 450 steps: 9.84 ms, 9.78 with every product rounded.
+// above the first row), whatever rows a thread takes.  1000x500, 64 shots, against
+// every product rounded: forward 247 -> 251 us, recompute 272 -> 274, adjoint 362 ->
+// 365.
 #pragma clang fp contract(off)
 
 namespace sg {
@@ -99,17 +100,14 @@ __device__ __forceinline__ float d4(float inner, float outer)
     return fmaf(S1, inner, S2 * outer);
 }
 
-// Place of a row of the tile in its group of four.
-__device__ __forceinline__ int quad_row(int r) { return r & 3; }
-
 // Outer difference d - a of z fluxes, a = ka sa and d = kd sd: in a tile away from
-// the layer (whole), a group's first row takes the product a unrounded and its last row
-// the product d.
-__device__ __forceinline__ float outer(bool whole, int row, float a, float ka, float sa, float d, float kd, float sd)
+// the layer, a group's first row (0) takes the product a unrounded and its last row (3) the
+// product d.
+__device__ __forceinline__ float outer(int row, float a, float ka, float sa, float d, float kd, float sd)
 {
     float o = d - a;
-    if (whole && row == 0) o = fmaf(-ka, sa, d);
-    if (whole && row == 3) o = fmaf(kd, sd, -a);
+    if (row == 0) o = fmaf(-ka, sa, d);
+    if (row == 3) o = fmaf(kd, sd, -a);
     return o;
 }
 
@@ -126,9 +124,14 @@ __device__ __forceinline__ int xcd_id(int nblocks)
 // Does the tile or its 3-node halo reach the absorbing layer or the edge of
 // the grid (layer memories, masks of the half-node range)?
 template <int RW>
+__device__ __forceinline__ bool near_edge_z(const Grid2 &g, int z0)
+{
+    return z0 - AH < g.P || z0 + RW + AH > g.P + g.nz;
+}
+template <int RW>
 __device__ __forceinline__ bool near_edge(const Grid2 &g, int x0, int z0)
 {
-    return x0 - AH < g.P || x0 + TX + AH > g.P + g.nx || z0 - AH < g.P || z0 + RW + AH > g.P + g.nz;
+    return x0 - AH < g.P || x0 + TX + AH > g.P + g.nx || near_edge_z<RW>(g, z0);
 }
 
 // RW rows (sub) of a tile.
@@ -308,7 +311,6 @@ __device__ __forceinline__ void fwd_tile(const Ad2FwdArgs &a, float *su, float *
     const float *u = a.u + so;
     const float *ch = a.chat + (long long)(shot / a.shots_per_model) * g.plane;
     const int tid = threadIdx.x, lx = tid % TX, ly = __builtin_amdgcn_readfirstlane(tid / TX), r0 = ly * RPA, ix = x0 + lx;
-    const bool whole = !NEAR && !near_edge<TZ>(g, x0, z0 - o.sub * RW);
 
     // u^k on the tile + 3 straight from global memory into LDS: 4 bytes per
     // lane and load into consecutive LDS words (item order is the row-major
@@ -360,6 +362,10 @@ __device__ __forceinline__ void fwd_tile(const Ad2FwdArgs &a, float *su, float *
     __builtin_amdgcn_s_waitcnt(0);       // the tile's direct loads have landed in LDS
     __syncthreads();
 
+    // place in its group of the thread's first row; none (8) in a tile that the layer reaches elsewhere
+    // (found here, not at the top: 1000x500, 64 shots, forward 251 against 262 us, adjoint 365 against 367)
+    const bool whole = !NEAR && !near_edge_z<TZ>(g, z0 - o.sub * RW);
+    const int quad = __builtin_amdgcn_readfirstlane(whole || NEAR ? r0 & 3 : 8);
     // z fluxes of the own column at half rows z0+r0-2+m, m = 0 .. RPA+2
     float uc[RPA], hz[RPA];
     {
@@ -394,7 +400,7 @@ __device__ __forceinline__ void fwd_tile(const Ad2FwdArgs &a, float *su, float *
         for (int j = 0; j < RPA; ++j) {
             uc[j] = uz[j + 3];
             if constexpr (NEAR) hz[j] = d4(qz[j], qz[j + 1], qz[j + 2], qz[j + 3]);
-            else hz[j] = d4(qz[j + 2] - qz[j + 1], outer(whole, quad_row(r0 + j), qz[j], kz[j], sz[j], qz[j + 3],
+            else hz[j] = d4(qz[j + 2] - qz[j + 1], outer(quad + j, qz[j], kz[j], sz[j], qz[j + 3],
                                                          kz[j + 3], sz[j + 3]));
         }
     }
@@ -517,7 +523,6 @@ __device__ __forceinline__ void adj_tile(const Ad2AdjArgs &a, float *hx, float *
     const float *l1 = a.l1 + so;
     const float *ch = a.chat + (long long)(shot / a.shots_per_model) * g.plane;
     const int tid = threadIdx.x, lx = tid % TX, ly = __builtin_amdgcn_readfirstlane(tid / TX), r0 = ly * RPA, ix = x0 + lx;
-    const bool whole = !NEAR && !near_edge<TZ>(g, x0, z0 - o.sub * RW);
 
     // Hb = lambda^{k+1} + Y^{k+1} per axis on the tile and its halo
     if constexpr (!NEAR) {
@@ -638,6 +643,9 @@ __device__ __forceinline__ void adj_tile(const Ad2AdjArgs &a, float *hx, float *
     __syncthreads();
     const float *hzz = NEAR ? hz : hx;
 
+    // place in its group of the thread's first row; none (8) in a tile that the layer reaches elsewhere
+    const bool whole = !NEAR && !near_edge_z<TZ>(g, z0 - o.sub * RW);
+    const int quad = __builtin_amdgcn_readfirstlane(whole || NEAR ? r0 & 3 : 8);
     float dz[RPA], gnz[RPA];              // Dm' Gb_z and the z gradient of the own rows
     {
         float hc[RPA + 6];
@@ -659,7 +667,7 @@ __device__ __forceinline__ void adj_tile(const Ad2AdjArgs &a, float *hx, float *
                 Gb = Sb;
                 if constexpr (NEAR) {
                     const float z = fmaf(co.ahz(a.t, m, iz), Sb, co.bhz(a.t, m, iz) * zz0[m]);
-                    const int M = quad_row(r0) + m;
+                    const int M = quad + m;
                     Gb = !GRAD || M < 2 || M == 6 ? fmaf(kz[m], qb, z) : Sb + z;
                     if (own) a.zzn[so + f] = z;
                 }
@@ -674,12 +682,12 @@ __device__ __forceinline__ void adj_tile(const Ad2AdjArgs &a, float *hx, float *
             const int iz = z0 + r0 + j;
             if constexpr (!NEAR) lc[j] = hc[j + 3];
             if constexpr (NEAR) dz[j] = d4(gz[j], gz[j + 1], gz[j + 2], gz[j + 3]);
-            else dz[j] = d4(gz[j + 2] - gz[j + 1], outer(whole, quad_row(r0 + j), gz[j], kz[j], qz[j], gz[j + 3],
+            else dz[j] = d4(gz[j + 2] - gz[j + 1], outer(quad + j, gz[j], kz[j], qz[j], gz[j + 3],
                                                          kz[j + 3], qz[j + 3]));
             float pp = pz[j + 1] + pz[j + 2];
             if constexpr (!NEAR && GRAD) {
-                if (whole && quad_row(r0 + j) == 0) pp = fmaf(qz[j + 1], sz0[j + 1], pz[j + 2]);
-                if (whole && quad_row(r0 + j) == 3) pp = fmaf(qz[j + 2], sz0[j + 2], pz[j + 1]);
+                if (quad + j == 0) pp = fmaf(qz[j + 1], sz0[j + 1], pz[j + 2]);
+                if (quad + j == 3) pp = fmaf(qz[j + 2], sz0[j + 2], pz[j + 1]);
             }
             gnz[j] = 0.5f * pp;
             if (iz == g.NZ - 1) gnz[j] = fmaf(0.5f, pz[j + 2], gnz[j]);
