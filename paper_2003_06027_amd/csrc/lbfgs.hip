@@ -12,6 +12,8 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstdint>
+#include <initializer_list>
 
 using sg::fail;
 
@@ -52,7 +54,7 @@ __device__ __forceinline__ double get_f64(const float *p)
 // elements took ten memory latencies (20 models, 4 at a time 8.0 us, 10 7.8).  ONE: one workgroup per model, which
 // writes the sums.  Otherwise nb workgroups per model leave their two partial
 // sums in the first 4 nb elements of the stored y, which lbfgs_pair_kernel
-// adds up and then replaces by the elements.
+// adds up and then replaces by the elements (so the inputs may not lie in S or Y).
 template <bool ONE>
 __global__ __launch_bounds__(LB_THREADS) void lbfgs_push_kernel(int nmodels, long long n, int mem, int nb,
                                                                 const int *slot, const float *m_new,
@@ -396,6 +398,12 @@ __global__ __launch_bounds__(LB_THREADS) void lbfgs_direction_kernel(int nmodels
     for (long long i = threadIdx.x; i < n; i += LB_THREADS) q[i] = -q[i];
 }
 
+// Do n floats at a and m at b share memory?
+bool overlap(const float *a, long long n, const float *b, long long m)
+{
+    return (uintptr_t)a < (uintptr_t)(b + m) && (uintptr_t)b < (uintptr_t)(a + n);
+}
+
 } // namespace
 
 extern "C" {
@@ -410,8 +418,14 @@ int lbfgs_push(int32_t nmodels, int64_t n, int32_t mem, const int32_t *slot, con
         return fail(SG_EINVAL, "NULL pointer argument");
     hipStream_t st = (hipStream_t)stream;
     // short vectors: one workgroup per model forms the pair and its sums
-    // (10201 elements: two launches would cost more than they spread)
-    if (n <= 16 * LB_THREADS || nmodels > (1 << 20)) {
+    // (10201 elements: two launches would cost more than they spread).  So do pairs
+    // formed in place, in an S or Y that holds one of the inputs: the partial sums
+    // of several workgroups and their replacement would read what they have overwritten.
+    bool in_place = false;
+    for (const float *in : {m_new, m_old, g_new, g_old})
+        for (const float *out : {S, Y})
+            in_place |= overlap(in, (long long)nmodels * n, out, (long long)mem * nmodels * n);
+    if (n <= 16 * LB_THREADS || nmodels > (1 << 20) || in_place) {
         lbfgs_push_kernel<true><<<nmodels, LB_THREADS, 0, st>>>(nmodels, n, mem, 1, slot, m_new, m_old, g_new, g_old,
                                                                 S, Y, ysyy);
     } else {
