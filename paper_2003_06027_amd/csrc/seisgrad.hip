@@ -73,7 +73,7 @@ struct Layout {
                        // auxiliaries over 2 pairs)
     size_t off_chat, off_cpad, off_tab, off_fwd, off_adj, off_ckpt, off_snap,
         off_grad, off_src, off_recoff, off_recent, off_part, off_tmp, off_acc, off_uoff, off_uid, off_mt,
-        off_tiles, off_soff, off_sent, off_nodef, off_items, off_flag, total;
+        off_tiles, off_soff, off_sent, off_nodef, off_items, off_flag, off_range, total;
 };
 
 int check_desc(const sg_desc *d)
@@ -223,7 +223,8 @@ Layout make_layout(const sg_desc *d, int max_shots, int max_rec, int ckpt)
     L.off_sent = take(sizeof(int) * (size_t)max_shots * SG_MAX_SRC);
     L.off_nodef = take(sizeof(long long) * (size_t)max_shots * SG_MAX_SRC);
     L.off_items = take(L.ndim == 3 ? sizeof(int4) * 2 * items3_cap(L.ntiles, L.g3.NZ) : 0);
-    L.off_flag = take(sizeof(int));
+    L.off_flag = take(2 * sizeof(int) + sizeof(ParamRange));   // the numeric flag, then the parameters' range
+    L.off_range = L.off_flag + 2 * sizeof(int);
     L.total = o;
     return L;
 }
@@ -1319,9 +1320,8 @@ int init_model(const sg_desc *d, const float *vp, const float *vs, const float *
     if ((uintptr_t)ws % ALIGN) return fail(SG_EINVAL, "workspace must be %zu-byte aligned", ALIGN);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
 
-    // the range goes through the misfit's partial sums, which hold nothing between calls
     if (const int e = check_velocities(d, L, vp, vs, rho,
-                                       reinterpret_cast<ParamRange *>(static_cast<char *>(ws) + L.off_part), s))
+                                       reinterpret_cast<ParamRange *>(static_cast<char *>(ws) + L.off_range), s))
         return e;
     const double zmax = d->npml > 0 ? 3.0 * d->pml_vmax * std::log(1.0 / d->pml_R) / (2.0 * d->npml * d->dx) : 0.0;
 
@@ -1506,7 +1506,8 @@ int update_model(sg_model *m, const float *vp, const float *vs, const float *rho
     if (elastic && (!vs || !rho)) return fail(SG_EINVAL, "elastic models need vs and rho");
     if (!vp) return fail(SG_EINVAL, "vp must be a device pointer");
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    if (const int e = check_velocities(d, L, vp, vs, rho, reinterpret_cast<ParamRange *>(m->partials), s)) return e;
+    // (a slot of its own: a misfit of this model may be running on another stream)
+    if (const int e = check_velocities(d, L, vp, vs, rho, reinterpret_cast<ParamRange *>(m->ws + L.off_range), s)) return e;
     if (elastic) launch_el2_prep(L.g2, d->nmodels, vp, vs, rho, m->model, m->model + 5, s);
     else if (L.ad2) launch_ad2_prep(L.g2, d->nmodels, vp, d->dt, d->dx, m->chat, m->cpad, s);
     else if (d->ndim == 2) launch_ac2_prep(L.g2, d->nmodels, vp, d->dt, d->dx, m->chat, m->cpad, s);
