@@ -284,9 +284,9 @@ SG_API int set_time_blocking(sg_model *m, int32_t steps);
  *   SG_TUNE_CHUNK_FWD3     planes per z chunk of the 3-D forward tile passes;
  *   SG_TUNE_CHUNK_ADJ3     planes per z chunk of the 3-D adjoint tile passes;
  *   SG_TUNE_CHUNK_LAYER3   planes per work item of the 3-D layer passes
- *                          (3-D chunks: 16 to 64, multiples of 8; until set,
- *                          32 and 64 in the tile passes, shorter on grids
- *                          of few tiles, and 16);
+ *                          (3-D chunks: 16 to 64, multiples of 8, or 0, the
+ *                          default: 32 and 64 in the tile passes, shorter on
+ *                          grids of few tiles, and 16);
  *   SG_TUNE_PAIR           2-D acoustic: 1 (the default) launches what a
  *                          step computes (the tiles by the layer, the other
  *                          one-step tiles, the blocked tiles) as one grid

@@ -1758,13 +1758,15 @@ int set_tuning(sg_model *m, int32_t key, int32_t value, sg_stream_t stream)
     case SG_TUNE_CHUNK_ADJ3:
     case SG_TUNE_CHUNK_LAYER3: {
         if (!three) return fail(SG_EINVAL, "3-D chunk lengths apply to 3-D acoustic models");
-        if (value < TZC_MIN || value > TZC || value % 8)
-            return fail(SG_EINVAL, "chunk of %d planes outside [%d, %d] or not a multiple of 8", value, TZC_MIN, TZC);
+        if (value != 0 && (value < TZC_MIN || value > TZC || value % 8))
+            return fail(SG_EINVAL, "chunk of %d planes: 0 (the library's rule), or %d to %d and a multiple of 8", value,
+                        TZC_MIN, TZC);
         Grid3 &g = m->L.g3;
-        if (key == SG_TUNE_CHUNK_FWD3) g.zcf = value;
+        if (key == SG_TUNE_CHUNK_FWD3) g.zcf = value;      // 0: chunk3's rule
         if (key == SG_TUNE_CHUNK_ADJ3) g.zca = value;
-        if (key == SG_TUNE_CHUNK_LAYER3 && m->items3 && value != m->zci) {
-            if (build_items3(m, value)) return fail(SG_EINVAL, "layer work list overflows its buffer");
+        const int items = value ? value : TZCI_DEF;
+        if (key == SG_TUNE_CHUNK_LAYER3 && m->items3 && items != m->zci) {
+            if (build_items3(m, items)) return fail(SG_EINVAL, "layer work list overflows its buffer");
             // the list is read by launches already enqueued: wait for them first
             hipStream_t s = reinterpret_cast<hipStream_t>(stream);
             HIPCHECK(hipStreamSynchronize(s));

@@ -6,10 +6,10 @@ Candidates (none changes what is computed; see set_tuning in the C ABI):
   bitwise identical, traffic and launch count differ), each eager or with
   the library's segment graphs (one HIP graph per checkpoint segment of the
   forward and of the adjoint sweep, captured once and replayed);
-* 3-D acoustic: the z-chunk lengths of the forward tile passes (16-64
-  planes), of the adjoint tile passes (32-64) and of the layer work items
-  (16-64), searched one at a time from the defaults (each moves different
-  kernels);
+* 3-D acoustic: the z-chunk lengths of the forward tile passes (the library's
+  rule or 16-64 planes), of the adjoint tile passes (the rule or 32-64) and of
+  the layer work items (the library's 16, or 32-64), searched one at a time
+  from the defaults (each moves different kernels);
 * 2-D elastic: shots of one model per thread (4, 2 or 1, those dividing the
   shots per model) and cell blocks of 32 x 8 or 64 x 4;
 * every physics: eager launches or graph replay.
@@ -42,9 +42,9 @@ GRAPH_MARGIN = 0.02
 class Strategy:
     time_blocking: int = 2     # 2-D acoustic
     graphs: bool = False
-    chunk_fwd3: int = 32       # 3-D acoustic
-    chunk_adj3: int = 64
-    chunk_layer3: int = 32
+    chunk_fwd3: int = 0        # 3-D acoustic (0: the library's rule)
+    chunk_adj3: int = 0
+    chunk_layer3: int = 0
     shot_group: int = 0        # elastic (0: the library's rule)
     block_x: int = 32
 
@@ -89,13 +89,13 @@ def candidates(d, nshots=1):
         groups = [gs for gs in (4, 2, 1) if spm % gs == 0]
         return [Strategy(shot_group=gs, block_x=bx) for gs in groups for bx in (32, 64)] + [Strategy(graphs=True)]
     if d.ndim == 3:
-        return [Strategy(chunk_fwd3=c) for c in (16, 32, 48, 64)]
+        return [Strategy(chunk_fwd3=c) for c in (0, 16, 32, 48, 64)]
     return [Strategy(), Strategy(graphs=True)]
 
 
 # 3-D coordinate search after the forward chunk: the adjoint chunk, then the layer items
-CHUNKS_ADJ3 = (32, 48, 64)
-CHUNKS_LAYER3 = (16, 32, 64)
+CHUNKS_ADJ3 = (0, 32, 48, 64)
+CHUNKS_LAYER3 = (0, 32, 64)
 
 
 class Runner:
