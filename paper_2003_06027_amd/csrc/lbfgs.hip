@@ -22,6 +22,7 @@ namespace {
 constexpr int LB_THREADS = 1024;
 constexpr int LB_MAXMEM = 64;
 constexpr int LB_CHUNKS = 256;   // workgroups per model of the partial sums, at most
+constexpr long long MAX_THREADS = (1ll << 32) - 1;   // of a launch's grid
 static_assert(LB_CHUNKS <= LB_THREADS && 4 * LB_CHUNKS <= 16 * LB_THREADS, "partial sums fit");
 
 // Sum of one double per thread in a fixed order (wavefront tree, then the
@@ -425,11 +426,11 @@ int lbfgs_push(int32_t nmodels, int64_t n, int32_t mem, const int32_t *slot, con
     for (const float *in : {m_new, m_old, g_new, g_old})
         for (const float *out : {S, Y})
             in_place |= overlap(in, (long long)nmodels * n, out, (long long)mem * nmodels * n);
-    if (n <= 16 * LB_THREADS || nmodels > (1 << 20) || in_place) {
+    const int nb = (int)std::min<long long>((n + 4 * LB_THREADS - 1) / (4 * LB_THREADS), LB_CHUNKS);
+    if (n <= 16 * LB_THREADS || (long long)nmodels * nb * LB_THREADS > MAX_THREADS || in_place) {
         lbfgs_push_kernel<true><<<nmodels, LB_THREADS, 0, st>>>(nmodels, n, mem, 1, slot, m_new, m_old, g_new, g_old,
                                                                 S, Y, ysyy);
     } else {
-        const int nb = (int)std::min<long long>((n + 4 * LB_THREADS - 1) / (4 * LB_THREADS), LB_CHUNKS);
         lbfgs_push_kernel<false><<<nmodels * nb, LB_THREADS, 0, st>>>(nmodels, n, mem, nb, slot, m_new, m_old, g_new,
                                                                       g_old, S, Y, ysyy);
         lbfgs_pair_kernel<<<nmodels, LB_THREADS, 0, st>>>(nmodels, n, mem, nb, slot, g_new, g_old, Y, ysyy);
@@ -452,11 +453,11 @@ int lbfgs_direction(int32_t nmodels, int64_t n, int32_t mem, const int32_t *hist
     // direction, loop / products: 2500 elements, 5 pairs 27.2 / 28.3 us; 1000, 8
     // 31.9 / 27.4; 6000, 5 38.8 / 28.7; both launches near the host's rate).
     const int per = 2 * lb_dots(std::min<int>(mem, LB_CMAX));     // floats of a chunk's partial sums
-    if (mem <= LB_CMAX && n >= LB_HEAD + 2 * per && mem * (n + 3000) >= 30000 && nmodels <= (1 << 20)) {
-        const long long room = std::min<long long>((n - LB_HEAD) / per, LB_CHUNKS);
-        const long long want = std::min<long long>((n + LB_SUB - 1) / LB_SUB, room);
-        const long long chunk = ((n + want - 1) / want + LB_SUB - 1) / LB_SUB * LB_SUB;
-        const int nchunks = (int)((n + chunk - 1) / chunk);
+    const bool room = mem <= LB_CMAX && n >= LB_HEAD + 2 * per && mem * (n + 3000) >= 30000;
+    const long long want = room ? std::min<long long>({(n + LB_SUB - 1) / LB_SUB, (n - LB_HEAD) / per, LB_CHUNKS}) : 1;
+    const long long chunk = ((n + want - 1) / want + LB_SUB - 1) / LB_SUB * LB_SUB;
+    const int nchunks = (int)((n + chunk - 1) / chunk);
+    if (room && (long long)nmodels * std::max(nchunks * LB_GT, LB_THREADS) <= MAX_THREADS) {
         if (mem <= 8)
             lbfgs_products_kernel<1><<<nmodels * nchunks, LB_GT, 0, st>>>(nmodels, n, mem, nchunks, chunk, hist, S, Y, g, p);
         else
