@@ -14,6 +14,7 @@
 #include <algorithm>
 #include <cstdint>
 #include <initializer_list>
+#include <type_traits>
 
 using sg::fail;
 
@@ -22,20 +23,56 @@ namespace {
 constexpr int LB_THREADS = 1024;
 constexpr int LB_MAXMEM = 64;
 constexpr int LB_CHUNKS = 256;   // workgroups per model of the partial sums, at most
+constexpr int PUSH_ONE = 24 * LB_THREADS;   // elements up to which one workgroup forms a pair
 constexpr long long MAX_THREADS = (1ll << 32) - 1;   // of a launch's grid
-static_assert(LB_CHUNKS <= LB_THREADS && 4 * LB_CHUNKS <= 16 * LB_THREADS, "partial sums fit");
+static_assert(LB_CHUNKS <= LB_THREADS && 4 * LB_CHUNKS <= PUSH_ONE, "partial sums fit");
 
-// Sum of one double per thread in a fixed order (wavefront tree, then the
-// wavefronts in turn); every thread gets it.
-__device__ double block_sum(double v, double *red)
+// v of another lane of the wavefront (DPP control CTRL), 0 where there is none
+// or the row of 16 lanes is not in the mask ROWS.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp(double v)
 {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    const long long u = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)u, CTRL, ROWS, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(u >> 32), CTRL, ROWS, 0xf, true);
+    return __longlong_as_double((long long)(unsigned)lo | (long long)hi << 32);
+}
+__device__ __forceinline__ double lane_of(double v, int l)
+{
+    const long long u = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)u, l), hi = __builtin_amdgcn_readlane((int)(u >> 32), l);
+    return __longlong_as_double((long long)(unsigned)lo | (long long)hi << 32);
+}
+// Sum over a row of 16 lanes, in its last lane.
+__device__ __forceinline__ double row_sum(double v)
+{
+    v += dpp<0x111, 0xf>(v);               // row_shr 1, 2, 4, 8
+    v += dpp<0x112, 0xf>(v);
+    v += dpp<0x114, 0xf>(v);
+    return v + dpp<0x118, 0xf>(v);
+}
+
+// Sums of N doubles per thread of a workgroup of LB_THREADS in a fixed order;
+// every thread gets them.  One barrier: another must follow before red is used
+// again.  (Lanes are added by DPP, off the LDS pipe: with a shuffle per step
+// and every thread adding up the 16 wavefronts, 2000 models of 500 elements
+// took 94 us for a direction of 5 pairs, with a tree in LDS 80, now 56.)
+template <int N>
+__device__ __forceinline__ void block_sums(double (&v)[N], double (*red)[LB_THREADS / 64])
+{
+    static_assert(LB_THREADS / 64 == 16 && N <= 4, "a row of lanes holds the wavefronts' sums");
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        double t = row_sum(v[k]);
+        t += dpp<0x142, 0xa>(t);           // row_bcast 15: row 0 into 1, 2 into 3
+        t += dpp<0x143, 0xc>(t);           // row_bcast 31: rows 0 and 1 into 2 and 3
+        if (lane == 63) red[k][threadIdx.x >> 6] = t;
+    }
     __syncthreads();
-    double r = 0.0;
-    for (int i = 0; i < LB_THREADS / 64; ++i) r += red[i];
-    __syncthreads();
-    return r;
+    const double t = row_sum(lane < 16 * N ? red[lane >> 4][lane & 15] : 0.0);
+#pragma unroll
+    for (int k = 0; k < N; ++k) v[k] = lane_of(t, 16 * k + 15);
 }
 
 // A model's vectors are only 4-byte aligned (n may be odd): doubles in two words.
@@ -51,8 +88,9 @@ __device__ __forceinline__ double get_f64(const float *p)
 }
 
 // s, y of the models that store a pair, and their sums (y.s, y.y).  Elements
-// are loaded NL at a time: with one in flight per thread a model of 10201
-// elements took ten memory latencies (20 models, 4 at a time 8.0 us, 10 7.8).  ONE: one workgroup per model, which
+// are loaded NL at a time, the last ones as far as there are any (with ten loads
+// per thread whatever n is, clamped to the last element, 2000 models of 500 elements
+// took 24 us, one element at a time 12, now 7.6; 20 of 10201, from memory, 9.5 / 9.8 / 8.4).  ONE: one workgroup per model, which
 // writes the sums.  Otherwise nb workgroups per model leave their two partial
 // sums in the first 4 nb elements of the stored y, which lbfgs_pair_kernel
 // adds up and then replaces by the elements (so the inputs may not lie in S or Y).
@@ -62,42 +100,48 @@ __global__ __launch_bounds__(LB_THREADS) void lbfgs_push_kernel(int nmodels, lon
                                                                 const float *m_old, const float *g_new,
                                                                 const float *g_old, float *S, float *Y, double *ysyy)
 {
-    constexpr int NL = ONE ? 10 : 4;
-    __shared__ double red[LB_THREADS / 64];
-    const int b = blockIdx.x / nb, blk = blockIdx.x - b * nb;
+    constexpr int NL = 4;
+    __shared__ double red[2][LB_THREADS / 64];
+    const int b = ONE ? blockIdx.x : blockIdx.x / nb, blk = ONE ? 0 : blockIdx.x - b * nb;
     const int k = slot[b];
     if (k < 0 || k >= mem) return;                 // this model keeps its history unchanged
-    const long long o = (long long)b * n;
+    const long long o = (long long)b * n, step = (ONE ? 1 : nb) * (long long)(NL * LB_THREADS);
     float *s = S + ((long long)k * nmodels + b) * n, *y = Y + ((long long)k * nmodels + b) * n;
-    double ys = 0.0, yy = 0.0;
-    for (long long i0 = blk * (long long)(NL * LB_THREADS) + threadIdx.x; i0 < n;
-         i0 += nb * (long long)(NL * LB_THREADS)) {
+    double sum[2] = {0.0, 0.0};
+    // NL elements from i0 on, or (TAIL) those of them below n
+    auto run = [&](long long i0, auto TAIL) {
+        constexpr bool tail = decltype(TAIL)::value;
         float mn[NL], mo[NL], gn[NL], go[NL];
 #pragma unroll
         for (int j = 0; j < NL; ++j) {
-            const long long i = min(i0 + j * LB_THREADS, n - 1);
-            mn[j] = m_new[o + i]; mo[j] = m_old[o + i]; gn[j] = g_new[o + i]; go[j] = g_old[o + i];
+            const long long i = i0 + j * LB_THREADS;
+            if (!tail || i < n) {
+                mn[j] = m_new[o + i]; mo[j] = m_old[o + i]; gn[j] = g_new[o + i]; go[j] = g_old[o + i];
+            }
         }
 #pragma unroll
         for (int j = 0; j < NL; ++j) {
             const long long i = i0 + j * LB_THREADS;
-            if (i >= n) break;
-            const float si = mn[j] - mo[j], yi = gn[j] - go[j];
-            s[i] = si;
-            if (ONE || i >= 4 * nb) y[i] = yi;
-            ys += (double)yi * si;
-            yy += (double)yi * yi;
+            if (!tail || i < n) {
+                const float si = mn[j] - mo[j], yi = gn[j] - go[j];
+                s[i] = si;
+                if (ONE || i >= 4 * nb) y[i] = yi;
+                sum[0] += (double)yi * si;
+                sum[1] += (double)yi * yi;
+            }
         }
-    }
-    ys = block_sum(ys, red);
-    yy = block_sum(yy, red);
+    };
+    long long i0 = blk * (long long)(NL * LB_THREADS) + threadIdx.x;
+    for (; i0 + (NL - 1) * LB_THREADS < n; i0 += step) run(i0, std::false_type());
+    if (i0 < n) run(i0, std::true_type());
+    block_sums(sum, red);
     if (threadIdx.x == 0) {
         if constexpr (ONE) {
-            ysyy[2 * ((long long)k * nmodels + b)] = ys;
-            ysyy[2 * ((long long)k * nmodels + b) + 1] = yy;
+            ysyy[2 * ((long long)k * nmodels + b)] = sum[0];
+            ysyy[2 * ((long long)k * nmodels + b) + 1] = sum[1];
         } else {
-            put_f64(y + 4 * blk, ys);
-            put_f64(y + 4 * blk + 2, yy);
+            put_f64(y + 4 * blk, sum[0]);
+            put_f64(y + 4 * blk + 2, sum[1]);
         }
     }
 }
@@ -108,20 +152,19 @@ __global__ __launch_bounds__(LB_THREADS) void lbfgs_pair_kernel(int nmodels, lon
                                                                 const int *slot, const float *g_new,
                                                                 const float *g_old, float *Y, double *ysyy)
 {
-    __shared__ double red[LB_THREADS / 64];
+    __shared__ double red[2][LB_THREADS / 64];
     const int b = blockIdx.x;
     const int k = slot[b];
     if (k < 0 || k >= mem) return;
     const long long o = (long long)b * n;
     float *y = Y + ((long long)k * nmodels + b) * n;
     const int t = threadIdx.x;
-    double ys = t < nb ? get_f64(y + 4 * t) : 0.0, yy = t < nb ? get_f64(y + 4 * t + 2) : 0.0;
-    ys = block_sum(ys, red);
-    yy = block_sum(yy, red);              // its barriers: every partial sum has been read
+    double sum[2] = {t < nb ? get_f64(y + 4 * t) : 0.0, t < nb ? get_f64(y + 4 * t + 2) : 0.0};
+    block_sums(sum, red);                 // its barrier: every partial sum has been read
     for (int i = t; i < 4 * nb; i += LB_THREADS) y[i] = g_new[o + i] - g_old[o + i];
     if (t == 0) {
-        ysyy[2 * ((long long)k * nmodels + b)] = ys;
-        ysyy[2 * ((long long)k * nmodels + b) + 1] = yy;
+        ysyy[2 * ((long long)k * nmodels + b)] = sum[0];
+        ysyy[2 * ((long long)k * nmodels + b) + 1] = sum[1];
     }
 }
 
@@ -356,7 +399,7 @@ __global__ __launch_bounds__(LB_THREADS) void lbfgs_direction_kernel(int nmodels
                                                                      const float *Y, const double *ysyy,
                                                                      const float *g, float *p)
 {
-    __shared__ double red[LB_THREADS / 64];
+    __shared__ double red[1][LB_THREADS / 64];
     __shared__ double alpha[LB_MAXMEM];
     const int b = blockIdx.x;
     const int newest = hist[2 * b + 1];
@@ -369,10 +412,10 @@ __global__ __launch_bounds__(LB_THREADS) void lbfgs_direction_kernel(int nmodels
     for (int j = 0; j < count; ++j) {
         const int k = slot_of(j);
         const float *s = S + ((long long)k * nmodels + b) * n, *y = Y + ((long long)k * nmodels + b) * n;
-        double sq = 0.0;
-        for (long long i = threadIdx.x; i < n; i += LB_THREADS) sq += (double)s[i] * q[i];
-        sq = block_sum(sq, red);
-        const double a = sq / ysyy[2 * ((long long)k * nmodels + b)];
+        double sq[1] = {0.0};
+        for (long long i = threadIdx.x; i < n; i += LB_THREADS) sq[0] += (double)s[i] * q[i];
+        block_sums(sq, red);
+        const double a = sq[0] / ysyy[2 * ((long long)k * nmodels + b)];
         if (threadIdx.x == 0) alpha[j] = a;
         const float af = (float)a;
         for (long long i = threadIdx.x; i < n; i += LB_THREADS) q[i] -= af * y[i];
@@ -388,10 +431,10 @@ __global__ __launch_bounds__(LB_THREADS) void lbfgs_direction_kernel(int nmodels
     for (int j = count - 1; j >= 0; --j) {
         const int k = slot_of(j);
         const float *s = S + ((long long)k * nmodels + b) * n, *y = Y + ((long long)k * nmodels + b) * n;
-        double yr = 0.0;
-        for (long long i = threadIdx.x; i < n; i += LB_THREADS) yr += (double)y[i] * q[i];
-        yr = block_sum(yr, red);
-        const double beta = yr / ysyy[2 * ((long long)k * nmodels + b)];
+        double yr[1] = {0.0};
+        for (long long i = threadIdx.x; i < n; i += LB_THREADS) yr[0] += (double)y[i] * q[i];
+        block_sums(yr, red);
+        const double beta = yr[0] / ysyy[2 * ((long long)k * nmodels + b)];
         const float c = (float)(alpha[j] - beta);
         for (long long i = threadIdx.x; i < n; i += LB_THREADS) q[i] += c * s[i];
         __syncthreads();
@@ -418,16 +461,19 @@ int lbfgs_push(int32_t nmodels, int64_t n, int32_t mem, const int32_t *slot, con
     if (!slot || !m_new || !m_old || !g_new || !g_old || !S || !Y || !ysyy)
         return fail(SG_EINVAL, "NULL pointer argument");
     hipStream_t st = (hipStream_t)stream;
-    // short vectors: one workgroup per model forms the pair and its sums
-    // (10201 elements: two launches would cost more than they spread).  So do pairs
-    // formed in place, in an S or Y that holds one of the inputs: the partial sums
-    // of several workgroups and their replacement would read what they have overwritten.
+    // Up to PUSH_ONE elements one workgroup per model forms the pair and its sums
+    // (models x elements, inputs in the L2 / in memory, us, one workgroup / several:
+    // 1 x 20000 6.2 / 8.4, 7.4 / 7.7; 200 x 20000 16.2 / 19.3, 23.3 / 25.7; 20 x 40000
+    // 11.3 / 8.6, 21.7 / 9.7; 200 x 40000 30.5 / 32.0, 43.9 / 43.2; 2 x 500000 128 / 8.6,
+    // 215 / 10.6).  So do pairs formed in place, in an S or Y that holds one of the
+    // inputs: the partial sums of several workgroups and their replacement would read
+    // what they have overwritten.
     bool in_place = false;
     for (const float *in : {m_new, m_old, g_new, g_old})
         for (const float *out : {S, Y})
             in_place |= overlap(in, (long long)nmodels * n, out, (long long)mem * nmodels * n);
     const int nb = (int)std::min<long long>((n + 4 * LB_THREADS - 1) / (4 * LB_THREADS), LB_CHUNKS);
-    if (n <= 16 * LB_THREADS || (long long)nmodels * nb * LB_THREADS > MAX_THREADS || in_place) {
+    if (n <= PUSH_ONE || (long long)nmodels * nb * LB_THREADS > MAX_THREADS || in_place) {
         lbfgs_push_kernel<true><<<nmodels, LB_THREADS, 0, st>>>(nmodels, n, mem, 1, slot, m_new, m_old, g_new, g_old,
                                                                 S, Y, ysyy);
     } else {

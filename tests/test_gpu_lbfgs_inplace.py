@@ -1,6 +1,7 @@
-"""GPU: lbfgs_push forms a pair in place, in history slots that hold the old
-model and gradient (elementwise differences), below and above the length from
-which several workgroups share a pair."""
+"""GPU: lbfgs_push forms a pair apart from its inputs or in place, in history
+slots that hold a model and a gradient (elementwise differences), at the ends
+of a workgroup's runs of elements and below and above the length from which
+several workgroups share a pair."""
 import pytest
 import torch
 
@@ -9,8 +10,8 @@ from gpu_common import S
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n", [16384, 16385, 20000])
-@pytest.mark.parametrize("where", ["old", "new"])
+@pytest.mark.parametrize("n", [1, 1024, 3073, 4096, 4097, 16384, 16385, 20000, 24576, 24577, 32768, 32769, 40001])
+@pytest.mark.parametrize("where", ["old", "new", "apart"])
 def test_pair_in_place(n, where):
     mem, k = 3, 1
     gen = torch.Generator(device="cuda").manual_seed(n)
@@ -20,7 +21,7 @@ def test_pair_in_place(n, where):
     ysyy = torch.zeros(mem, 1, 2, dtype=torch.float64, device="cuda")
     s, y = m_new - m_old, g_new - g_old
     a = [m_new, m_old, g_new, g_old]
-    for i, h in ((1, Sh), (3, Y)) if where == "old" else ((0, Sh), (2, Y)):
+    for i, h in {"old": ((1, Sh), (3, Y)), "new": ((0, Sh), (2, Y)), "apart": ()}[where]:
         h[k] = a[i]
         a[i] = h[k]
     keep = Sh[::2].clone(), Y[::2].clone()
