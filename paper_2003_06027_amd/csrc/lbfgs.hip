@@ -442,6 +442,27 @@ __global__ __launch_bounds__(LB_THREADS) void lbfgs_direction_kernel(int nmodels
     for (long long i = threadIdx.x; i < n; i += LB_THREADS) q[i] = -q[i];
 }
 
+// Is the direction of c pairs faster by products over the whole chip than by
+// one workgroup per model?  Estimates in us fitted to 1 .. 4000 models of 600 ..
+// 500000 elements.  The loop: a chain of reductions per pair and model, about
+// 400 models at a time, and its traffic, from memory once the vectors of the
+// models at work exceed the last-level cache.  The products: three launches, and the
+// FP64 matrix cores' rate, which has one of few pairs pay for 16 columns.
+// Measured, loop / products, by models x elements and pairs: 1 x 2000, 3 10.4 / 12.3,
+// 5 14.6 / 12.9; 20 x 10201, 8 47 / 15; 200 x 10000, 2 30.5 / 44.9; 100 x 20000, 1 30 / 43,
+// 5 117 / 53; 1000 x 40000, 1 392 / 620; 1000 x 6000, 5 145 / 149; 1000 x 2000, 8 80 / 77;
+// 400 x 20000, 5 292 / 192; 1000 x 3000, 15 241 / 198; 1 x 500000, 1 729 / 41.
+bool products_faster(int nmodels, long long n, int c)
+{
+    const double e = 1e-5 * nmodels * n;
+    const bool cached = (2.0 * c + 2.0) * 4.0 * std::min(nmodels, 512) * n <= 128e6;
+    const double per_element = 0.6e-3 * std::min(2.4, 1.0 + n / 60000.0);
+    const double loop = 1.06 * (3.0 + c * (1.0 + per_element * n)) * std::max(1.0, nmodels / 400.0) +
+                        e * (cached ? 0.3 + 0.13 * c : 0.5 + 0.45 * c);
+    const double products = 12.0 + 6e-3 * nmodels + (c > 8 ? 6.0 + e * (1.0 + 0.33 * c) : e * (1.25 + 0.2 * c));
+    return products < loop;
+}
+
 // Do n floats at a and m at b share memory?
 bool overlap(const float *a, long long n, const float *b, long long m)
 {
@@ -494,12 +515,10 @@ int lbfgs_direction(int32_t nmodels, int64_t n, int32_t mem, const int32_t *hist
     if (!hist || !S || !Y || !ysyy || !g || !p) return fail(SG_EINVAL, "NULL pointer argument");
     if (p == g) return fail(SG_EINVAL, "p must not alias g");
     hipStream_t st = (hipStream_t)stream;
-    // The products over the whole chip where p has room for two chunks' partial
-    // sums; long histories and short loops keep one workgroup per model (push +
-    // direction, loop / products: 2500 elements, 5 pairs 27.2 / 28.3 us; 1000, 8
-    // 31.9 / 27.4; 6000, 5 38.8 / 28.7; both launches near the host's rate).
+    // The products where they are faster and p has room for two chunks' partial
+    // sums; longer histories keep one workgroup per model.
     const int per = 2 * lb_dots(std::min<int>(mem, LB_CMAX));     // floats of a chunk's partial sums
-    const bool room = mem <= LB_CMAX && n >= LB_HEAD + 2 * per && mem * (n + 3000) >= 30000;
+    const bool room = mem <= LB_CMAX && n >= LB_HEAD + 2 * per && products_faster(nmodels, n, mem);
     const long long want = room ? std::min<long long>({(n + LB_SUB - 1) / LB_SUB, (n - LB_HEAD) / per, LB_CHUNKS}) : 1;
     const long long chunk = ((n + want - 1) / want + LB_SUB - 1) / LB_SUB * LB_SUB;
     const int nchunks = (int)((n + chunk - 1) / chunk);
