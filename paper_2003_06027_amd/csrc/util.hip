@@ -60,18 +60,23 @@ void launch_copy_fields(const CopyFields &c, long long n, hipStream_t s)
 
 // Fold the padded cells of 2-D models onto the physical cells that they
 // replicate: each cell's sum over its padded cells in z, x order, times
-// dchat/dc = 2 dt^2 c / dx^2 if cpad is given.  A workgroup per row: two
-// wavefronts the columns between the ends, one each end cell, whose P + 1
+// dchat/dc = 2 dt^2 c / dx^2 if cpad is given.  A workgroup per row and run of
+// `cols` of the columns between the ends: all four wavefronts the columns, in the
+// first run two of them, and one each end cell, whose P + 1
 // (corner: (P + 1)^2) cells it loads 64 at a time and adds up lane by lane (a
 // thread that loaded and added them one by one took 38 us for P = 20, 84 us
-// for P = 32; now 15 for P = 20).
-__global__ __launch_bounds__(256) void fold2_kernel(Grid2 g, const float *acc, const float *cpad, double dt, double dx,
-                                                    float *out)
+// for P = 32; now 14 and 30).  Long rows are cut so that a few of them fill the
+// chip as well (16000 x 64, P = 20: a thread per cell 43 us, a workgroup per
+// whole row 275, now 15).
+// m0, iz0: model and row of the first workgroup.
+__global__ __launch_bounds__(256) void fold2_kernel(Grid2 g, int m0, int iz0, int cols, const float *acc,
+                                                    const float *cpad, double dt, double dx, float *out)
 {
     constexpr int U = 8;                   // loads in flight
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const long long m = blockIdx.x / g.nz;
-    const int iz = (int)(blockIdx.x - m * g.nz);
+    const unsigned r = iz0 + blockIdx.x, dm = r / g.nz;
+    const long long m = m0 + (int)dm;
+    const int iz = (int)(r - dm * g.nz);
     const int zlo = iz == 0 ? 0 : iz + g.P, zhi = iz == g.nz - 1 ? g.NZ - 1 : iz + g.P;
     const float *am = acc + m * g.plane;
     auto at = [&](int pz, int px) { return (long long)(pz + OZ) * g.SX + px + OX; };
@@ -82,10 +87,12 @@ __global__ __launch_bounds__(256) void fold2_kernel(Grid2 g, const float *acc, c
         }
         out[(m * g.nz + iz) * g.nx + ix] = v;
     };
-    if (wv >= 2) {
-        for (int ix = 1 + (wv - 2) * 64 + lane; ix < g.nx - 1; ix += 128) {
+    if (blockIdx.y > 0 || wv >= 2) {
+        const int waves = blockIdx.y > 0 ? 4 : 2, x0 = 1 + blockIdx.y * cols, x1 = min(x0 + cols, g.nx - 1);
+        for (int ix = x0 + (wv + waves - 4) * 64 + lane; ix < x1; ix += waves * 64) {
             float v = 0.f;
-            for (int p0 = zlo; p0 <= zhi; p0 += U) {
+            if (zlo == zhi) v += am[at(zlo, ix + g.P)];
+            else for (int p0 = zlo; p0 <= zhi; p0 += U) {
                 float x[U];
 #pragma unroll
                 for (int u = 0; u < U; ++u) x[u] = am[at(min(p0 + u, zhi), ix + g.P)];
@@ -128,12 +135,13 @@ __global__ __launch_bounds__(256) void fold2_kernel(Grid2 g, const float *acc, c
 void launch_fold2(const Grid2 &g, int nmodels, const float *acc, const float *cpad, double dt, double dx, float *out,
                   hipStream_t s)
 {
-    for (int m0 = 0; m0 < nmodels;) {      // a launch's workgroups are an int
-        const int k = (int)std::min<long long>(nmodels - m0, std::max(1, (1 << 30) / g.nz));
-        fold2_kernel<<<(unsigned)(k * g.nz), 256, 0, s>>>(g, acc + m0 * g.plane, cpad ? cpad + m0 * g.plane : nullptr, dt,
-                                                          dx, out + (long long)m0 * g.nz * g.nx);
-        m0 += k;
-    }
+    const long long rows = (long long)nmodels * g.nz;
+    const int most = (int)std::max(1ll, std::min<long long>(g.nx / 128, 2048 / rows));
+    const int cols = std::max(1, (g.nx - 2 + most - 1) / most), runs = std::max(1, (g.nx - 2 + cols - 1) / cols);
+    constexpr long long R = 1 << 23;       // a launch holds fewer than 2^32 threads on an axis
+    for (long long row0 = 0; row0 < rows; row0 += R)
+        fold2_kernel<<<dim3((unsigned)std::min(R, rows - row0), runs), 256, 0, s>>>(g, (int)(row0 / g.nz), (int)(row0 % g.nz), cols,
+                                                                                    acc, cpad, dt, dx, out);
 }
 
 // Ricker wavelet r(t) = (1 - 2 a) exp(-a), a = (pi f0 (t - t0))^2, in FP64.
