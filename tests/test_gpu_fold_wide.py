@@ -9,10 +9,10 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("nx,nz,P,models,spm", [
-    (255, 5, 4, 1, 1),             # one run
-    (256, 5, 4, 1, 1),             # two runs of 127 columns
-    (385, 4, 6, 2, 1),             # three, the last of 127
-    (1500, 6, 5, 1, 2),            # eleven of 137
+    (255, 5, 8, 1, 1),             # one run
+    (256, 5, 8, 1, 1),             # two runs of 127 columns
+    (385, 4, 8, 2, 1),             # three, the last of 127
+    (1500, 6, 7, 1, 2),            # eleven of 137
     (700, 1, 0, 1, 1),
 ])
 def test_runs_of_columns(nx, nz, P, models, spm):
