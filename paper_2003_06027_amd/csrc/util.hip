@@ -255,7 +255,9 @@ void launch_dot(const float *x, const float *y, long long n, double *out, hipStr
 // checks fail.  Bound by the one read of the fields: 400^3 cells (256 MB) in
 // 58 us, 128^3 in 16 (with two atomics per wavefront on the one result 158 and
 // 97), where copying them to the host and looping over them took about 110 ms
-// of every init_model and update_model.
+// of every init_model and update_model.  A small model is one workgroup's, with
+// nothing to clear before it (update_model of 16 x 16 cells, host loop / two launches /
+// one: 27.5 / 32.1 / 30.0 us).
 __global__ __launch_bounds__(256) void range_kernel(const float *vp, const float *vs, const float *rho, long long n,
                                                     ParamRange *out)
 {
@@ -293,7 +295,9 @@ __global__ __launch_bounds__(256) void range_kernel(const float *vp, const float
         top = fmaxf(top, __shfl_down(top, o, 64));
         bad |= __shfl_down(bad, o, 64);
     }
-    if (threadIdx.x == 0) {
+    if (threadIdx.x == 0 && gridDim.x == 1) {
+        *out = ParamRange{__float_as_uint(top), bad};
+    } else if (threadIdx.x == 0) {
         atomicMax(&out->vmax_bits, __float_as_uint(top));
         if (bad) atomicOr(&out->bad, bad);
     }
@@ -303,8 +307,8 @@ void launch_param_range(const float *vp, const float *vs, const float *rho, long
                         hipStream_t s)
 {
     static_assert(sizeof(ParamRange) == 2 * sizeof(float), "cleared as floats");
-    launch_fill(reinterpret_cast<float *>(out), 2, 0.f, s);
-    const int blocks = (int)std::min<long long>((n + 2047) / 2048, 1024);
+    const int blocks = n <= 8192 ? 1 : (int)std::min<long long>((n + 2047) / 2048, 1024);
+    if (blocks > 1) launch_fill(reinterpret_cast<float *>(out), 2, 0.f, s);
     range_kernel<<<blocks, 256, 0, s>>>(vp, vs, rho, n, out);
 }
 
