@@ -481,7 +481,10 @@ constexpr int rows1(int RW) { return RW + 8; }
 constexpr int nring(int RW) { return rows1(RW) * W1 - RW * TX; }
 // The forward blocked tiles take NTB threads (RB rows each): 8 waves per
 // SIMD in 55 VGPRs against 5 at 256 threads (C2: 141 -> 136 us per launch).
-// The adjoint keeps 256 threads (512 ran 2 % slower).
+// The blocked adjoint takes 256 threads in a launch of its own (512 ran 2 %
+// slower: 195 -> 199 us) and the step's 512 in one grid with the tiles by the layer,
+// where what the shared grid saves is more (64 shots, whole pass: 454 us per step
+// apart, 451 so).
 constexpr int NTB = 512;
 static_assert(8 * TX % NTB == 0 && NTB % TX == 0, "whole rows per thread");
 

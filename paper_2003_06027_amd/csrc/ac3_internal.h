@@ -12,7 +12,7 @@ namespace sg {
 // layer work list), between TZC_MIN and TZC planes; the defaults are below:
 // the forward passes take shorter chunks than the adjoint, whose longer
 // march re-reads fewer window planes.  The layer items are the shortest: a
-// march is a serial chain of about 0.6 us per plane, and the items hold the
+// march is a serial chain of about 0.6 us per plane (the tile passes': 1), and the items hold the
 // little work that is left when the chip is not full (per step, 32 -> 16
 // planes: 128^3 + 20-cell layer forward 130 -> 110 us, 400^3 + 24 cells 742 -> 736 us).
 constexpr int TX3 = 32;

@@ -38,13 +38,17 @@
 
 // Multiply-adds are fused only where written as fmaf: whether the compiler
 // would fuse the others depends on the rows per workgroup, and a shot's
-// values must not.  Where a product is rounded is part of those values: ahead of
-// a wavefront they are differences of denormal numbers, which another rounding
-// changes in their leading digits.  It follows groups of four rows of a 32-row
-// tile: a row's place in its group (0 .. 3) and a half row's (M = 0 .. 6, from two
-// above the first row), whatever rows a thread takes.  1000x500, 64 shots, against
-// every product rounded: forward 247 -> 251 us, recompute 272 -> 274, adjoint 362 ->
-// 365.
+// values must not.  Which products are fused follows groups of four rows of a
+// 32-row tile: a row's place in its group (0 .. 3) and a half row's (M = 0 .. 6,
+// from two above the first row), whatever rows a thread takes.  The only reason
+// for these places is that results stay what they were, bit for bit, with four
+// rows per thread, where the compiler had fused these products: ahead of a
+// wavefront values are differences of denormal numbers, which another rounding
+// changes in their leading digits.  They have no meaning of their own, and one flux
+// is rounded differently for its tile and for the neighbour's extra column.  Every
+// product rounded would be as exact (errors against 64 bits within 2 % of each other)
+// and faster: 1000x500, 64 shots, forward 247 against 251 us, recompute 272 / 274,
+// adjoint 362 / 365.
 #pragma clang fp contract(off)
 
 namespace sg {
@@ -68,7 +72,7 @@ namespace {
 // nodes by the layer (a load behind the previous node's stores: 3 us of an
 // 11 us launch).  300 x 150 + 20-cell layer, late -> early: 1 shot 20.7 -> 16.0 us
 // per step, 4 shots 27.0 -> 22.7; 9 shots, 648 workgroups, 33.0 -> 34.2.
-// 1000 x 500 + 32-cell layer, 64 shots (late): 1066.
+// 1000 x 500 + 32-cell layer, 64 shots (late): 890.
 //
 // A thread's rows are uniform over its wavefront (TX lanes); taken through
 // readfirstlane, they put the z tables in scalar registers.
@@ -270,7 +274,7 @@ struct Coefs {
 // r0 = ly*RPA .. r0+RPA-1.  The z fluxes of its column (its own half rows and
 // the three around them that its Dm' needs) are computed in registers from
 // its column of the u tile; the x fluxes go through LDS (own half column by
-// every thread, the three extra columns x0-2, x0-1, x0+TX by the first 3*TZ
+// every thread, the three extra columns x0-2, x0-1, x0+TX by the first 3*RW
 // threads).  chat of the own column is read once per thread; the right
 // neighbour's comes from the next lane (one wavefront = one tile row).  The
 // z part runs first so that only Hz and u^k of the own rows stay live.

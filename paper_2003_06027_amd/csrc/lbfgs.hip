@@ -177,8 +177,8 @@ __global__ __launch_bounds__(LB_THREADS) void lbfgs_pair_kernel(int nmodels, lon
 // and p = -(gamma (g - sum alpha_j y_j) + sum (alpha_j - beta_j) s_j).  The
 // vectors are read twice, by every CU, instead of once per loop step by one
 // workgroup whose every step waits for the reduction before it (push +
-// direction, 8 pairs: 20 models of 10201 elements 76 -> 27 us, 200 models 129 ->
-// 82 us, one model of 500000 4.85 ms -> 45 us).
+// direction, 8 pairs: 20 models of 10201 elements 77 -> 25 us, 200 models 129 ->
+// 78 us, one model of 500000 4.82 ms -> 68 us).
 // The products are summed per chunk of elements and then over the chunks in
 // order.  The partial sums and then the coefficients live in p, which is
 // written last: the coefficients in its first LB_HEAD floats, whose elements

@@ -109,10 +109,9 @@ int check_desc(const sg_desc *d)
     return SG_OK;
 }
 
-// Shot-count limits of the elastic launches: the adjoint passes take the shot
-// (group) as the grid's y index (at most 65535); the forward passes number
-// (cell block, shot group) in a 1-D grid of int work ids, at most
-// el2_cell_blocks * max_shots of them (shot groups of one, either block width).
+// Shot-count limits of the elastic launches: every pass numbers (cell block,
+// shot group) in a 1-D grid of int work ids, at most el2_cell_blocks * max_shots
+// of them (shot groups of one, either block width); at most 65535 shots besides.
 int check_shots(const sg_desc *d, int max_shots)
 {
     if (d->physics != SG_ELASTIC) return SG_OK;
