@@ -76,11 +76,14 @@ TRAFFIC_FILES = {   # workload -> committed counter summary, the kernel sources 
 }
 
 
-def measured_traffic(phase, workload="c2"):
+def measured_traffic(phase, workload="c2", settings="default"):
     """HBM bytes per step of `phase` from the committed FETCH_SIZE/WRITE_SIZE
     summary (counters scaled by a plain copy of known size), or None when the
-    kernels' source has changed since the counters were taken."""
+    kernels' source has changed since the counters were taken, or the run's
+    launch settings are not the default ones that they were taken with."""
     import hashlib
+    if settings != "default":
+        return None
     name, files = TRAFFIC_FILES[workload]
     path = os.path.join(ROOT, "profiles", name)
     src = os.path.join(ROOT, "paper_2003_06027_amd", "csrc")
@@ -325,7 +328,7 @@ def measure(a, S, synth, torch):
     value = updates / T / 1e9
     pml_frac = 1.0 - cfg.nx * cfg.ny * cfg.nz / cells
     if wl == "c3":
-        bpc = bytes_per_cell_step_el2(pml_frac, el2_group(ns // d.nmodels))
+        bpc = bytes_per_cell_step_el2(pml_frac, strategy.shot_group or el2_group(ns // d.nmodels))
     else:
         bpc = (bytes_per_cell_step_div if div else bytes_per_cell_step_ac3 if wl == "c4"
                else bytes_per_cell_step)(pml_frac)
@@ -339,7 +342,7 @@ def measure(a, S, synth, torch):
                     "alg_bytes_per_cell": round(bpc[name], 3), "gbs": round(gbs, 1),
                     "frac_hbm": round(gbs / HBM_PEAK_GBS, 4)}
     dom = max(ph, key=lambda k: phases[k][0])
-    traffic = measured_traffic(dom, "div" if div else wl)   # HBM bytes per step (all launches)
+    traffic = measured_traffic(dom, "div" if div else wl, strategy.label())   # HBM bytes per step (all launches)
     out = {
         "metric": METRIC, "value": round(value, 3), "unit": "Gcell-updates/s", "n_gpus": 1,
         "steps": a.steps, "warmup": a.warmup, "ms_per_step": round(T * 1e3, 3),
