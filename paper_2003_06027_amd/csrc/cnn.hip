@@ -30,6 +30,7 @@ namespace {
 using u16 = unsigned short;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));   // where only floats are aligned
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
 
@@ -477,7 +478,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
             f32x4 v = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int w = 0; w < 4; ++w) v += *(const f32x4 *)(red + ((w * 3 + t) * CH + co) * RS + ci);
-            *(f32x4 *)(out + (co * 9 + t0 + t) * CH + ci) = v;
+            *(f32x4u *)(out + (co * 9 + t0 + t) * CH + ci) = v;
         }
         if (t0 == 0 && threadIdx.x < CH) {
             float v = 0.f;
